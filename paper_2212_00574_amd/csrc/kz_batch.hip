@@ -68,12 +68,6 @@ __device__ __forceinline__ unsigned long long bcast64(unsigned long long x, int 
   return ((unsigned long long)hi << 32) | lo;
 }
 
-__device__ __forceinline__ int bsum(int x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-  return x;
-}
-
 __device__ __forceinline__ bool tbit(const unsigned *b, int i) { return (b[i >> 5] >> (i & 31)) & 1u; }
 
 __device__ __forceinline__ unsigned long long lanes_below(int lane) {
@@ -240,7 +234,7 @@ __device__ void vertex_chunk(const GView &V, BatchLds &S, int v0, bool first, in
     if (first) V.valive[v] = fail ? 0 : 1;
     else if (fail) V.valive[v] = 0;
   }
-  const int nf = bsum(fail ? 1 : 0);
+  const int nf = wave_sum(fail ? 1 : 0);
   if (lane == 0 && nf) atomicAdd(&S.removed_v, (unsigned long long)nf);
 }
 
@@ -381,7 +375,7 @@ __device__ void tile(const GView &V, BatchLds &S, int X, int Y, bool first, int 
     if (lane < yl) V.nxt[(long long)(ys + lane) * R + X] = newET;
     if (chU) atomicOr(&S.tn[(xs + lane) >> 5], 1u << ((xs + lane) & 31));
     if (chV) atomicOr(&S.tn[(ys + lane) >> 5], 1u << ((ys + lane) & 31));
-    const int rem = bsum(lane < xl ? __popcll(Eu & ~Pu) : 0);
+    const int rem = wave_sum(lane < xl ? __popcll(Eu & ~Pu) : 0);
     if (lane == 0) {
       if (bu) atomicOr(&S.btn[X >> 5], 1u << (X & 31));
       if (bv) atomicOr(&S.btn[Y >> 5], 1u << (Y & 31));
@@ -390,7 +384,7 @@ __device__ void tile(const GView &V, BatchLds &S, int X, int Y, bool first, int 
       atomicAdd(&S.removed_e, (unsigned long long)rem);
     }
   }
-  const int cnt = bsum(lane < xl ? __popcll(Eu & (((TU >> lane) & 1ull) ? ~0ull : TV)) : 0);
+  const int cnt = wave_sum(lane < xl ? __popcll(Eu & (((TU >> lane) & 1ull) ? ~0ull : TV)) : 0);
   if (lane == 0 && cnt) atomicAdd(&S.tests, (unsigned long long)cnt);
 }
 

@@ -24,12 +24,6 @@ namespace {
 
 __device__ __forceinline__ bool csr_bad(const Hdr *h) { return (h->bad_colour | h->bad_layout) != 0; }
 
-__device__ __forceinline__ int wave_sum_i(int x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-  return x;
-}
-
 // Adds two per-wave counts into counter slots (par, slot, j0) and (par,
 // slot, j1) with one atomic each per workgroup of 4 waves: the counter lines
 // take one update per workgroup instead of one per wave.  Every thread of the
@@ -37,8 +31,8 @@ __device__ __forceinline__ int wave_sum_i(int x) {
 __device__ __forceinline__ void wg_add2(Hdr *h, int par, int j0, long long a, int j1, long long b) {
   __shared__ long long sRed[4][2];
   const int wv = threadIdx.x >> 6;
-  a = (long long)wave_sum_i((int)a);
-  b = (long long)wave_sum_i((int)b);
+  a = (long long)wave_sum((int)a);
+  b = (long long)wave_sum((int)b);
   if ((threadIdx.x & 63) == 0) {
     sRed[wv][0] = a;
     sRed[wv][1] = b;

@@ -14,8 +14,8 @@ namespace kzi {
 constexpr int kWave = 64;          // CDNA wavefront
 constexpr int kBlk = 64;           // slots per block == bits per word
 constexpr int kEdgeThreads = 256;  // edge pass: 4 waves per workgroup
-constexpr long long kEdgeWaveTiles = 16384;  // tiles from which the edge pass gives a tile one wave, not four
-constexpr int kEdgeSquare = 16;              // then the side of its squares of tiles (in blocks)
+constexpr long long kEdgeSquareTiles = 16384;  // tiles from which the edge pass orders them in squares
+constexpr int kEdgeSquare = 8;                 // the side of those squares, in groups of 2 x 2 tiles
 constexpr int kMfThreads = 256;    // MFMA count path: 4 waves per 128x128 group tile
 constexpr int kMfMaxWords = 2048;  // MFMA count path: row words it supports
 constexpr int kRankChunk = 256;    // vertices per stable-partition chunk
@@ -31,22 +31,57 @@ constexpr int kCtrStride = 16;     // words per counter slot: 4 per pass parity,
 // stage-2 status priorities (largest wins)
 enum : int { P_NONE = 0, P_EILLEGAL = 1, P_EASYM = 2, P_ESELFLOOP = 3, P_EINVAL = 4 };
 
+// A lane's 32-bit value from the lane CTRL names (data-parallel primitives:
+// vector-ALU latency, no LDS round trip).
+template <int CTRL>
+__device__ __forceinline__ unsigned dpp(unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
+constexpr int kDppRor = 0x120;         // + r: rotate by r lanes within 16
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor3 = 0x1B;  // quad permutations
+constexpr int kDppHalfMirror = 0x141;  // lane ^ 7
+
+// Sum over the wave, the same in every lane: rotations add up each 16 lanes,
+// four scalar reads the wave.
+__device__ __forceinline__ int wave_sum(int v) {
+  unsigned x = (unsigned)v;
+  x += dpp<kDppRor + 8>(x);
+  x += dpp<kDppRor + 4>(x);
+  x += dpp<kDppRor + 2>(x);
+  x += dpp<kDppRor + 1>(x);
+  return __builtin_amdgcn_readlane((int)x, 0) + __builtin_amdgcn_readlane((int)x, 16) +
+         __builtin_amdgcn_readlane((int)x, 32) + __builtin_amdgcn_readlane((int)x, 48);
+}
+
 // Transposes a 64x64 bit matrix held one row per lane (lane l holds row l,
 // bit b = column b): returns row l of the transpose, i.e. bit b of the
 // result is bit l of lane b's input.  Six butterfly stages: at stage j,
 // lanes l and l^j swap the j-wide column groups on the wrong side of the
-// diagonal.  Every lane of the wave must take part.
-__device__ __forceinline__ unsigned long long wave_transpose64(unsigned long long x, int lane) {
-  constexpr unsigned long long kM[6] = {0xFFFFFFFF00000000ull, 0xFFFF0000FFFF0000ull, 0xFF00FF00FF00FF00ull,
-                                        0xF0F0F0F0F0F0F0F0ull, 0xCCCCCCCCCCCCCCCCull, 0xAAAAAAAAAAAAAAAAull};
+// diagonal.  The stages of 32 and 16 are lane swaps, those of 16 and 8 byte
+// permutes, the others a rotate and a bit select per 32 bits.  Every lane of
+// the wave must take part.
+__device__ __forceinline__ unsigned long long wave_transpose64(unsigned long long v, int lane) {
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)(v >> 32), false, false);
+  unsigned x[2] = {h[0], h[1]};
+  const unsigned s16 = (lane & 16) ? 0x07060302u : 0x05040100u;  // bytes of (y, x): 4..7 are y's
+  const unsigned s8 = (lane & 8) ? 0x03070105u : 0x06020400u;
+  const unsigned m4 = (lane & 4) ? 0x0F0F0F0Fu : 0xF0F0F0F0u, r4 = (lane & 4) ? 4u : 28u;
+  const unsigned m2 = (lane & 2) ? 0x33333333u : 0xCCCCCCCCu, r2 = (lane & 2) ? 2u : 30u;
+  const unsigned m1 = (lane & 1) ? 0x55555555u : 0xAAAAAAAAu, r1 = (lane & 1) ? 1u : 31u;
 #pragma unroll
-  for (int st = 0; st < 6; ++st) {
-    const int j = 32 >> st;
-    const unsigned long long m = kM[st];
-    const unsigned long long y = (unsigned long long)__shfl_xor((long long)x, j, kWave);
-    x = (lane & j) ? ((x & m) | ((y & m) >> j)) : ((x & ~m) | ((y & ~m) << j));
+  for (int i = 0; i < 2; ++i) {
+    const auto q = __builtin_amdgcn_permlane16_swap(x[i], x[i], false, false);
+    unsigned z = __builtin_amdgcn_perm(q[1], q[0], s16);
+    z = __builtin_amdgcn_perm(dpp<kDppRor + 8>(z), z, s8);
+    unsigned y = dpp<kDppXor3>(dpp<kDppHalfMirror>(z));  // lane ^ 4
+    z = (m4 & __builtin_amdgcn_alignbit(y, y, r4)) | (~m4 & z);
+    y = dpp<kDppXor2>(z);
+    z = (m2 & __builtin_amdgcn_alignbit(y, y, r2)) | (~m2 & z);
+    y = dpp<kDppXor1>(z);
+    z = (m1 & __builtin_amdgcn_alignbit(y, y, r1)) | (~m1 & z);
+    x[i] = z;
   }
-  return x;
+  return ((unsigned long long)x[1] << 32) | x[0];
 }
 
 // Device-resident header at the start of the workspace.
@@ -99,8 +134,6 @@ struct Plan {
   uint64_t *F;       // [n*kF] F[slot*kF + c]: the first word of the slot's class-c segment
                      // (0 for an empty class); all-ones for the slot's own class and
                      // for c >= k (so those classes never fail a first-word test)
-  uint64_t *S;       // [n*kF] S[slot*kF + c]: the second word of the slot's class-c segment
-                     // (0 where the segment is shorter)
   uint64_t *fb;      // [n*Rmax] MFMA count path: fail bits of the pairs of a pass
   int32_t *src;      // [nnz] csr: row of every entry
   uint8_t *efail;    // [nnz] csr: entry failed the edge test this pass
@@ -109,16 +142,15 @@ struct Plan {
   int n, k, Rmax, nchunks;
   int kF;            // row stride of F: k rounded up to the edge pass's class chunk
   long long Tmax;    // Rmax*(Rmax-1)/2
-  // the edge pass's tile order (set by its launcher): 0 or 1, row-major over
-  // the triangle of block pairs; else squares of Sq x Sq block pairs, the
-  // squares row-major over the triangle of squares, Tcells cells in all
+  // the edge pass's order of its 2 x 2 groups of tiles (set by its launcher):
+  // 0 or 1, row-major over the triangle of groups; else squares of Sq x Sq
+  // groups, the squares row-major over the triangle of squares
   int Sq;
-  long long Tcells;
 };
 
-// Classes per chunk of the bit-row edge test (the rows' first words of a
-// chunk are held in 2*KC registers), and the row stride of F that makes
-// every chunk's load of a row in bounds.
+// Classes per chunk of the bit-row edge test (at most what a workgroup stages
+// at once), and the row stride of F that makes every chunk's load of a row in
+// bounds: a multiple of 4, so rows of F start on 32 bytes.
 __host__ __device__ inline int edge_chunk(int k) { return k <= 4 ? 4 : k <= 32 ? (k + 3) / 4 * 4 : 32; }
 __host__ __device__ inline int f_stride(int k) {
   const int c = edge_chunk(k);
@@ -129,7 +161,7 @@ struct WsSizes {
   size_t total;
   size_t off_counts, off_coff, off_soff, off_bcls, off_bstart, off_blen, off_hist, off_perm,
       off_inv, off_scls, off_valive, off_touched0, off_touched1, off_bt0, off_bt1, off_tiles,
-      off_packed, off_spare, off_F, off_S, off_fb, off_src, off_efail, off_pm;
+      off_packed, off_spare, off_F, off_fb, off_src, off_efail, off_pm;
   int Rmax, nchunks;
   long long Tmax;
 };

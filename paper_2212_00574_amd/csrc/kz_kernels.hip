@@ -22,25 +22,13 @@
 // a dead vertex has an empty row (every edge at a failing vertex fails the
 // edge test in the same round).
 #include "kz_internal.h"
+#include "kz_mx.h"
 
 namespace kzi {
 
 namespace {
 
 __device__ __forceinline__ bool stage1_bad(const Hdr *h) { return (h->bad_colour | h->bad_layout) != 0; }
-
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-  return x;
-}
-
-// A value every lane holds identically, moved to scalar registers.
-__device__ __forceinline__ unsigned long long uniform64(unsigned long long x) {
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)x);
-  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(x >> 32));
-  return ((unsigned long long)hi << 32) | lo;
-}
 
 // Spreads workgroup ids so that each XCD (ids are dealt round-robin to the
 // 8 XCDs) gets one contiguous range of tiles: neighbouring tiles share a
@@ -62,29 +50,6 @@ __device__ __forceinline__ void tri_decode(long long t, int NB, int &X, int &Y) 
   while (x < NB - 2 && start(x + 1) <= t) ++x;
   X = (int)x;
   Y = (int)(t - start(x) + x + 1);
-}
-
-// Tile t of the edge pass.  Row-major over the triangle (p.Sq <= 1), or in
-// squares of Sq x Sq block pairs: the squares (I, J), I <= J, row-major over
-// the triangle of squares with its diagonal, the cells of a square
-// row-major.  The tiles a chip's XCD has in flight then come from a few
-// squares, whose rows and first words fit its L2, instead of from one or
-// two block rows paired with every other block.  Cells with X >= Y or
-// Y >= NB are not tiles: false.
-__device__ __forceinline__ bool tile_decode(long long t, int NB, int Sq, int &X, int &Y) {
-  if (Sq <= 1) {
-    tri_decode(t, NB, X, Y);
-    return true;
-  }
-  const int NS = (NB + Sq - 1) / Sq;
-  const long long sq = t / ((long long)Sq * Sq);
-  const int cell = (int)(t - sq * Sq * Sq);
-  int I, J;
-  tri_decode(sq, NS + 1, I, J);  // (I, J+1) over NS+1 blocks: I <= J over NS
-  J -= 1;
-  X = I * Sq + cell / Sq;
-  Y = J * Sq + cell % Sq;
-  return X < Y && Y < NB;
 }
 
 // ---------------------------------------------------------------- setup
@@ -392,10 +357,7 @@ __global__ void __launch_bounds__(256) k_vertex(Plan p, const int *scls, const u
         if (c >= k) break;
         const int w0 = lds_off ? sOff[c] : p.soff[c];
         const int w1 = lds_off ? sOff[c + 1] : p.soff[c + 1];
-        if (active) {
-          p.F[(long long)v * p.kF + c] = c == cv ? ~0ull : x0[g];
-          p.S[(long long)v * p.kF + c] = x1[g];
-        }
+        if (active) p.F[(long long)v * p.kF + c] = c == cv ? ~0ull : x0[g];
         if (c == cv) continue;
         // an empty class has no words: no neighbour possible
         bool nz = (x0[g] | x1[g]) != 0;
@@ -511,10 +473,7 @@ __global__ void __launch_bounds__(256) k_vertex_first(Plan p, const int *scls, c
   // own class is never empty); F of an empty class is zero
   auto empty_class = [&](int c) {
     sEmpty = 1;
-    for (int r = 0; r < nrows; ++r) {
-      p.F[(long long)(v0 + r) * p.kF + c] = 0ull;
-      p.S[(long long)(v0 + r) * p.kF + c] = 0ull;
-    }
+    for (int r = 0; r < nrows; ++r) p.F[(long long)(v0 + r) * p.kF + c] = 0ull;
   };
   if (lds_off) {
     for (int c = tid; c < k; c += 256)
@@ -564,8 +523,6 @@ __global__ void __launch_bounds__(256) k_vertex_first(Plan p, const int *scls, c
       if (valid) {
         dst[(long long)v * R + w] = xi;
         if (off == 0) p.F[(long long)v * p.kF + cw] = cw == cvr ? ~0ull : xi;
-        if (off == 1) p.S[(long long)v * p.kF + cw] = xi;
-        if (off == 0 && ends) p.S[(long long)v * p.kF + cw] = 0ull;
         if (bl < 64 && (xi >> bl)) pr = max(pr, (int)P_EINVAL);
       }
       const unsigned long long nz = __ballot(valid && xi != 0);
@@ -616,24 +573,10 @@ __global__ void __launch_bounds__(256) k_vertex_first(Plan p, const int *scls, c
   if (lane == 0 && nf) atomicAdd(&h->ctr(cur, blockIdx.x % kCtrSlots, 0), (unsigned long long)nf);
 }
 
-// Reads lane l's 64-bit value into scalar registers.
-__device__ __forceinline__ unsigned long long lane64(unsigned long long x, int l) {
-  const unsigned lo = __builtin_amdgcn_readlane((unsigned)x, l);
-  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(x >> 32), l);
-  return ((unsigned long long)hi << 32) | lo;
-}
-
-// x with lane l's value replaced by the uniform value y.
-__device__ __forceinline__ unsigned long long set_lane64(unsigned long long x, unsigned long long y, int l,
-                                                         int lane) {
-  return lane == l ? y : x;
-}
-
 constexpr int kTileWaves = kEdgeThreads / kWave;  // waves per workgroup of the edge pass
 
 // What a wave knows about its tile (X, Y): blocks of two different classes,
-// lane l standing for row u = xs + l and for row v = ys + l.  A workgroup
-// takes kTileWaves / TW tiles, TW waves each.
+// lane l standing for row u = xs + l and for row v = ys + l.
 struct Tile {
   int X, Y, xs, xl, ys, yl, cx, cy;
   unsigned long long E;   // lane u: row u's word Y (its edges into block Y)
@@ -642,16 +585,15 @@ struct Tile {
 };
 
 // Decodes this wave's tile and loads its words; false when the wave has no
-// inter-class tile to test in this pass (the same answer for the TW waves of
-// a tile).
-template <bool FIRST, int TW>
+// inter-class tile to test in this pass.
+template <bool FIRST>
 __device__ __forceinline__ bool tile_begin(const Plan &p, const uint64_t *__restrict__ src, int cur, int lane,
                                            Tile &T) {
   const Hdr *h = p.hdr;
   const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const long long t = xcd_remap(blockIdx.x, gridDim.x) * (kTileWaves / TW) + wid / TW;
-  if (t >= (p.Sq > 1 ? p.Tcells : p.Tmax)) return false;
-  if (!tile_decode(t, p.Rmax, p.Sq, T.X, T.Y)) return false;
+  const long long t = xcd_remap(blockIdx.x, gridDim.x) * kTileWaves + wid;
+  if (t >= p.Tmax) return false;
+  tri_decode(t, p.Rmax, T.X, T.Y);
   // one round of independent loads (X, Y < Rmax: the block table is in
   // bounds even where this call's layout is shorter or invalid)
   const int bad = h->bad_colour | h->bad_layout | h->done, R = h->R;
@@ -718,114 +660,299 @@ __device__ __forceinline__ void tile_finish(const Plan &p, uint64_t *__restrict_
   if (lane == 0 && cnt) atomicAdd(&h->ctr(cur, slot, 2), (unsigned long long)cnt);
 }
 
-// Edge test (witness search) for every edge of one inter-class block pair
-// (X, Y), X < Y.  Edge {u,v} fails when some class other than class(X) and
-// class(Y) holds no common neighbour.  The first-word matrix F (F[v*kF + c]
-// = the first word of row v's class-c segment) feeds the common case: per
-// chunk of KC classes, lane v holds its row's first words in registers; for
-// each row u, u's first words of the chunk come in as one block of scalar
-// loads (the address is uniform), and one AND, a compare and a wave ballot
-// per class give the lanes with a common neighbour there.  No class needs a
-// special case in this loop: F holds all-ones for a row's own class and for
-// the padding classes past k, and the registers of class(X) are set to
-// all-ones once per chunk, so the tile's own two classes and the padding
-// pass (class(Y) is v's own class), and an empty class holds zero words.
-// The one exception is a row u with no neighbour in the first word of
-// class(Y): its ballots for that class are empty, and the row takes the rare
-// path below like a row with a miss.  A lane that is still an edge and has
-// no witness in some third class's first word tries the second words (the
-// second-word matrix S, laid out like F and as small, so both sides come
-// from the L2), then scans the rest of the segment in the rows.  TW = 1: the
-// four waves of a workgroup test four neighbouring tiles (same X, so their
-// scalar loads share the cache), with no LDS and no barrier; TW = 4 (graphs
-// with few tiles): the workgroup's waves split one tile's rows u, 16 each,
-// so four times as many waves hide the scalar loads' latency, and wave 0
-// finishes the tile from the rows' results gathered in LDS.
-template <bool FIRST, int KC, int TW>
-__global__ void __launch_bounds__(kEdgeThreads) k_edge(Plan p, const uint64_t *__restrict__ src,
-                                                       uint64_t *__restrict__ dst, int pass,
-                                                       const uint64_t *__restrict__ F,
-                                                       const uint64_t *__restrict__ S) {
-  static_assert(TW == 1 || TW == kTileWaves, "a tile takes one wave or the whole workgroup");
-  const int lane = threadIdx.x & 63, cur = pass & 1;
-  Tile T;
-  if (!tile_begin<FIRST, TW>(p, src, cur, lane, T)) return;
-  const int k = p.k, kF = p.kF, R = p.hdr->R;
-  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int u0 = TW == 1 ? 0 : wid * (kBlk / TW), u1 = TW == 1 ? T.xl : min(u0 + kBlk / TW, T.xl);
-  const int vrc = lane < T.yl ? lane : T.yl - 1;
-  const uint64_t *rowv = src + (long long)(T.ys + vrc) * R;
-  const uint64_t *Sv = S + (long long)(T.ys + vrc) * kF;
-  unsigned long long P = T.E;
-  for (int q = 0; q < k; q += KC) {
-    // third classes of the tile in this chunk
-    const int hi = min(q + KC, k);
-    const int nthird = hi - q - (T.cx >= q && T.cx < hi) - (T.cy >= q && T.cy < hi);
-    if (nthird <= 0) continue;
-    const uint64_t *Fv = F + (long long)(T.ys + vrc) * kF + q;
-    unsigned long long vf[KC];
+// ---------------------------------------------------------------- edge test
+//
+// A workgroup's four waves take the 2 x 2 tiles of two pairs of blocks
+// (X0, X0 + 1) x (Y0, Y0 + 1); a wave's tile (X, Y) counts only where X < Y,
+// the classes differ and a block is touched.  Pair {u, v} passes when every
+// third class holds a common neighbour.  First the first word of every class
+// as a 4-bit matrix product (see kz_mx.h): per class four 32x32x64 MFMAs for
+// the wave's 64 x 64 pairs, and the minimum over the classes of the sums,
+// which is zero where some class had no witness.  The edges left are then
+// searched one per lane (edge_resolve).  Where nearly all would be left, or
+// few edges are to be tested at all (later passes), the product is skipped;
+// the results do not depend on it.
+//
+// The workgroup stages the first words in LDS (kEdgeRows = 2 x 128 rows), 16
+// bytes of padding a row, so that 64 lanes reading a column of 16-byte pieces
+// meet no bank conflict.  Per two classes a wave issues 8 MFMAs (256 cycles
+// of the matrix cores) and 112 vector instructions (448 cycles), 64 of them
+// the minima: vector issue bounds it.  Measured at 20 classes of 1000, p =
+// 0.3: 242 us, of which about 86 us pass without the product and the search
+// (652 us before, with a ballot per row and class over 64 lanes of which 30 %
+// held an edge; 10 classes of 800 at p = 0.2: 219 -> 78 us).  Three waves a
+// SIMD (CH <= 20, 51 KB of LDS) against two: 274 and 337 us.  All words of
+// every class as matrix products, with nothing left to search, took 2240 us.
+constexpr int kEdgeRows = 256;    // rows staged by a workgroup: 128 of each side
+constexpr int kEdgeList = 512;    // pairs a wave lists at a time
+constexpr int kEdgeFew = 128;     // edges to test per tile passing the product from which it is worth its time
+
+// Tile group g (of G, dealt over the XCDs as xcd_remap does) of the triangle
+// with its diagonal of NM x NM pairs of blocks: row-major (Sq = 1) or in
+// squares of Sq x Sq groups (Sq = kEdgeSquare), so that the groups an XCD has
+// in flight share their rows in its L2.  32-bit arithmetic (G < 2^31).
+__device__ __forceinline__ bool group_decode(unsigned g, unsigned G, int NM, int Sq, int &I, int &J) {
+  const unsigned xcd = g % 8, rem = G % 8;
+  const unsigned t = xcd * (G / 8) + min(xcd, rem) + g / 8;
+  const unsigned cell = Sq == 1 ? 0 : t % (kEdgeSquare * kEdgeSquare);
+  const int sq = (int)(Sq == 1 ? t : t / (kEdgeSquare * kEdgeSquare));
+  const int N = Sq == 1 ? NM : (NM + kEdgeSquare - 1) / kEdgeSquare;
+  // row x of the triangle starts at x (2 N - x + 1) / 2
+  auto start = [N](int x) { return (int)((unsigned)x * (2u * N - x + 1u) / 2u); };
+  const float d = 2.f * N + 1.f;
+  int x = (int)((d - sqrtf(fmaxf(d * d - 8.f * (float)sq, 0.f))) * 0.5f);
+  x = min(max(x, 0), N - 1);
+  while (x > 0 && start(x) > sq) --x;
+  while (x < N - 1 && start(x + 1) <= sq) ++x;
+  I = x * Sq + (int)(cell / kEdgeSquare);
+  J = (sq - start(x) + x) * Sq + (int)(cell % kEdgeSquare);
+  return I <= J && J < NM;
+}
+
+// Two neighbouring words of a row (rows start on 8 bytes only).
+struct __attribute__((packed, aligned(8))) Words {
+  unsigned long long a, b;
+};
+
+// The pairs M (lane u: row u's bits) one per lane: word by word over every
+// third class until a witness is found; a pair with a class that holds none
+// leaves `ok` (LDS, row u's bits).  The first words come from the staged
+// matrix (PU 16-byte pieces a row, `nc` classes from q on; soff: their word
+// ranges), the others from the rows.  Bounded by the latency of the rows' words, one round trip per
+// two words of a missing class.
+template <int PU>
+__device__ __forceinline__ void edge_resolve(unsigned long long M, const Tile &T, int lane, const mx_u4 *sA,
+                                             const mx_u4 *sB, int q, int nc, int k, const int *soff,
+                                             const uint64_t *__restrict__ src, int R, unsigned short *list,
+                                             unsigned long long *ok) {
+  for (;;) {
+    const int cnt = __popcll(M);
+    int at = cnt;
 #pragma unroll
-    for (int j = 0; j < KC; ++j) vf[j] = q + j == T.cx ? ~0ull : Fv[j];
-    unsigned third = 0;  // chunk positions of the tile's third classes
-#pragma unroll
-    for (int j = 0; j < KC; ++j)
-      if (q + j < k && q + j != T.cx && q + j != T.cy) third |= 1u << j;
-    const uint64_t *Fu = F + (long long)(T.xs + u0) * kF + q;  // row u's first words: uniform, scalar loads
-    for (int u = u0; u < u1; ++u, Fu += kF) {
-      unsigned long long Pu = lane64(P, u);
-      const unsigned long long Pt = Pu & (((T.TU >> u) & 1ull) ? ~0ull : T.TV);
-      if (!Pt) continue;
-      unsigned long long uf[KC];
-#pragma unroll
-      for (int j = 0; j < KC; ++j) uf[j] = Fu[j];
-      // lanes with a witness in every class of each quarter of the chunk
-      constexpr int KQ = KC / 4;
-      unsigned long long all[4] = {~0ull, ~0ull, ~0ull, ~0ull};
-#pragma unroll
-      for (int j = 0; j < KC; ++j) all[j / KQ] &= __ballot((uf[j] & vf[j]) != 0ull);
-      if (!(Pt & ~(all[0] & all[1] & all[2] & all[3]))) continue;
-      // some edge of u lacks a witness in a first word: in each quarter with
-      // a miss, third class by third class (u's word reloaded, so the hot
-      // loop's scalar registers need not live on into this path), the
-      // second words (S sits in the L2), then the rest of the segment in the
-      // rows; every load is made only by the lanes still missing a witness
-      const uint64_t *Su = S + (long long)(T.xs + u) * kF;
-      const uint64_t *rowu = src + (long long)(T.xs + u) * R;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        if (!(Pt & ~all[g])) continue;
-#pragma unroll
-        for (int jj = 0; jj < KQ; ++jj) {
-          const int j = g * KQ + jj;
-          const unsigned long long ufj = __builtin_nontemporal_load(Fu + j);
-          unsigned long long m = Pt & ~__ballot((ufj & vf[j]) != 0ull);
-          if (!m || !((third >> j) & 1u)) continue;
-          const int c = q + j;
-          const bool mine = (m >> lane) & 1ull;
-          const unsigned long long x2 = mine ? Su[c] : 0ull, y2 = mine ? Sv[c] : 0ull;
-          m &= ~__ballot((x2 & y2) != 0ull);
-          if (!m) continue;
-          const int w1 = p.soff[c + 1];
-          for (int w = p.soff[c] + 2; w < w1 && m; ++w) {
-            const bool still = (m >> lane) & 1ull;
-            const unsigned long long x = still ? rowu[w] : 0ull, y = still ? rowv[w] : 0ull;
-            m &= ~__ballot((x & y) != 0ull);
-          }
-          Pu &= ~m;
-        }
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int x = __shfl_up(at, off, kWave);
+      if (lane >= off) at += x;
+    }
+    const int total = __shfl(at, kWave - 1, kWave);
+    if (total == 0) return;
+    at -= cnt;
+    while (M && at < kEdgeList) {
+      list[at++] = (unsigned short)(lane << 6 | __builtin_ctzll(M));
+      M &= M - 1;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int n = min(total, kEdgeList);
+    for (int b = 0; b < n; b += kWave) {
+      const bool have = b + lane < n;
+      const int pr = have ? list[b + lane] : 0;
+      const int u = pr >> 6, v = pr & 63;
+      const mx_u4 *a = sA + u * PU, *c = sB + v * PU;
+      unsigned miss = 0;  // classes whose first word holds no witness
+#pragma unroll 4
+      for (int j = 0; j < nc; j += 2) {
+        const mx_u4 x = a[j >> 1], y = c[j >> 1];
+        miss |= (((x.x & y.x) | (x.y & y.y)) != 0u ? 0u : 1u) << j;
+        miss |= (((x.z & y.z) | (x.w & y.w)) != 0u ? 0u : 2u) << j;
       }
-      P = set_lane64(P, Pu, u, lane);
+      if (T.cx >= q && T.cx < q + nc) miss &= ~(1u << (T.cx - q));
+      if (T.cy >= q && T.cy < q + nc) miss &= ~(1u << (T.cy - q));
+      if (q + nc > k) miss &= (1u << (k - q)) - 1;
+      if (!have) miss = 0;
+      const uint64_t *ru = src + (long long)(T.xs + u) * R, *rv = src + (long long)(T.ys + v) * R;
+      bool fail = false;
+      while (miss && !fail) {
+        const int cl = __builtin_ctz(miss);
+        miss &= miss - 1;
+        const int w1 = soff[cl + 1];
+        bool hit = false;
+        for (int w = soff[cl] + 1; w < w1 && !hit; w += 2) {
+          // two words with one load; at a row's end the pair starts a word
+          // early (a word of this class that held no witness)
+          const int wb = min(w, R - 2);
+          const Words x = *(const Words *)(ru + wb), y = *(const Words *)(rv + wb);
+          hit = ((x.a & y.a) | (wb == w && w + 1 >= w1 ? 0ull : x.b & y.b)) != 0ull;
+        }
+        fail = !hit;
+      }
+      if (fail) atomicAnd(&ok[u], ~(1ull << v));
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Lane u: the rows v with a witness for {u, v} in the first word of each of
+// the staged classes.
+template <int PU>
+__device__ __forceinline__ unsigned long long edge_first(const Tile &T, const mx_u4 *sM, int q, int nc, int k, int wr,
+                                                         int wc, int lane) {
+  unsigned m[2][2][16];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) m[i][j][e] = 1u;
+  const mx_u4 *sA = sM + (64 * wr + lane) * PU, *sB = sM + (128 + 64 * wc + lane) * PU;
+  auto third = [&](int c) { return c < k && c != T.cx && c != T.cy; };
+  for (int c = 0; c < nc; c += 2) {
+    const bool t0 = third(q + c), t1 = third(q + c + 1);
+    if (!(t0 | t1)) continue;
+    mx_u4 a = sA[c >> 1], b = sB[c >> 1];
+    // a class of the tile's own (or past the last) always passes
+    if (!t0) a.x = a.y = b.x = b.y = ~0u;
+    if (!t1) a.z = a.w = b.z = b.w = ~0u;
+    const mx_u2 a0 = mx_split(a.x, a.y), a1 = mx_split(a.z, a.w), b0 = mx_split(b.x, b.y), b1 = mx_split(b.z, b.w);
+    const mx_v8i V[2][2] = {{mx_codes(b0.x), mx_codes(b1.x)}, {mx_codes(b0.y), mx_codes(b1.y)}};
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const mx_v8i U0 = mx_codes(j ? a0.y : a0.x), U1 = mx_codes(j ? a1.y : a1.x);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const mx_v16f d0 = mx_mma(V[i][0], U0, mx_v16f{}), d1 = mx_mma(V[i][1], U1, mx_v16f{});
+#pragma unroll
+        for (int e = 0; e < 16; ++e) m[i][j][e] = min(m[i][j][e], min(mx_bits(d0[e]), mx_bits(d1[e])));
+      }
     }
   }
-  if (TW > 1) {
-    // gather the rows' results (lane u of the wave that owns row u)
-    __shared__ unsigned long long sP[kBlk];
-    if (lane >= u0 && lane < u0 + kBlk / TW) sP[lane] = P;
-    __syncthreads();
-    if (wid != 0) return;
-    P = sP[lane];
+  const unsigned ok[2][2] = {{mx_pack(m[0][0]), mx_pack(m[0][1])}, {mx_pack(m[1][0]), mx_pack(m[1][1])}};
+  return mx_columns(ok, lane);
+}
+
+// Whether the matrix product of the first words is worth its time for tiles
+// with at most `most` edges to test each, `edges` edges in `area` pairs and k
+// classes.  It takes about 56 k cycles of a compute unit per tile and saves
+// the search of the edges that pass it, about 20 k / 64 cycles each; of
+// edges of density d, each class fails (1 - d^2)^64 of them.
+__device__ __forceinline__ bool edge_product_pays(int most, int edges, int area, int k) {
+  const float d = (float)edges / (float)max(area, 1);
+  const float miss = exp2f(64.f * __log2f(fmaxf(1.f - d * d, 1e-6f)));
+  return (float)most * exp2f(-1.44f * (float)k * miss) > (float)kEdgeFew;
+}
+
+// CH: classes staged at a time.
+template <bool FIRST, int CH>
+__global__ void __launch_bounds__(kEdgeThreads, CH <= 20 ? 3 : 2) k_edge(Plan p, const uint64_t *__restrict__ src,
+                                                          uint64_t *__restrict__ dst, int pass,
+                                                          const uint64_t *__restrict__ F) {
+  constexpr int PU = (CH / 2) | 1;             // 16-byte pieces of a staged row, odd
+  constexpr int LPR = CH / 2 <= 8 ? 8 : 16;    // lanes that load a row's pieces
+  __shared__ mx_u4 sM[kEdgeRows * PU];
+  __shared__ unsigned short sList[kTileWaves][kEdgeList];
+  __shared__ unsigned long long sOk[kTileWaves][kBlk];
+  __shared__ int sOff[CH + 1], sCnt[kTileWaves][2];
+  const int lane = threadIdx.x & 63, tid = threadIdx.x, cur = pass & 1;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wid >> 1, wc = wid & 1;
+  const Hdr *h = p.hdr;
+  const int NM = (p.Rmax + 1) / 2;
+  int I, J;
+  if (!group_decode(blockIdx.x, gridDim.x, NM, p.Sq, I, J)) return;
+  // one round of independent loads (the block table is in bounds below Rmax
+  // even where this call's layout is shorter or invalid)
+  const int bad = h->bad_colour | h->bad_layout | h->done, R = h->R, k = p.k;
+  // blocks X0, X0 + 1, Y0, Y0 + 1
+  struct Block {
+    int cls, start, len;
+    bool in, touched;
+  };
+  auto block = [&](int B) __attribute__((always_inline)) {
+    const int Bc = min(B, p.Rmax - 1);
+    const bool in = B < R;
+    return Block{p.bcls[Bc], p.bstart[Bc], p.blen[Bc], in, FIRST || p.btouched[cur][Bc] != 0};
+  };
+  const Block x0 = block(2 * I), x1 = block(2 * I + 1), y0 = block(2 * J), y1 = block(2 * J + 1);
+  auto live = [](const Block &x, const Block &y, bool above) __attribute__((always_inline)) {
+    return above && x.in && y.in && x.cls != y.cls && (x.touched || y.touched);
+  };
+  const bool l00 = live(x0, y0, I < J), l01 = live(x0, y1, true), l10 = live(x1, y0, I < J), l11 = live(x1, y1, I < J);
+  if (bad || !(l00 || l01 || l10 || l11)) return;
+  const bool mine = wr ? (wc ? l11 : l10) : (wc ? l01 : l00);
+  Tile T;
+  T.X = 2 * I + wr;
+  T.Y = 2 * J + wc;
+  T.cx = wr ? x1.cls : x0.cls;
+  T.cy = wc ? y1.cls : y0.cls;
+  T.xs = wr ? x1.start : x0.start;
+  T.xl = wr ? x1.len : x0.len;
+  T.ys = wc ? y1.start : y0.start;
+  T.yl = wc ? y1.len : y0.len;
+  T.E = T.ET = T.TU = T.TV = 0ull;
+  // row r of staged block i (0, 1: side X, 2, 3: side Y), clamped into its
+  // block, and a block past the last one onto the first of its pair
+  auto row_of = [&](int i, int r) __attribute__((always_inline)) {
+    const int b = i == 0 ? x0.start : i == 1 ? (x1.in ? x1.start : x0.start)
+                : i == 2 ? y0.start : (y1.in ? y1.start : y0.start);
+    const int l = i == 0 ? x0.len : i == 1 ? (x1.in ? x1.len : x0.len) : i == 2 ? y0.len : (y1.in ? y1.len : y0.len);
+    return b + min(r, l - 1);
+  };
+  // first words of the classes q .. q + nc - 1 (nc a multiple of 4), in two
+  // steps so that other loads can go out before the wait for these
+  constexpr int RPI = kEdgeThreads / LPR;  // rows per step: a divisor of 64
+  const int pc = tid & (LPR - 1), sr = tid / LPR;
+  mx_u4 x[LPR];
+  int so;
+  auto stage_load = [&](int q, int nc) __attribute__((always_inline)) {
+    const int pcc = min(pc, nc / 2 - 1);
+    so = p.soff[min(q + tid, k)];
+#pragma unroll
+    for (int i = 0; i < LPR; ++i)
+      x[i] = *(const mx_u4 *)(F + (long long)row_of(i * RPI / 64, i * RPI % 64 + sr) * p.kF + q + 2 * pcc);
+  };
+  auto stage_store = [&](int nc) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < LPR; ++i)
+      if (pc < nc / 2) sM[(i * RPI + sr) * PU + pc] = x[i];
+    if (tid <= CH) sOff[tid] = so;
+  };
+  const int nc0 = min(p.kF, CH);
+  stage_load(0, nc0);
+  unsigned long long Pt = 0ull;  // lane u: the edges of row u to test
+  if (mine) {
+    const unsigned long long ymask = T.yl == 64 ? ~0ull : ((1ull << T.yl) - 1);
+    const int urc = min(lane, T.xl - 1), vrc = min(lane, T.yl - 1);
+    const unsigned long long e = src[(long long)(T.xs + urc) * R + T.Y];
+    const unsigned long long et = src[(long long)(T.ys + vrc) * R + T.X];
+    T.E = lane < T.xl ? e & ymask : 0ull;
+    T.ET = lane < T.yl ? et : 0ull;
+    // pairs to re-test: those with a touched endpoint (all of them in pass
+    // 1); the others keep their outcome, so masks and rounds equal full sweeps
+    T.TU = FIRST ? ~0ull : __ballot(lane < T.xl && p.touched[cur][T.xs + lane]);
+    T.TV = FIRST ? ~0ull : __ballot(lane < T.yl && p.touched[cur][T.ys + lane]);
+    Pt = T.E & (((T.TU >> lane) & 1ull) ? ~0ull : T.TV);
   }
-  tile_finish<FIRST>(p, dst, T, P, cur, lane);
+  stage_store(nc0);
+  const int nE = wave_sum(__popcll(T.E)), nPt = wave_sum(__popcll(Pt));
+  if (lane == 0) {
+    sCnt[wid][0] = nE;
+    sCnt[wid][1] = nPt;
+  }
+  sOk[wid][lane] = ~0ull;
+  __syncthreads();
+  int most = 0, edges = 0;
+#pragma unroll
+  for (int i = 0; i < kTileWaves; ++i) {
+    most = max(most, sCnt[i][1]);
+    edges += sCnt[i][0];
+  }
+  const int area = (l00 ? x0.len * y0.len : 0) + (l01 ? x0.len * y1.len : 0) + (l10 ? x1.len * y0.len : 0) +
+                   (l11 ? x1.len * y1.len : 0);
+  if (k > 2 && most > 0) {
+    const bool product = edge_product_pays(most, edges, area, k);
+    for (int q = 0;;) {
+      const int nc = min(p.kF - q, CH);
+      unsigned long long M = Pt & sOk[wid][lane];
+      if (product && mine) M &= ~edge_first<PU>(T, sM, q, nc, k, wr, wc, lane);
+      edge_resolve<PU>(M, T, lane, sM + 64 * wr * PU, sM + (128 + 64 * wc) * PU, q, nc, k, sOff, src, R, sList[wid],
+                       sOk[wid]);
+      q += CH;
+      if (q >= k) break;
+      __syncthreads();  // every wave is done with the staged classes
+      stage_load(q, min(p.kF - q, CH));
+      stage_store(min(p.kF - q, CH));
+      __syncthreads();
+    }
+  }
+  if (mine) tile_finish<FIRST>(p, dst, T, T.E & ~(Pt & ~sOk[wid][lane]), cur, lane);
 }
 
 // The MFMA count path's tile epilogue: the pairs with a touched endpoint
@@ -837,7 +964,7 @@ __global__ void __launch_bounds__(kEdgeThreads) k_edge_mf(Plan p, const uint64_t
                                                           const uint64_t *__restrict__ fb) {
   const int lane = threadIdx.x & 63, cur = pass & 1;
   Tile T;
-  if (!tile_begin<FIRST, 1>(p, src, cur, lane, T)) return;
+  if (!tile_begin<FIRST>(p, src, cur, lane, T)) return;
   const int R = p.hdr->R;
   unsigned long long P = T.E;
   if (lane < T.xl) {
@@ -1090,42 +1217,21 @@ void launch_edge_pass(const Plan &plan, const uint64_t *src, uint64_t *dst, int 
                       hipStream_t s) {
   if (plan.Tmax <= 0) return;
   Plan p = plan;
-  const uint64_t *F = p.F, *S = p.S;
-  // a wave per tile when there are tiles enough to fill the chip many times
-  // over, else a workgroup per tile
-  const bool wide = p.Tmax < kEdgeWaveTiles;
-  // many tiles: in squares of kEdgeSquare x kEdgeSquare block pairs
-  p.Sq = wide ? 1 : kEdgeSquare;
-  if (p.Sq > 1) {
-    const long long NS = (p.Rmax + p.Sq - 1) / p.Sq;
-    p.Tcells = NS * (NS + 1) / 2 * p.Sq * p.Sq;
-  }
-  const long long cells = p.Sq > 1 ? p.Tcells : p.Tmax;
-  const dim3 grid((unsigned)(wide ? cells : (cells + kTileWaves - 1) / kTileWaves));
-  // classes per chunk: edge_chunk(k), which F's row stride is a multiple of
-#define KZ_EDGE(FI, KC)                                                                                       \
-  do {                                                                                                        \
-    if (wide)                                                                                                 \
-      hipLaunchKernelGGL((k_edge<FI, KC, kTileWaves>), grid, dim3(kEdgeThreads), 0, s, p, src, dst, pass, F, S); \
-    else                                                                                                      \
-      hipLaunchKernelGGL((k_edge<FI, KC, 1>), grid, dim3(kEdgeThreads), 0, s, p, src, dst, pass, F, S);       \
+  const uint64_t *F = p.F;
+  const long long NM = (p.Rmax + 1) / 2;
+  // many groups: in squares of kEdgeSquare x kEdgeSquare groups
+  p.Sq = p.Tmax < kEdgeSquareTiles ? 1 : kEdgeSquare;
+  const long long NS = (NM + p.Sq - 1) / p.Sq;
+  const dim3 grid((unsigned)(NS * (NS + 1) / 2 * p.Sq * p.Sq));
+#define KZ_EDGE(FI, CH) hipLaunchKernelGGL((k_edge<FI, CH>), grid, dim3(kEdgeThreads), 0, s, p, src, dst, pass, F)
+#define KZ_EDGE_K(FI)               \
+  do {                              \
+    if (p.kF <= 12) KZ_EDGE(FI, 12); \
+    else if (p.kF <= 20) KZ_EDGE(FI, 20); \
+    else KZ_EDGE(FI, 32);           \
   } while (0)
-#define KZ_EDGE_K(FI)                \
-  switch (edge_chunk(p.k)) {         \
-    case 4: KZ_EDGE(FI, 4); break;   \
-    case 8: KZ_EDGE(FI, 8); break;   \
-    case 12: KZ_EDGE(FI, 12); break; \
-    case 16: KZ_EDGE(FI, 16); break; \
-    case 20: KZ_EDGE(FI, 20); break; \
-    case 24: KZ_EDGE(FI, 24); break; \
-    case 28: KZ_EDGE(FI, 28); break; \
-    default: KZ_EDGE(FI, 32); break; \
-  }
-  if (first) {
-    KZ_EDGE_K(true)
-  } else {
-    KZ_EDGE_K(false)
-  }
+  if (first) KZ_EDGE_K(true);
+  else KZ_EDGE_K(false);
 #undef KZ_EDGE_K
 #undef KZ_EDGE
 }
