@@ -46,6 +46,7 @@
 // kBatchR, or n > kBatchN) get status KZ_ETOOLARGE in their result and are
 // left to the single-graph path.
 #include "kz_internal.h"
+#include "kz_mx.h"
 
 namespace kzi {
 
@@ -66,6 +67,17 @@ __device__ __forceinline__ unsigned long long bcast64(unsigned long long x, int 
   const unsigned lo = __builtin_amdgcn_readlane((unsigned)x, lane);
   const unsigned hi = __builtin_amdgcn_readlane((unsigned)(x >> 32), lane);
   return ((unsigned long long)hi << 32) | lo;
+}
+
+// A value every lane holds identically, moved to a scalar register: the job
+// and item words come from LDS or memory, which the compiler takes to differ
+// from lane to lane.
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+template <typename T>
+__device__ __forceinline__ T *uni(T *p) {
+  const unsigned long long x = (unsigned long long)p;
+  const unsigned lo = (unsigned)uni((int)x), hi = (unsigned)uni((int)(x >> 32));
+  return (T *)(((unsigned long long)hi << 32) | lo);
 }
 
 __device__ __forceinline__ bool tbit(const unsigned *b, int i) { return (b[i >> 5] >> (i & 31)) & 1u; }
@@ -118,6 +130,18 @@ __device__ __forceinline__ void acquire_agent() {
   __builtin_amdgcn_s_waitcnt(0);
 }
 
+// A job's sizes and buffers.
+struct GView {
+  int g, n, k, R;
+  int slack;  // classes a test may find without a witness: k - clique size
+  const uint64_t *rows;
+  uint64_t *cur, *nxt;
+  const int *colour;
+  uint8_t *valive;
+  int *changed, *items;  // each starts on a 128-byte line
+  BatchJob *J;
+};
+
 // What a workgroup keeps in LDS about the job it works on.
 struct BatchLds {
   int coff[kBatchK + 1], soff[kBatchK + 1];
@@ -134,17 +158,7 @@ struct BatchLds {
   unsigned long long removed_v, removed_e, tests;
   int gi, queue_empty, bad_colour, bad_layout, pick, quit, end, status;
   unsigned long long ticket;  // session mode: the ticket of the job being started
-};
-
-struct GView {
-  int g, n, k, R;
-  int slack;  // classes a test may find without a witness: k - clique size
-  const uint64_t *rows;
-  uint64_t *cur, *nxt;
-  const int *colour;
-  uint8_t *valive;
-  int *changed, *items;  // each starts on a 128-byte line
-  BatchJob *J;
+  GView view;          // the job whose items are run
 };
 
 // A job's descriptor: the batch's, or in session mode the copy its starter
@@ -156,38 +170,41 @@ __device__ __forceinline__ kz_batch_graph job_desc(const BatchArgs &a, int g) {
 __device__ __forceinline__ GView gview(const BatchArgs &a, int g) {
   const kz_batch_graph G = job_desc(a, g);
   GView v;
-  v.g = g;
-  v.n = G.n;
-  v.k = G.k;
-  v.R = G.row_words;
-  v.slack = G.clique > 0 && G.clique < G.k ? G.k - G.clique : 0;
-  const long long T = (long long)v.R * (v.R - 1) / 2;
+  v.g = uni(g);
+  v.n = uni(G.n);
+  v.k = uni(G.k);
+  v.R = uni(G.row_words);
+  v.slack = uni(G.clique > 0 && G.clique < G.k ? G.k - G.clique : 0);
   if (a.ptrs || a.session) {
     const BatchPtrs P = a.session ? a.jobs[g].sptrs : a.ptrs[g];
-    v.rows = P.rows;
-    v.cur = P.emask;
-    v.nxt = P.next;
-    v.colour = P.colour;
-    v.valive = P.vmask;
-    v.changed = P.lists;
-    v.items = P.items;
+    v.rows = uni(P.rows);
+    v.cur = uni(P.emask);
+    v.nxt = uni(P.next);
+    v.colour = uni(P.colour);
+    v.valive = uni(P.vmask);
+    v.changed = uni(P.lists);
+    v.items = uni(P.items);
   } else {
-    v.rows = a.rows + G.row_offset;
-    v.cur = a.emask + G.row_offset;
-    v.nxt = a.next + G.row_offset;
-    v.colour = a.colour + G.vertex_offset;
-    v.valive = a.vmask + G.vertex_offset;
-    v.changed = a.lists + 2 * G.row_offset;
-    v.items = a.items + 2 * G.row_offset;
+    v.rows = uni(a.rows + G.row_offset);
+    v.cur = uni(a.emask + G.row_offset);
+    v.nxt = uni(a.next + G.row_offset);
+    v.colour = uni(a.colour + G.vertex_offset);
+    v.valive = uni(a.vmask + G.vertex_offset);
+    v.changed = uni(a.lists + 2 * G.row_offset);
+    v.items = uni(a.items + 2 * G.row_offset);
   }
-  (void)T;
-  v.J = a.jobs + g;
+  v.J = uni(a.jobs + g);
   return v;
 }
 
-// ---- vertex test on 64 vertices (one wave): vertex v fails when some other
-// class holds none of its neighbours; pass 1 also validates the rows.
-__device__ void vertex_chunk(const GView &V, BatchLds &S, int v0, bool first, int lane) {
+// ---- vertex test on 64 vertices (one wave): vertex v fails when more than
+// `slack` other classes hold none of its neighbours; pass 1 also validates
+// the rows.  A lane reads its row kVertexWords at a time, all loads of a turn
+// in flight together: walking the classes one load at a time cost a memory
+// round trip per class, and a cascade's passes wait for their vertex items.
+constexpr int kVertexWords = 8;
+
+__device__ __forceinline__ void vertex_chunk(const GView &V, BatchLds &S, int v0, bool first, int lane) {
   const int n = V.n, k = V.k, R = V.R;
   const uint64_t *src = V.cur;
   const int v = v0 + lane;
@@ -196,37 +213,47 @@ __device__ void vertex_chunk(const GView &V, BatchLds &S, int v0, bool first, in
   const uint64_t *row = src + (long long)(act ? v : v0) * R;
   const int cv = act ? V.colour[v] : -1;
   int miss = 0;  // other classes without a neighbour
-  int pr = 0;
-  for (int c = 0; c < k; ++c) {
-    const int w0 = S.soff[c], w1 = S.soff[c + 1];
-    const int s = S.coff[c + 1] - S.coff[c];
-    if (!act) continue;
-    if (w1 == w0) {
-      miss += c != cv;
-      continue;
+  int pr = 0, seen = 0;
+  bool own = false;  // a bit in the row's own class
+  unsigned long long any = 0;
+#pragma unroll 1
+  for (int t = 0; t < R; t += kVertexWords) {
+    unsigned long long x[kVertexWords];
+#pragma unroll
+    for (int i = 0; i < kVertexWords; ++i) x[i] = row[min(t + i, R - 1)];
+#pragma unroll
+    for (int i = 0; i < kVertexWords; ++i) {
+      const int w = t + i;
+      if (w >= R) break;
+      const int c = uni(S.bcls[w]);
+      any |= x[i];
+      own |= c == cv && x[i] != 0ull;
+      if (w + 1 < uni(S.soff[c + 1])) continue;
+      // the class's last word
+      ++seen;
+      const int s = uni(S.coff[c + 1]) - uni(S.coff[c]);
+      if (first && act && (s & 63) && (x[i] >> (s & 63))) pr = max(pr, P_EINVAL);
+      miss += c != cv && any == 0ull;
+      any = 0;
     }
-    if (first && (s & 63) && (row[w1 - 1] >> (s & 63))) pr = max(pr, P_EINVAL);
-    if (c == cv) {
-      if (!first) continue;
-      const int jv = v - S.coff[c];
-      for (int w = w0; w < w1; ++w) {
-        unsigned long long y = row[w];
-        if (w == w1 - 1 && (s & 63)) y &= (1ull << (s & 63)) - 1;
-        while (y) {
-          const int b = __builtin_ctzll(y);
-          y &= y - 1;
-          const int t = S.coff[c] + (w - w0) * 64 + b;
-          if (t == v) pr = max(pr, P_ESELFLOOP);
-          else
-            pr = max(pr, ((src[(long long)t * R + w0 + (jv >> 6)] >> (jv & 63)) & 1ull) ? (int)P_EILLEGAL
-                                                                                         : (int)P_EASYM);
-        }
+  }
+  miss += k - seen;  // classes without a vertex
+  if (first && act && own) {
+    // bits inside a row's own class (invalid input): classify them
+    const int w0 = S.soff[cv], w1 = S.soff[cv + 1], s = S.coff[cv + 1] - S.coff[cv], jv = v - S.coff[cv];
+    for (int w = w0; w < w1; ++w) {
+      unsigned long long y = row[w];
+      if (w == w1 - 1 && (s & 63)) y &= (1ull << (s & 63)) - 1;
+      while (y) {
+        const int b = __builtin_ctzll(y);
+        y &= y - 1;
+        const int t = S.coff[cv] + (w - w0) * 64 + b;
+        if (t == v) pr = max(pr, P_ESELFLOOP);
+        else
+          pr = max(pr, ((src[(long long)t * R + w0 + (jv >> 6)] >> (jv & 63)) & 1ull) ? (int)P_EILLEGAL
+                                                                                       : (int)P_EASYM);
       }
-      continue;
     }
-    bool nz = false;
-    for (int w = w0; w < w1 && !nz; ++w) nz = row[w] != 0;
-    miss += !nz;
   }
   if (pr) atomicMax(&S.prio, pr);
   const bool fail = act && miss > V.slack;
@@ -238,128 +265,300 @@ __device__ void vertex_chunk(const GView &V, BatchLds &S, int v0, bool first, in
   if (lane == 0 && nf) atomicAdd(&S.removed_v, (unsigned long long)nf);
 }
 
-// ---- edge test on tile (X, Y) (one wave): edge (u, v) fails when some third
-// class holds no common neighbour.  Only pairs with a touched endpoint are
-// tested again after pass 1; the others keep their outcome.
-template <int CH>
-__device__ void tile(const GView &V, BatchLds &S, int X, int Y, bool first, int lane,
-                     unsigned long long (*sU)[kBlk], unsigned long long (*sU2)[kBlk]) {
+// ---- edge test on tile (X, Y) (one wave): edge (u, v) fails when more than
+// `slack` third classes hold no common neighbour.  Only pairs with a touched
+// endpoint are tested again after pass 1; the others keep their outcome.
+//
+// The rows' words are multiplied as FP4 codes (kz_mx.h), a class's words
+// summed up, so a zero sum is a class without a witness: no search is left.
+// The wave takes the 32 columns u of one half of block X after the other (32
+// sums and 32 minima in half floats fit the 128 registers that 16 waves of a
+// workgroup leave each), over windows of kTileWords words of both blocks'
+// rows in LDS of its own: pieces of consecutive rows load whole cache lines,
+// where 64 lanes reading a word of 64 rows touch 64 lines for 512 bytes.  A
+// class of more than four words ends early once every pair to test has a
+// witness.  With slack the zero sums of a class are packed and added up as
+// bit planes.  Tiles with few pairs to test (later passes: a third of the
+// tiles of 4096 graphs of 4..16 classes of 8..128 vertices have up to 128)
+// take them one per lane.  On those graphs a launch took 28.1 ms with a
+// ballot per row and class, and takes 17.7 ms (15.1 ms with the order below):
+// 16 waves keep the vector ALUs busy, about 2000 instructions a tile, 64 of
+// them per class for the minima.  With clique sizes two below the classes
+// (512 graphs) 44.3 and 9.6 ms.
+constexpr int kTileWords = 7;  // odd: 64 lanes reading a column of words meet no bank conflict
+constexpr int kTilePairs = 128;  // edges to test up to which they are taken one per lane
+constexpr int kPlanes = 6;     // bits of a miss count (at most 62 third classes)
+
+struct TileRows {
+  unsigned long long u[kBlk][kTileWords], v[kBlk][kTileWords];
+};
+
+// 16 sums, element e's "zero" to bit e.
+__device__ __forceinline__ unsigned zeros16(const mx_v16f &acc) {
+  unsigned z = 0;
+#pragma unroll
+  for (int e = 15; e >= 0; --e) z = (z << 1) | min(mx_bits(acc[e]), 1u);
+  return ~z & 0xffffu;
+}
+
+// Column half j of the pairs `want` (lane u: bits v) in the sums' layout: the
+// inverse of mx_columns, quarter 0 in the low and quarter 1 in the high half.
+__device__ __forceinline__ unsigned want_bits(unsigned long long want, int j, int lane) {
+  unsigned out = 0;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const unsigned x = (unsigned)(want >> (32 * i));
+    const mx_u2 both = mx_split(x, x);  // lanes 0..31's, lanes 32..63's in both halves
+    unsigned y = ((j ? both.y : both.x) >> ((lane >> 5) * 4)) & 0x0f0f0f0fu;
+    y = (y | (y >> 4)) & 0x00ff00ffu;
+    y = (y | (y >> 8)) & 0xffffu;
+    out |= y << (16 * i);
+  }
+  return out;
+}
+
+// Words t .. t + nw - 1 of the rows of the block that starts at slot s0, into
+// LDS: eight lanes a row, eight rows a load.  Rows past the block's end (not
+// past the graph's) are the next block's; no pair to test is in them.
+__device__ __forceinline__ void stage_rows(const GView &V, unsigned long long (*dst)[kTileWords], int s0, int t,
+                                           int nw, int lane) {
+  const int R = V.R, pc = lane & 7, top = V.n - 1 - s0;
+  int r = lane >> 3;
+  const char *base = (const char *)(V.cur + (long long)s0 * R + t);
+  const unsigned word = 8u * (unsigned)min(pc, nw - 1);
+  unsigned long long x[8];
+  if (top >= kBlk - 1) {
+    const unsigned off = 8u * (unsigned)(r * R) + word;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = *(const unsigned long long *)(base + (long long)(64 * i) * R + off);
+  } else {
+    asm volatile("" : "+v"(r));  // not kept from one window to the next
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      x[i] = *(const unsigned long long *)(base + (8u * (unsigned)(min(r + 8 * i, top) * R) + word));
+  }
+  if (pc < nw)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dst[8 * i + r][pc] = x[i];
+}
+
+// Stages a window of both blocks' rows from word w on and returns its start.
+__device__ __forceinline__ int stage_tile(const GView &V, TileRows &W, int xs, int ys, int w, int lane) {
+  const int nw = min(kTileWords, V.R - w);
+  __builtin_amdgcn_wave_barrier();  // the previous window is read
+  stage_rows(V, W.u, xs, w, nw, lane);
+  stage_rows(V, W.v, ys, w, nw, lane);
+  __builtin_amdgcn_wave_barrier();
+  return w;
+}
+
+// Lane u: the pairs (bits v) of `want` with at most `slack` third classes
+// without a witness, as matrix products.  t: first word of the window staged.
+template <bool SLACK>
+__device__ __forceinline__ unsigned long long tile_product(const GView &V, const BatchLds &S, int X, int Y, int lane,
+                                                           unsigned long long want, TileRows &W, int t) {
+  const int cx = uni(S.bcls[X]), cy = uni(S.bcls[Y]);
+  const int xs = uni(S.bstart[X]), ys = uni(S.bstart[Y]);
+  const bool two_u = uni(S.blen[X]) > 32, two_v = uni(S.blen[Y]) > 32;
+  const mx_u2 *pu = (const mx_u2 *)W.u[lane], *pv = (const mx_u2 *)W.v[lane];
+  // per column half j: the minima so far, two per register as half floats
+  // (the sums are positive or zero, so they compare as whole numbers; the
+  // conversion keeps zeros and only zeros zero), or with slack the bit planes
+  // of the miss counts
+  mx_us2 m[2][2][8];
+  unsigned plane[2][kPlanes];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) m[j][i][e] = mx_us2{1, 1};
+#pragma unroll
+    for (int b = 0; b < kPlanes; ++b) plane[j][b] = 0u;
+  }
+  auto fold = [&](int j, const mx_v16f &a0, const mx_v16f &a1) __attribute__((always_inline)) {
+    if constexpr (SLACK) {
+      unsigned carry = zeros16(a0) | (two_v ? zeros16(a1) << 16 : 0u);
+#pragma unroll
+      for (int b = 0; b < kPlanes; ++b) {
+        const unsigned x = plane[j][b];
+        plane[j][b] = x ^ carry;
+        carry &= x;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        m[j][0][e] = __builtin_elementwise_min(m[j][0][e], mx_halves(a0[2 * e], a0[2 * e + 1]));
+      if (two_v)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          m[j][1][e] = __builtin_elementwise_min(m[j][1][e], mx_halves(a1[2 * e], a1[2 * e + 1]));
+    }
+  };
+  int seen = 0;  // third classes with a word
+#pragma unroll 1
+  for (int c = 0; c < V.k; ++c) {
+    const int w0 = uni(S.soff[c]), w1 = uni(S.soff[c + 1]);
+    if (c == cx || c == cy || w0 == w1) continue;
+    ++seen;
+    // the whole class in the window where it fits one
+    if (w0 >= t + kTileWords || (w1 > t + kTileWords && w1 - w0 <= kTileWords))
+      t = stage_tile(V, W, xs, ys, w0, lane);
+    if (w1 - w0 <= 2) {
+      const bool two_w = w1 - w0 == 2;
+      const mx_u2 u0 = pu[w0 - t], v0 = pv[w0 - t], us0 = mx_split(u0.x, u0.y), vs0 = mx_split(v0.x, v0.y);
+      const mx_v8i V00 = mx_codes(vs0.x), V01 = mx_codes(vs0.y);
+      mx_u2 us1 = {};
+      mx_v8i V10 = {}, V11 = {};
+      if (two_w) {
+        const mx_u2 u1 = pu[w0 + 1 - t], v1 = pv[w0 + 1 - t], vs1 = mx_split(v1.x, v1.y);
+        us1 = mx_split(u1.x, u1.y);
+        V10 = mx_codes(vs1.x);
+        V11 = mx_codes(vs1.y);
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (j == 1 && !two_u) break;
+        const mx_v8i U0 = mx_codes(j ? us0.y : us0.x);
+        mx_v16f a0 = mx_mma(V00, U0, mx_v16f{}), a1 = mx_mma(V01, U0, mx_v16f{});
+        if (two_w) {
+          const mx_v8i U1 = mx_codes(j ? us1.y : us1.x);
+          a0 = mx_mma(V10, U1, a0);
+          a1 = mx_mma(V11, U1, a1);
+        }
+        fold(j, a0, a1);
+      }
+      continue;
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if (j == 1 && !two_u) break;
+      const unsigned wb = want_bits(want, j, lane);
+      if (w0 < t || w0 >= t + kTileWords) t = stage_tile(V, W, xs, ys, w0, lane);
+      mx_v16f a0, a1;
+      {
+        const mx_u2 uw = pu[w0 - t], vw = pv[w0 - t], us = mx_split(uw.x, uw.y), vs = mx_split(vw.x, vw.y);
+        const mx_v8i U = mx_codes(j ? us.y : us.x);
+        a0 = mx_mma(mx_codes(vs.x), U, mx_v16f{});
+        a1 = mx_mma(mx_codes(vs.y), U, mx_v16f{});
+      }
+#pragma unroll 1
+      for (int w = w0 + 1; w < w1; ++w) {
+        // every few words: done once each pair to test has a witness
+        const int done = w - w0;
+        if (done >= 4 && (done & (done - 1)) == 0 &&
+            __ballot(((zeros16(a0) | (zeros16(a1) << 16)) & wb) != 0u) == 0ull)
+          break;
+        if (w >= t + kTileWords) t = stage_tile(V, W, xs, ys, w, lane);
+        const mx_u2 uw = pu[w - t], vw = pv[w - t], us = mx_split(uw.x, uw.y), vs = mx_split(vw.x, vw.y);
+        const mx_v8i U = mx_codes(j ? us.y : us.x);
+        a0 = mx_mma(mx_codes(vs.x), U, a0);
+        a1 = mx_mma(mx_codes(vs.y), U, a1);
+      }
+      fold(j, a0, a1);
+    }
+  }
+  const int empty = V.k - 2 - seen;  // third classes without a vertex
+  unsigned okb[2][2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    if constexpr (SLACK) {
+      // misses + empty <= slack, bit plane by bit plane from the top
+      const int room = V.slack - empty;
+      unsigned less = 0u, equal = ~0u;
+#pragma unroll
+      for (int b = kPlanes - 1; b >= 0; --b) {
+        const unsigned x = plane[j][b], r = (room >> b) & 1 ? ~0u : 0u;
+        less |= equal & r & ~x;
+        equal &= ~(x ^ r);
+      }
+      const unsigned ok = room < 0 ? 0u : less | equal;
+      okb[0][j] = ok & 0xffffu;
+      okb[1][j] = ok >> 16;
+    } else {
+      okb[0][j] = empty > 0 ? 0u : mx_pack_halves(m[j][0]);
+      okb[1][j] = empty > 0 ? 0u : mx_pack_halves(m[j][1]);
+    }
+  }
+  return mx_columns(okb, lane);
+}
+
+// The same for up to 2 * 64 pairs, one per lane and turn: a word costs two
+// LDS reads and a few instructions, where the product takes all 4096 pairs.
+__device__ __forceinline__ unsigned long long tile_pairs(const GView &V, const BatchLds &S, int X, int Y, int lane,
+                                                         unsigned long long want, TileRows &W) {
+  const int cx = uni(S.bcls[X]), cy = uni(S.bcls[Y]);
+  const int xs = uni(S.bstart[X]), ys = uni(S.bstart[Y]);
+  // the pairs listed in the rows' place, then two in registers
+  unsigned short *list = (unsigned short *)W.u;
+  const int cnt = __popcll(want);
+  int at = cnt;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int x = __shfl_up(at, off, kWave);
+    if (lane >= off) at += x;
+  }
+  const int total = __builtin_amdgcn_readlane(at, kWave - 1);
+  at -= cnt;
+  __builtin_amdgcn_wave_barrier();
+  for (unsigned long long x = want; x; x &= x - 1) list[at++] = (unsigned short)(lane << 6 | __builtin_ctzll(x));
+  __builtin_amdgcn_wave_barrier();
+  const bool have0 = lane < total, have1 = lane + kWave < total;
+  const int p0 = have0 ? list[lane] : 0, p1 = have1 ? list[lane + kWave] : 0;
+  const bool more = total > kWave;
+  const unsigned long long *u0 = W.u[p0 >> 6], *v0 = W.v[p0 & 63], *u1 = W.u[p1 >> 6], *v1 = W.v[p1 & 63];
+  int t = -kTileWords, miss0 = 0, miss1 = 0, seen = 0;
+#pragma unroll 1
+  for (int c = 0; c < V.k; ++c) {
+    const int w0 = uni(S.soff[c]), w1 = uni(S.soff[c + 1]);
+    if (c == cx || c == cy || w0 == w1) continue;
+    ++seen;
+    unsigned long long wit0 = have0 ? 0ull : 1ull, wit1 = have1 ? 0ull : 1ull;
+#pragma unroll 1
+    for (int w = w0; w < w1; ++w) {
+      if (w >= t + kTileWords) t = stage_tile(V, W, xs, ys, w, lane);
+      wit0 |= u0[w - t] & v0[w - t];
+      if (more) wit1 |= u1[w - t] & v1[w - t];
+      if (__ballot(wit0 == 0ull || wit1 == 0ull) == 0ull) break;
+    }
+    miss0 += wit0 == 0ull;
+    miss1 += wit1 == 0ull;
+  }
+  const int room = V.slack - (V.k - 2 - seen);  // less the third classes without a vertex
+  unsigned long long *ok = W.u[0];
+  __builtin_amdgcn_wave_barrier();
+  ok[lane] = ~0ull;
+  __builtin_amdgcn_wave_barrier();
+  if (have0 && miss0 > room) atomicAnd(&ok[p0 >> 6], ~(1ull << (p0 & 63)));
+  if (have1 && miss1 > room) atomicAnd(&ok[p1 >> 6], ~(1ull << (p1 & 63)));
+  __builtin_amdgcn_wave_barrier();
+  return ok[lane];
+}
+
+__device__ __forceinline__ void tile(const GView &V, BatchLds &S, int X, int Y, bool first, int lane, TileRows &W) {
   const int R = V.R;
   const uint64_t *src = V.cur;
-  const int cx = S.bcls[X], cy = S.bcls[Y];
-  const int xs = S.bstart[X], xl = S.blen[X], ys = S.bstart[Y], yl = S.blen[Y];
+  const int xs = uni(S.bstart[X]), xl = uni(S.blen[X]), ys = uni(S.bstart[Y]), yl = uni(S.blen[Y]);
   const unsigned long long ymask = yl == 64 ? ~0ull : ((1ull << yl) - 1);
   const unsigned long long xmask = xl == 64 ? ~0ull : ((1ull << xl) - 1);
-  const uint64_t *rowu_l = src + (long long)(xs + (lane < xl ? lane : 0)) * R;  // lane as row u
-  const uint64_t *rowv = src + (long long)(ys + (lane < yl ? lane : 0)) * R;    // lane as row v
-  const unsigned long long Eu = lane < xl ? (rowu_l[Y] & ymask) : 0ull;          // E(u) of row u = lane
-  const unsigned long long ET = lane < yl ? rowv[X] : 0ull;
+  const unsigned long long eu = src[(long long)(xs + min(lane, xl - 1)) * R + Y];
+  const unsigned long long ev = src[(long long)(ys + min(lane, yl - 1)) * R + X];
+  // the first window, in flight with the loads above (the pairs path's list
+  // takes its place and stages again)
+  stage_tile(V, W, xs, ys, 0, lane);
+  const unsigned long long Eu = lane < xl ? eu & ymask : 0ull;  // the edges of row u = lane
+  const unsigned long long ET = lane < yl ? ev : 0ull;          // and of row v = lane
   const unsigned long long TU = first ? ~0ull : __ballot(lane < xl && tbit(S.tc, xs + lane));
   const unsigned long long TV = first ? ~0ull : __ballot(lane < yl && tbit(S.tc, ys + lane));
-  unsigned long long myP = Eu;  // P of the row this lane stands for
-  const int nthird = V.slack > 0 ? 0 : V.k - 2;
-  if (V.slack > 0) {
-    // more classes than the clique size: an edge fails when more than slack
-    // third classes hold no common neighbour; lane v counts its misses
-    for (int u = 0; u < xl; ++u) {
-      unsigned long long P = bcast64(myP, u);
-      const unsigned long long Pt = P & (((TU >> u) & 1ull) ? ~0ull : TV);
-      if (!Pt) continue;
-      const uint64_t *rowu = src + (long long)(xs + u) * R;
-      const bool tested = (Pt >> lane) & 1ull;
-      int miss = 0;
-      for (int c = 0; c < V.k; ++c) {
-        if (c == cx || c == cy) continue;
-        bool wit = false;
-        for (int w = S.soff[c]; w < S.soff[c + 1]; ++w) {
-          const uint64_t xu = rowu[w];
-          if (!xu) continue;
-          const uint64_t yv = tested && !wit ? rowv[w] : 0ull;
-          wit |= (xu & yv) != 0ull;
-          if (!(Pt & ~__ballot(wit))) break;  // every tested lane has its witness
-        }
-        miss += !wit;
-      }
-      P &= ~(Pt & __ballot(tested && miss > V.slack));
-      if (lane == u) myP = P;
-    }
+  const unsigned long long Pt = Eu & (((TU >> lane) & 1ull) ? ~0ull : TV);
+  unsigned long long Pu = Eu;
+  const int cnt = wave_sum(__popcll(Pt));
+  if (V.k - 2 > V.slack && cnt > 0) {
+    const unsigned long long ok = cnt <= kTilePairs ? tile_pairs(V, S, X, Y, lane, Pt, W)
+                                  : V.slack > 0    ? tile_product<true>(V, S, X, Y, lane, Pt, W, 0)
+                                                   : tile_product<false>(V, S, X, Y, lane, Pt, W, 0);
+    Pu &= ~(Pt & ~ok);
   }
-  for (int q = 0; q < nthird; q += CH) {
-    // stage the first two words of each third-class segment: row u's in LDS
-    // (read as broadcasts), row v's in registers
-    unsigned long long vv[CH], vv2[CH];
-    int w2[CH];
-    bool any2 = false, any3 = false;  // some segment of the chunk has a second / third word
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      const int i = q + j;
-      if (i < nthird) {
-        int c = i;
-        if (c >= cx) ++c;
-        if (c >= cy) ++c;
-        const int w0 = S.soff[c], w1 = S.soff[c + 1];
-        const bool has = w1 > w0, two = w1 > w0 + 1;
-        any2 |= two;
-        any3 |= w0 + 2 < w1;
-        sU[j][lane] = (has && lane < xl) ? rowu_l[w0] : 0ull;
-        sU2[j][lane] = (two && lane < xl) ? rowu_l[w0 + 1] : 0ull;
-        vv[j] = (has && lane < yl) ? rowv[w0] : 0ull;
-        vv2[j] = (two && lane < yl) ? rowv[w0 + 1] : 0ull;
-        w2[j] = w0 + 2 < w1 ? w0 + 2 : -1;
-      } else {
-        sU[j][lane] = ~0ull;
-        sU2[j][lane] = 0ull;
-        vv[j] = ~0ull;
-        vv2[j] = 0ull;
-        w2[j] = -1;
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-    for (int u = 0; u < xl; ++u) {
-      unsigned long long P = bcast64(myP, u);
-      const unsigned long long Pt = P & (((TU >> u) & 1ull) ? ~0ull : TV);
-      if (!Pt) continue;
-      unsigned long long all = ~0ull;
-#pragma unroll
-      for (int j = 0; j < CH; ++j) all &= __ballot((sU[j][u] & vv[j]) != 0ull);
-      if (!(Pt & ~all)) continue;
-      // level 2: the first two words (nothing new when no segment has two)
-      if (any2) {
-        all = ~0ull;
-#pragma unroll
-        for (int j = 0; j < CH; ++j) all &= __ballot(((sU[j][u] & vv[j]) | (sU2[j][u] & vv2[j])) != 0ull);
-        if (!(Pt & ~all)) continue;
-      }
-      if (!any3) {
-        // the first two words are the whole segments: a lane missing a
-        // witness in some class loses its edge
-        P &= ~(Pt & ~all);
-        if (lane == u) myP = P;
-        continue;
-      }
-      // level 3: scan the rest of the segment in memory
-      const uint64_t *rowu = src + (long long)(xs + u) * R;
-#pragma unroll
-      for (int j = 0; j < CH; ++j) {
-        unsigned long long miss = Pt & ~__ballot(((sU[j][u] & vv[j]) | (sU2[j][u] & vv2[j])) != 0ull);
-        if (!miss) continue;
-        if (w2[j] >= 0) {
-          int c = q + j;
-          if (c >= cx) ++c;
-          if (c >= cy) ++c;
-          for (int w = w2[j]; w < S.soff[c + 1] && miss; ++w) {
-            const unsigned long long x = rowu[w];
-            const unsigned long long y = ((miss >> lane) & 1ull) ? rowv[w] : 0ull;
-            miss &= ~__ballot((x & y) != 0ull);
-          }
-        }
-        P &= ~miss;
-      }
-      if (lane == u) myP = P;
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-  const unsigned long long Pu = myP;
   // transposes: lane v gets bit v of every P(u) (rows u >= xl hold zero) and,
   // in pass 1, of every E(u), to check that the rows are symmetric
   const unsigned long long newET = wave_transpose64(Pu, lane);
@@ -384,30 +583,60 @@ __device__ void tile(const GView &V, BatchLds &S, int X, int Y, bool first, int 
       atomicAdd(&S.removed_e, (unsigned long long)rem);
     }
   }
-  const int cnt = wave_sum(lane < xl ? __popcll(Eu & (((TU >> lane) & 1ull) ? ~0ull : TV)) : 0);
   if (lane == 0 && cnt) atomicAdd(&S.tests, (unsigned long long)cnt);
 }
 
+// The workgroup's LDS, reachable from run_items as well as from the kernel.
+__device__ __forceinline__ BatchLds &lds() {
+  __shared__ BatchLds S;
+  return S;
+}
+template <int NW>
+__device__ __forceinline__ TileRows &lds_rows(int wid) {
+  __shared__ TileRows W[NW];
+  return W[wid];
+}
+
 // The waves of the workgroup take the items of the claimed run one by one.
-template <int NW, int CH>
-__device__ void run_items(const GView &V, BatchLds &S, unsigned long long (*sU)[CH][kBlk],
-                          unsigned long long (*sU2)[CH][kBlk]) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const bool first = S.pass == S.pass0;
-  const int cnt = S.cnt, base = S.base;
+// A function of its own: a tile's sums need most of the registers, and next
+// to the rest of the kernel the compiler keeps them in scratch memory (27 GB
+// of writes a launch of 4096 graphs).
+template <int NW>
+__device__ __attribute__((noinline)) void run_items() {
+  BatchLds &S = lds();
+  const int lane0 = threadIdx.x & 63, wid = uni((int)(threadIdx.x >> 6));
+  TileRows &W = lds_rows<NW>(wid);
+  GView V;
+  V.n = uni(S.view.n);
+  V.k = uni(S.view.k);
+  V.R = uni(S.view.R);
+  V.slack = uni(S.view.slack);
+  V.cur = uni(S.view.cur);
+  V.nxt = uni(S.view.nxt);
+  V.colour = uni(S.view.colour);
+  V.valive = uni(S.view.valive);
+  V.changed = uni(S.view.changed);
+  V.items = uni(S.view.items);
+  V.J = uni(S.view.J);
+  const bool first = uni(S.pass) == uni(S.pass0);
+  const int cnt = uni(S.cnt), base = uni(S.base);
   for (;;) {
-    int i = 0;
+    // what an item computes from the lane stays inside the loop: hoisted, it
+    // goes to scratch memory and back around every tile
+    int i = 0, lane = lane0;
+    asm volatile("" : "+v"(lane));
     if (lane == 0) i = atomicAdd(&S.next_item, 1);
-    i = __builtin_amdgcn_readfirstlane(i);
+    i = uni(i);
     if (i >= cnt) break;
-    const int it = V.items[base + i];
+    const int it = uni(V.items[base + i]);
     if (it & kVertexItem) {
       // both halves of the item's line of the vertex mask, by this wave
       const int v0 = (it & 0xffff) * kVChunk;
-      vertex_chunk(V, S, v0, first, lane);
-      vertex_chunk(V, S, v0 + kWave, first, lane);
+#pragma unroll 1
+      for (int h = 0; h < kVChunk; h += kWave) vertex_chunk(V, S, v0 + h, first, lane);
+    } else {
+      tile(V, S, it & kXMask, (it >> kYShift) & kXMask, first, lane, W);
     }
-    else tile<CH>(V, S, it & kXMask, (it >> kYShift) & kXMask, first, lane, sU[wid], sU2[wid]);
   }
   __syncthreads();
 }
@@ -967,11 +1196,9 @@ __device__ int take_request(const BatchArgs &a, BatchLds &S) {
   return -1;
 }
 
-template <int NW, int CH>
-__global__ void __launch_bounds__(NW * 64) k_batch(BatchArgs a) {
-  __shared__ BatchLds S;
-  __shared__ unsigned long long sU[NW][CH][kBlk];
-  __shared__ unsigned long long sU2[NW][CH][kBlk];
+template <int NW>
+__global__ void __launch_bounds__(NW * 64, 4) k_batch(BatchArgs a) {
+  BatchLds &S = lds();
   const int tid = threadIdx.x;
   if (tid == 0) {
     S.job = -1;
@@ -990,7 +1217,9 @@ __global__ void __launch_bounds__(NW * 64) k_batch(BatchArgs a) {
       if (!S.got) claim<NW>(a, S, job);
       if (S.got) {
         const GView V = gview(a, job);
-        run_items<NW, CH>(V, S, sU, sU2);
+        if (tid == 0) S.view = V;
+        __syncthreads();
+        run_items<NW>();
         if (retire(V, S) && !carry<NW>(a, V, S)) job = -1;
         continue;
       }
@@ -1046,10 +1275,61 @@ __global__ void __launch_bounds__(NW * 64) k_batch(BatchArgs a) {
   }
 }
 
-// Orders the graphs by an estimate of their work, largest first (so the
-// persistent workgroups finish together), or keeps the given order; resets
-// the queue, the finished count and the board.  One workgroup, bitonic sort
-// in LDS for up to kBatchSortMax graphs.
+// Estimates the time every graph keeps a workgroup (one wave per graph) into
+// order[g], for k_batch_order: the passes to expect times what a pass takes
+// (its fixed part is worth about 30 tiles).  The passes follow from the
+// edges' density d, taken from kCostRows rows, and the class sizes: lam = the
+// sum over the third classes of (1 - d^2)^s is how many classes an edge is
+// expected to find no witness in.  Of 4096 graphs of 4..16 classes of 8..128
+// vertices, p = 0.2..0.8, those with lam in 0.03 .. 0.3 run 8 to 16 passes on
+// average and up to 119, the others 2 to 7; a long cascade that starts late
+// keeps the launch waiting: 18.0 ms in order of size, 15.0 ms in this order,
+// 14.7 ms in order of the true number of passes.
+constexpr int kCostRows = 16;
+__global__ void __launch_bounds__(64) k_batch_cost(BatchArgs a) {
+  const int g = blockIdx.x, lane = threadIdx.x;
+  const kz_batch_graph G = a.graphs[g];
+  const int n = G.n, k = G.k, R = G.row_words;
+  unsigned cost = 0;
+  if (n > 0 && k > 0 && k <= kBatchK && R > 0 && R <= kBatchR && n <= kBatchN && G.row_offset >= 0 &&
+      G.vertex_offset >= 0) {
+    const uint64_t *rows = a.rows + G.row_offset;
+    const int *colour = a.colour + G.vertex_offset;
+    int ones = 0;
+    for (int w = lane; w < R; w += kWave)
+#pragma unroll
+      for (int i = 0; i < kCostRows; ++i) ones += __popcll(rows[(long long)(i * n / kCostRows) * R + w]);
+    ones = wave_sum(ones);
+    // lane c: where class c starts (the colours are sorted)
+    int lo = 0, hi = n;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (colour[mid] < lane) lo = mid + 1;
+      else hi = mid;
+    }
+    const int next = __shfl_down(lo, 1, kWave);
+    const float s = (float)((lane == kWave - 1 ? n : next) - lo);
+    const float d = fminf((float)ones / (kCostRows * fmaxf((float)n - (float)n / (float)k, 1.f)), 0.999f);
+    float lam = lane < k ? exp2f(s * __log2f(1.f - d * d)) : 0.f;
+    for (int off = 32; off > 0; off >>= 1) lam += __shfl_xor(lam, off, kWave);
+    lam *= (float)max(k - 2, 0) / (float)k;
+    const float passes = lam < 0.01f  ? 3.f
+                         : lam < 0.03f ? 6.f
+                         : lam < 0.1f  ? 30.f
+                         : lam < 0.3f  ? 40.f
+                         : lam < 0.4f  ? 20.f
+                         : lam < 0.5f  ? 10.f
+                                       : 6.f;
+    cost = (unsigned)(passes * (30.f + 0.5f * (float)R * (float)(R - 1)));
+  }
+  if (lane == 0) a.order[g] = (int)cost;
+}
+
+// Orders the graphs by their estimated time (`lpt` 2: order[] holds it), or
+// by their sizes (1), largest first, so the persistent workgroups finish
+// together, or keeps the given order (0); resets the queue, the finished
+// count and the board.  One workgroup, bitonic sort in LDS for up to
+// kBatchSortMax graphs.
 __global__ void __launch_bounds__(1024) k_batch_order(BatchArgs a, int lpt) {
   __shared__ unsigned long long key[kBatchSortMax];
   const int t = threadIdx.x, G = a.G;
@@ -1067,10 +1347,14 @@ __global__ void __launch_bounds__(1024) k_batch_order(BatchArgs a, int lpt) {
   for (int i = t; i < P; i += 1024) {
     unsigned long long cost = 0;
     if (i < G) {
-      const kz_batch_graph gg = a.graphs[i];
-      const long long R = gg.row_words > 0 ? gg.row_words : 0;
-      cost = (unsigned long long)(R * R * 64LL * (gg.k > 2 ? gg.k : 1) + gg.n);
-      if (cost > 0xffffffffull) cost = 0xffffffffull;
+      if (lpt == 2) {
+        cost = (unsigned)a.order[i];
+      } else {
+        const kz_batch_graph gg = a.graphs[i];
+        const long long R = gg.row_words > 0 ? gg.row_words : 0;
+        cost = (unsigned long long)(R * R * 64LL * (gg.k > 2 ? gg.k : 1) + gg.n);
+        if (cost > 0xffffffffull) cost = 0xffffffffull;
+      }
       key[i] = (~cost << 32) | (unsigned)i;  // ascending key = descending cost
     } else {
       key[i] = ~0ull;
@@ -1102,18 +1386,17 @@ void launch_batch(const BatchArgs &args, const BatchConfig &cfg, hipStream_t s) 
   BatchArgs a = args;
   if (a.board_mask <= 0) a.board_mask = kBatchBoard - 1;
   // a session's queue and board are set up once, when its server is made
-  if (!a.session) hipLaunchKernelGGL(k_batch_order, dim3(1), dim3(1024), 0, s, a, cfg.lpt);
-  const dim3 grid(cfg.workgroups);
-#define KZ_B(NW, CH) hipLaunchKernelGGL((k_batch<NW, CH>), grid, dim3(NW * 64), 0, s, a)
-  if (cfg.waves == 4) {
-    if (cfg.chunk == 4) KZ_B(4, 4);
-    else KZ_B(4, 8);
-  } else if (cfg.waves == 8) {
-    if (cfg.chunk == 4) KZ_B(8, 4);
-    else KZ_B(8, 8);
-  } else {
-    KZ_B(16, 4);  // 16 waves with 8-class chunks would exceed the LDS and register budget
+  if (!a.session) {
+    // the estimate pays where graphs wait for a workgroup
+    const bool cost = cfg.lpt && a.G > cfg.workgroups && a.G <= kBatchSortMax;
+    if (cost) hipLaunchKernelGGL(k_batch_cost, dim3(a.G), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(k_batch_order, dim3(1), dim3(1024), 0, s, a, cost ? 2 : cfg.lpt);
   }
+  const dim3 grid(cfg.workgroups);
+#define KZ_B(NW) hipLaunchKernelGGL((k_batch<NW>), grid, dim3(NW * 64), 0, s, a)
+  if (cfg.waves == 4) KZ_B(4);
+  else if (cfg.waves == 8) KZ_B(8);
+  else KZ_B(16);
 #undef KZ_B
 }
 

@@ -19,6 +19,7 @@ namespace kzi {
 
 typedef unsigned mx_u4 __attribute__((ext_vector_type(4)));  // two 64-bit words
 typedef unsigned mx_u2 __attribute__((ext_vector_type(2)));
+typedef unsigned short mx_us2 __attribute__((ext_vector_type(2)));
 typedef int mx_v8i __attribute__((ext_vector_type(8)));
 typedef float mx_v16f __attribute__((ext_vector_type(16)));
 
@@ -54,6 +55,21 @@ __device__ __forceinline__ unsigned mx_pack(const unsigned (&m)[16]) {
 #pragma unroll
   for (int e = 14; e >= 0; --e) x = (x << 1) | m[e];
   return x;
+}
+
+// Two sums as half floats, rounded towards zero (their smallest value above
+// zero, 0.25, stays above it), as whole numbers of the same order.
+__device__ __forceinline__ mx_us2 mx_halves(float x, float y) {
+  return __builtin_bit_cast(mx_us2, __builtin_amdgcn_cvt_pkrtz(x, y));
+}
+
+// 16 whole numbers, element e's "not zero" to bit e.
+__device__ __forceinline__ unsigned mx_pack_halves(const mx_us2 (&m)[8]) {
+  unsigned x = 0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    x |= __builtin_bit_cast(unsigned, __builtin_elementwise_min(m[e], mx_us2{1, 1})) << (2 * e);
+  return (x & 0xffffu) | (x >> 15);  // the even elements' bits, the odd elements' one place up
 }
 
 // Which of 64 x 64 pairs are set, from four 32 x 32 quarters (quarter (i, j):
