@@ -93,225 +93,398 @@ __global__ void __launch_bounds__(256) k_dom_setup(const uint64_t *__restrict__ 
   }
 }
 
+// ---- the sweeps
+//
+// One workgroup runs a graph's fixpoint.  Rows are read by groups of GL
+// lanes, lane l of a group holding words l, l + GL, ... (WPL of them), so a
+// row is one coalesced load; small graphs keep all rows in LDS (LDS = true).
+// Both tests come down to the same loop: a set `cur` of nodes still thought
+// dominated loses the neighbours of every x of a set T (row x is taken out
+// of it, four rows in flight), and most of the time it is empty after a
+// few rows, as the graphs are dense.  What bounds it is the chain of LDS or
+// L2 reads of a step.  Edge mode on the evaluation recipe at 1100 nodes (rows
+// in LDS) 73.9 -> 11.0 ms, at 1900 (rows in L2) 271 -> 26.8 ms; vertex mode
+// 2.6 -> 0.87 and 5.5 -> 2.8 ms; the earlier form tested node by node, a
+// chain of dependent loads per test.
+constexpr int kDomLdsWords = 19840;  // rows kept in LDS up to this many words ...
+constexpr int kDomLdsR = 32;         // ... and this row width (then at most 1127 nodes)
+constexpr int kDomLdsNodes = 1152;
+
+template <int GL, int WPL>
+struct DomSet {
+  uint64_t w[WPL];
+};
+
+// The lanes of my group with a bit, from a ballot over the wave.
+template <int GL>
+__device__ __forceinline__ unsigned long long group_lanes(bool p, int lane) {
+  const unsigned long long b = __ballot(p);
+  if (GL == kWave) return b;
+  return (b >> (lane & ~(GL - 1))) & ((1ull << (GL & 63)) - 1);
+}
+
+// cur loses the neighbours of the nodes of T, until it is empty or T is.
+// D (may be null): nodes x of D count only for the nodes before x.
+template <int GL, int WPL>
+__device__ __forceinline__ void dom_strike(const uint64_t *rows, int R, int lane, DomSet<GL, WPL> &cur,
+                                           DomSet<GL, WPL> &T, const uint64_t *D) {
+  constexpr int kAhead = WPL < 16 ? 4 : 1;  // rows in flight
+  const int gl = lane & (GL - 1), base = lane & ~(GL - 1);
+  for (;;) {
+    bool mine = false, left = false;
+    int x = 0;  // this lane's first node of T
+#pragma unroll
+    for (int j = WPL - 1; j >= 0; --j) {
+      mine |= cur.w[j] != 0ull;
+      if (T.w[j]) {
+        left = true;
+        x = 64 * (gl + GL * j) + __builtin_ctzll(T.w[j]);
+      }
+    }
+    unsigned long long lanes = group_lanes<GL>(left, lane);
+    if (group_lanes<GL>(mine, lane) == 0ull || lanes == 0ull) return;
+    int f[kAhead], xs[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      f[i] = lanes ? __builtin_ctzll(lanes) : f[0];
+      lanes &= lanes - 1;
+      xs[i] = __shfl(x, base + f[i], kWave);
+    }
+    uint64_t rx[kAhead][WPL];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+      for (int j = 0; j < WPL; ++j) {
+        const int w = gl + GL * j;
+        rx[i][j] = w < R ? rows[(long long)xs[i] * R + w] : 0ull;
+      }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int xw = xs[i] >> 6;
+      const uint64_t below = (1ull << (xs[i] & 63)) - 1;
+      const bool later = D && ((D[xw] >> (xs[i] & 63)) & 1ull);
+#pragma unroll
+      for (int j = 0; j < WPL; ++j) {
+        const int w = gl + GL * j;
+        const uint64_t m = !later || w < xw ? ~0ull : w == xw ? below : 0ull;
+        cur.w[j] &= ~(rx[i][j] & m);
+        if (gl == f[i] && w == xw) T.w[j] &= ~(1ull << (xs[i] & 63));
+      }
+    }
+  }
+}
+
+// The same for sparse graphs, where a struck row takes out few nodes: every
+// node of cur against row b, a lane per word.
+template <int GL, int WPL>
+__device__ __forceinline__ void dom_scan(const uint64_t *rows, int R, int b, int lane, DomSet<GL, WPL> &cur) {
+  const uint64_t *rb = rows + (long long)b * R;
+#pragma unroll
+  for (int j = 0; j < WPL; ++j) {
+    uint64_t cand = cur.w[j];
+    while (cand) {
+      const int i = __builtin_ctzll(cand);
+      cand &= cand - 1;
+      const uint64_t *ra = rows + (long long)(64 * ((lane & (GL - 1)) + GL * j) + i) * R;
+      for (int w = 0; w < R; ++w)
+        if (ra[w] & ~rb[w]) {
+          cur.w[j] &= ~(1ull << i);
+          break;
+        }
+    }
+  }
+}
+
+__device__ __forceinline__ uint64_t dom_valid(int w, int n) {
+  const int lo = 64 * w;
+  return lo + 64 <= n ? ~0ull : lo < n ? (1ull << (n - lo)) - 1 : 0ull;
+}
+
 // ---- vertex dominance (Definition 4.3.1): the whole fixpoint, one workgroup
 //
-// Most steps delete nothing, so the waves first test consecutive steps at
-// once (wave w: does node b0 + w dominate anyone?), on the same graph; the
-// first step in sweep order that does is then run in full by the whole
-// workgroup, and the scan goes on right after it.  Steps before it saw the
-// graph the sequential sweep would have shown them (nothing was deleted in
-// between); the results of the steps after it are dropped.
-__global__ void __launch_bounds__(1024) k_dom_vertex_run(uint64_t *__restrict__ st, uint8_t *__restrict__ alive,
-                                                         int n, int R, DomHdr *h) {
-  __shared__ uint64_t AL[kDomMaxWords];  // live nodes (bit v of word v / 64)
-  __shared__ uint64_t rb[kDomMaxWords], D[kDomMaxWords];
-  __shared__ int dw[kDomMaxWords];       // the words of D that hold a deleted node
+// b dominates a iff they are not adjacent and no neighbour of a is outside
+// N(b).  With M = the live nodes not adjacent to b (b itself apart), that is
+// M less the neighbours of M's nodes (taken row by row in dense graphs: about
+// n ln(n) / degree rows; tested node by node in sparse ones).  Most steps delete nothing, so every
+// group tests a step of its own (group g: node b0 + g) on the same graph;
+// the first step in sweep order that dominates a node is applied, and the
+// scan goes on right after it.  Steps before it saw the graph the sequential
+// sweep would have shown them (nothing was deleted in between); the results
+// of the steps after it are dropped.
+template <int NT, int GL, int WPL, bool LDS>
+__global__ void __launch_bounds__(NT) k_dom_vertex_run(uint64_t *__restrict__ st,
+                                                                uint8_t *__restrict__ alive, int n, int R,
+                                                                DomHdr *h) {
+  constexpr int kGroups = NT / GL;
+  constexpr int kWords = LDS ? kDomLdsR : kDomMaxWords;
+  __shared__ uint64_t sRows[LDS ? kDomLdsWords : 1];
+  __shared__ uint64_t AL[kWords], D[kWords];  // live nodes; the nodes a step deletes
+  __shared__ int dw[kWords];                  // the words of D that hold a node
+  __shared__ int first[2], ndw;
   __shared__ unsigned long long nv, ne;
-  __shared__ int any_sweep, ndw;
-  __shared__ unsigned hits;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int nwaves = blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, gl = lane & (GL - 1);
+  const int group = tid / GL;
   if (h->prio != P_NONE) return;
-  for (int w = tid; w < R; w += blockDim.x) {
-    const int lo = 64 * w;
-    AL[w] = lo + 64 <= n ? ~0ull : lo < n ? (1ull << (n - lo)) - 1 : 0ull;
+  uint64_t *rows = LDS ? sRows : st;
+  if (LDS)
+    for (int i = tid; i < n * R; i += NT) sRows[i] = st[i];
+  for (int w = tid; w < R; w += NT) AL[w] = dom_valid(w, n);
+  if (tid == 0) {
+    nv = 0;
+    ne = 0;
+    first[0] = first[1] = n;
   }
+  __syncthreads();
+  const double degree = (double)h->dirs / n;
+  const bool sparse = degree * degree * degree < 8. * n;
   long long sweeps = 0, steps = 0;
+  int par = 0;
   for (;;) {
-    // every thread has read the previous sweep's flag before it is reset
-    __syncthreads();
-    if (tid == 0) any_sweep = 0;
+    bool any_sweep = false;
     int b0 = 0;
     while (b0 < n) {
-      if (tid == 0) hits = 0;
-      __syncthreads();
-      // scan: wave w tests step b0 + w; its lanes take the row words of the
-      // live non-neighbours of b and test those nodes one by one
-      {
-        const int b = b0 + wid;
-        if (b < n && ((AL[b >> 6] >> (b & 63)) & 1ull)) {
-          const uint64_t *rbg = st + (long long)b * R;
-          bool hit = false;
-          for (int w = lane; w < R && !hit; w += kWave) {
-            uint64_t cand = AL[w] & ~rbg[w];
-            if (w == (b >> 6)) cand &= ~(1ull << (b & 63));
-            while (cand && !hit) {
-              const int a = 64 * w + __builtin_ctzll(cand);
-              cand &= cand - 1;
-              const uint64_t *ra = st + (long long)a * R;
-              bool sub = true;
-              for (int w2 = 0; w2 < R; ++w2) {
-                if (ra[w2] & ~rbg[w2]) {
-                  sub = false;
-                  break;
-                }
-              }
-              hit = sub;
-            }
-          }
-          if (__ballot(hit) != 0ull && lane == 0) atomicOr(&hits, 1u << wid);
+      const int b = b0 + group;
+      DomSet<GL, WPL> cur, T;
+      bool hit = false;
+      if (b < n && ((AL[b >> 6] >> (b & 63)) & 1ull)) {
+#pragma unroll
+        for (int j = 0; j < WPL; ++j) {
+          const int w = gl + GL * j;
+          cur.w[j] = w < R ? AL[w] & ~rows[(long long)b * R + w] : 0ull;
+          if (w == (b >> 6)) cur.w[j] &= ~(1ull << (b & 63));
+          T.w[j] = cur.w[j];
         }
+        if (sparse) dom_scan<GL, WPL>(rows, R, b, lane, cur);
+        else dom_strike<GL, WPL>(rows, R, lane, cur, T, nullptr);
+        bool some = false;
+#pragma unroll
+        for (int j = 0; j < WPL; ++j) some |= cur.w[j] != 0ull;
+        hit = group_lanes<GL>(some, lane) != 0ull;
+        if (hit && gl == 0) atomicMin(&first[par], b);
       }
       __syncthreads();
-      const unsigned hm = hits;
-      if (!hm) {
-        b0 += nwaves;
+      const int bf = first[par];
+      par ^= 1;  // the other one is at n
+      if (bf == n) {
+        b0 += kGroups;
         continue;
       }
-      const int b = b0 + __builtin_ctz(hm);
-      // the step in full: every node b dominates, deleted with its edges
-      for (int w = tid; w < R; w += blockDim.x) {
-        rb[w] = st[(long long)b * R + w];
-        D[w] = 0;
-      }
-      if (tid == 0) {
-        nv = 0;
-        ne = 0;
-        ndw = 0;
-      }
-      __syncthreads();
-      for (int w = tid; w < R; w += blockDim.x) {
-        uint64_t cand = AL[w] & ~rb[w];
-        if (w == (b >> 6)) cand &= ~(1ull << (b & 63));
-        while (cand) {
-          const int a = 64 * w + __builtin_ctzll(cand);
-          cand &= cand - 1;
-          const uint64_t *ra = st + (long long)a * R;
-          bool sub = true;
-          unsigned long long deg = 0;
-          for (int w2 = 0; w2 < R; ++w2) {
-            const uint64_t x = ra[w2];
-            deg += __popcll(x);
-            if (x & ~rb[w2]) {
-              sub = false;
-              break;
-            }
-          }
-          if (sub) {
-            D[w] |= 1ull << (a & 63);   // word w belongs to this thread alone
-            atomicAdd(&nv, 1ull);
-            atomicAdd(&ne, deg);
-          }
+      // the step that dominates someone: its group has the set
+      if (b == bf) {
+#pragma unroll
+        for (int j = 0; j < WPL; ++j) {
+          const int w = gl + GL * j;
+          if (w < R) D[w] = cur.w[j];
         }
-        if (D[w]) dw[atomicAdd(&ndw, 1)] = w;
       }
+      if (tid == 0) ndw = 0;
       __syncthreads();
-      // the deleted nodes lose their rows and their place in AL; their
-      // neighbours (all in N(b)) lose them, in the words listed in dw
+      if (tid == 0) first[par ^ 1] = n;  // every thread has read it
+      for (int w = tid; w < R; w += NT)
+        if (D[w]) {
+          dw[atomicAdd(&ndw, 1)] = w;
+          AL[w] &= ~D[w];
+          atomicAdd(&nv, (unsigned long long)__popcll(D[w]));
+        }
+      __syncthreads();
+      // the deleted nodes lose their rows; their neighbours (all in N(b))
+      // lose them, in the words listed in dw.  Row b itself does not change.
       const int nd = ndw;
-      for (int w = tid; w < R; w += blockDim.x) AL[w] &= ~D[w];
-      for (int x = tid; x < n; x += blockDim.x) {
-        uint64_t *rx = st + (long long)x * R;
+      const uint64_t *rb = rows + (long long)bf * R;
+      for (int x = tid; x < n; x += NT) {
+        uint64_t *rx = rows + (long long)x * R;
         if ((D[x >> 6] >> (x & 63)) & 1ull) {
           alive[x] = 0;
-          for (int w = 0; w < R; ++w) rx[w] = 0;
+          unsigned long long deg = 0;
+          for (int w = 0; w < R; ++w) {
+            deg += __popcll(rx[w]);
+            rx[w] = 0;
+          }
+          if (deg) atomicAdd(&ne, deg);
         } else if ((rb[x >> 6] >> (x & 63)) & 1ull) {
           for (int i = 0; i < nd; ++i) {
             const int w = dw[i];
-            if (rx[w] & D[w]) rx[w] &= ~D[w];
+            const uint64_t y = rx[w];
+            if (y & D[w]) rx[w] = y & ~D[w];
           }
         }
       }
-      if (tid == 0) {
-        h->dv += (long long)nv;
-        h->de += (long long)ne;
-        any_sweep = 1;
-        ++steps;
-      }
-      b0 = b + 1;
-      // every thread has read `hits` and the step is applied before the next scan
+      any_sweep = true;
+      ++steps;
+      b0 = bf + 1;
       __syncthreads();
     }
-    __syncthreads();
     if (!any_sweep) break;
     ++sweeps;
   }
+  if (LDS)
+    for (int i = tid; i < n * R; i += NT) st[i] = sRows[i];
   if (tid == 0) {
+    h->dv = (long long)nv;
+    h->de = (long long)ne;
     h->sweeps = sweeps;
     h->events = steps;
   }
 }
 
 // ---- edge dominance (Definition 4.3.2): the whole fixpoint, one workgroup
-__global__ void __launch_bounds__(1024) k_dom_edge_run(uint64_t *__restrict__ st, int n, int R, DomHdr *h) {
-  __shared__ uint64_t na[kDomMaxWords], D[kDomMaxWords];
-  __shared__ int grew, any_sweep;
+//
+// Step a deletes {a, u} for the nodes u of N(a) that some b makes dominated:
+// b a neighbour of u, not of a, and N(a) & N(u) inside N(b).  For one b those
+// are the nodes of N(a) & N(b) less the neighbours of N(a) \ N(b).  A group
+// takes one b at a time from the list of the nodes not adjacent to a (where a
+// has few neighbours, of those next to one of them); nodes
+// already deleted in the step (D) join the list, for the nodes after them,
+// and count as gone from N(a) for the nodes after them.
+template <int NT, int GL, int WPL, bool LDS>
+__global__ void __launch_bounds__(NT) k_dom_edge_run(uint64_t *__restrict__ st, int n, int R, DomHdr *h) {
+  constexpr int kGroups = NT / GL;
+  constexpr int kWords = LDS ? kDomLdsR : kDomMaxWords;
+  __shared__ uint64_t sRows[LDS ? kDomLdsWords : 1];
+  __shared__ uint64_t na[kWords], D[kWords], Dn[kWords];  // N(a); deleted so far; found in this pass
+  __shared__ unsigned short list[LDS ? kDomLdsNodes : 64 * kDomMaxWords];
+  __shared__ int cnt[2];
+  __shared__ long long found;  // the last pass that found a node
   __shared__ unsigned long long nd;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, gl = lane & (GL - 1), group = tid / GL;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (h->prio != P_NONE) return;
+  uint64_t *rows = LDS ? sRows : st;
+  if (LDS)
+    for (int i = tid; i < n * R; i += NT) sRows[i] = st[i];
+  if (tid == 0) {
+    cnt[0] = cnt[1] = 0;
+    found = -1;
+    nd = 0;
+  }
+  __syncthreads();
   long long sweeps = 0, passes = 0;
+  unsigned long long deleted = 0;  // this thread's share
+  int par = 0;
   for (;;) {
-    // every thread has read the previous sweep's flag before it is reset
-    __syncthreads();
-    if (tid == 0) any_sweep = 0;
-    for (int a = 0; a < n; ++a) {
-      __syncthreads();
-      for (int w = tid; w < R; w += blockDim.x) {
-        na[w] = st[(long long)a * R + w];
-        D[w] = 0;
+    bool any_sweep = false;
+    for (int a = 0; a < n; ++a, par ^= 1) {
+      // word w's nodes to the list, a lane per bit (the whole wave calls it)
+      auto append = [&](int w, uint64_t m) __attribute__((always_inline)) {
+        if (!m) return;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&cnt[par], __popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if ((m >> lane) & 1ull)
+          list[at + __popcll(m & ((1ull << lane) - 1))] = (unsigned short)(64 * w + lane);
+      };
+      auto self = [&](int w) { return w == (a >> 6) ? 1ull << (a & 63) : 0ull; };
+      for (int w = wid; w < R; w += NT / kWave) {
+        const uint64_t x = rows[(long long)a * R + w];
+        if (lane == 0) {
+          na[w] = x;
+          D[w] = 0;
+          Dn[w] = 0;
+        }
+        append(w, ~x & dom_valid(w, n) & ~self(w));
       }
-      if (tid == 0) nd = 0;
+      __syncthreads();
+      if (tid == 0) cnt[par ^ 1] = 0;  // the next step's: nobody uses it in this one
+      int have = cnt[par];
+      bool grew = false;
+      const int deg = n - 1 - have;
+      if ((long long)deg * deg < have && have > 2 * kGroups) {
+        // few neighbours, many turns: only their neighbours can be b (gathered
+        // in Dn)
+        __syncthreads();
+        if (tid == 0) cnt[par] = 0;
+        __syncthreads();
+        for (int w = wid; w < R; w += NT / kWave) append(w, na[w]);
+        __syncthreads();
+        for (int i = group; i < deg; i += kGroups) {
+          const uint64_t *ru = rows + (long long)list[i] * R;
+          for (int w = gl; w < R; w += GL) {
+            const uint64_t x = ru[w];
+            if (x) atomicOr((unsigned long long *)&Dn[w], (unsigned long long)x);
+          }
+        }
+        __syncthreads();
+        if (tid == 0) cnt[par] = 0;
+        __syncthreads();
+        for (int w = wid; w < R; w += NT / kWave) {
+          append(w, Dn[w] & ~na[w] & ~self(w));
+          if (lane == 0) Dn[w] = 0;
+        }
+        __syncthreads();
+        have = cnt[par];
+      }
+      int old = 0;  // list entries the last pass has tested
       for (;;) {
-        // every thread has read the previous pass's flag (and the step's rows
-        // and D are in place) before the flag is reset
-        __syncthreads();
-        if (tid == 0) grew = 0;
-        __syncthreads();
-        // one pass: every neighbour u of a not yet in D, tested with D below u
-        for (int u = tid; u < n; u += blockDim.x) {
-          const int uw = u >> 6;
-          const uint64_t ub = 1ull << (u & 63);
-          if (!(na[uw] & ub) || (D[uw] & ub)) continue;
-          const uint64_t *ru = st + (long long)u * R;
-          bool dom = false;
-          for (int cw = 0; cw < R && !dom; ++cw) {
-            const uint64_t below = cw < uw ? D[cw] : cw == uw ? (D[cw] & (ub - 1)) : 0ull;
-            uint64_t cand = ru[cw] & (~na[cw] | below);
-            if (cw == (a >> 6)) cand &= ~(1ull << (a & 63));
-            while (cand && !dom) {
-              const int bv = 64 * cw + __builtin_ctzll(cand);
-              cand &= cand - 1;
-              const uint64_t *rbv = st + (long long)bv * R;
-              bool sub = true;
-              for (int w2 = 0; w2 < R; ++w2) {
-                const uint64_t b2 = w2 < uw ? D[w2] : w2 == uw ? (D[w2] & (ub - 1)) : 0ull;
-                if (((na[w2] & ~b2) & ru[w2]) & ~rbv[w2]) {
-                  sub = false;
-                  break;
-                }
-              }
-              dom = sub;
+        const long long pass = passes++;
+        for (int i = group; i < have; i += kGroups) {
+          const int b = list[i];
+          const bool later = grew && ((D[b >> 6] >> (b & 63)) & 1ull);  // b counts for the nodes after it
+          DomSet<GL, WPL> cur, T;
+#pragma unroll
+          for (int j = 0; j < WPL; ++j) {
+            const int w = gl + GL * j;
+            cur.w[j] = T.w[j] = 0ull;
+            if (w < R) {
+              const uint64_t rb = rows[(long long)b * R + w], x = na[w];
+              const uint64_t after = !later || w > (b >> 6) ? ~0ull
+                                     : w == (b >> 6)        ? ~((2ull << (b & 63)) - 1)
+                                                            : 0ull;
+              cur.w[j] = x & rb & ~D[w] & after;
+              T.w[j] = x & ~rb;
             }
           }
-          if (dom) {
-            atomicOr((unsigned long long *)&D[uw], ub);
-            grew = 1;
+          if (i < old) {
+            // tested before: something changes only where T meets a node
+            // deleted in this step
+            bool meets = false;
+#pragma unroll
+            for (int j = 0; j < WPL; ++j) {
+              const int w = gl + GL * j;
+              meets |= w < R && (T.w[j] & D[w]) != 0ull;
+            }
+            if (group_lanes<GL>(meets, lane) == 0ull) continue;
           }
+          dom_strike<GL, WPL>(rows, R, lane, cur, T, grew ? D : nullptr);
+#pragma unroll
+          for (int j = 0; j < WPL; ++j)
+            if (cur.w[j]) {
+              atomicOr((unsigned long long *)&Dn[gl + GL * j], (unsigned long long)cur.w[j]);
+              found = pass;
+            }
         }
         __syncthreads();
-        if (tid == 0) ++passes;
-        if (!grew) break;
-      }
-      // apply: {a, u} for every u in D
-      for (int w = tid; w < R; w += blockDim.x) {
-        if (D[w]) {
-          st[(long long)a * R + w] = na[w] & ~D[w];
-          atomicAdd(&nd, (unsigned long long)__popcll(D[w]));
+        if (found != pass) break;
+        grew = true;
+        old = have;
+        for (int w = wid; w < R; w += NT / kWave) {
+          const uint64_t add = Dn[w] & ~D[w];
+          if (lane == 0) D[w] |= add;
+          append(w, add);
         }
+        __syncthreads();
+        have = cnt[par];
       }
-      for (int u = tid; u < n; u += blockDim.x)
-        if ((D[u >> 6] >> (u & 63)) & 1ull) st[(long long)u * R + (a >> 6)] &= ~(1ull << (a & 63));
+      if (!grew) continue;
+      // apply: {a, u} for every u in D
+      any_sweep = true;
+      for (int w = tid; w < R; w += NT)
+        if (D[w]) {
+          rows[(long long)a * R + w] = na[w] & ~D[w];
+          deleted += __popcll(D[w]);
+        }
+      for (int u = tid; u < n; u += NT)
+        if ((D[u >> 6] >> (u & 63)) & 1ull) rows[(long long)u * R + (a >> 6)] &= ~(1ull << (a & 63));
       __syncthreads();
-      if (tid == 0 && nd) {
-        h->de += (long long)nd;
-        any_sweep = 1;
-      }
     }
-    __syncthreads();
     if (!any_sweep) break;
     ++sweeps;
   }
+  if (LDS)
+    for (int i = tid; i < n * R; i += NT) st[i] = sRows[i];
+  if (deleted) atomicAdd(&nd, deleted);
+  __syncthreads();
   if (tid == 0) {
+    h->de = (long long)nd;
     h->sweeps = sweeps;
     h->events = h->de;
     h->passes = passes;
@@ -361,8 +534,25 @@ int kz_dominance(kz_ctx *ctx, int32_t mode, int32_t n, const uint64_t *rows, int
   const long long words = (long long)n * R;
   const int grid = (int)std::min<long long>((words + 255) / 256, 4096);
   hipLaunchKernelGGL(k_dom_setup, dim3(grid), dim3(256), 0, s, rows, emask, vmask, n, R, h);
-  if (mode == KZ_DOM_VERTEX) hipLaunchKernelGGL(k_dom_vertex_run, dim3(1), dim3(1024), 0, s, emask, vmask, n, R, h);
-  else hipLaunchKernelGGL(k_dom_edge_run, dim3(1), dim3(1024), 0, s, emask, n, R, h);
+  // rows in LDS where they fit; a group of 4 to 64 lanes a row, several words
+  // a lane beyond 64; fewer waves at the barriers where the rows are short
+#define KZ_DOM(NT, GL, WPL, LDS)                                                                                 \
+  do {                                                                                                           \
+    if (mode == KZ_DOM_VERTEX)                                                                                   \
+      hipLaunchKernelGGL((k_dom_vertex_run<NT, GL, WPL, LDS>), dim3(1), dim3(NT), 0, s, emask, vmask, n, R, h);  \
+    else                                                                                                         \
+      hipLaunchKernelGGL((k_dom_edge_run<NT, GL, WPL, LDS>), dim3(1), dim3(NT), 0, s, emask, n, R, h);           \
+  } while (0)
+  if (words <= kDomLdsWords && R <= kDomLdsR) {
+    if (R <= 4) KZ_DOM(256, 4, 1, true);
+    else if (R <= 8) KZ_DOM(512, 8, 1, true);
+    else if (R <= 16) KZ_DOM(1024, 16, 1, true);
+    else KZ_DOM(1024, 32, 1, true);
+  } else if (R <= 32) KZ_DOM(1024, 32, 1, false);
+  else if (R <= 64) KZ_DOM(1024, 64, 1, false);
+  else if (R <= 256) KZ_DOM(1024, 64, 4, false);
+  else KZ_DOM(1024, 64, 16, false);
+#undef KZ_DOM
   DomHdr *hh = (DomHdr *)ctx->pinned;
   if (hipGetLastError() != hipSuccess ||
       hipMemcpyAsync(hh, h, sizeof(DomHdr), hipMemcpyDeviceToHost, s) != hipSuccess ||
