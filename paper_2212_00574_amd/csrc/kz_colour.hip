@@ -6,16 +6,29 @@
 // Every vertex v has the key (priority[v], v), compared lexicographically.
 // A round takes every uncoloured vertex whose key beats the key of each of
 // its uncoloured neighbours; each vertex taken gets the smallest colour that
-// no neighbour coloured in an earlier round holds.  Vertices taken in one
-// round are pairwise non-adjacent, so the colouring is legal and independent
-// of the order in which a round's vertices are coloured.
+// no neighbour coloured in an earlier round holds.
 //
-// Layout: U, a bit set of the uncoloured vertices (ceil(n/64) words); per
-// round one wave per vertex tests row & U (only uncoloured neighbours can
-// beat it), then one wave per taken vertex marks the colours of row & ~U in
-// an LDS bitmap and takes its lowest zero bit.  A taken vertex clears its own
-// bit of U in the same kernel: the other vertices taken in the round are not
-// its neighbours, so no one reads that bit for it.
+// The neighbours coloured before v are exactly those with larger keys (one
+// with a smaller key waits for v), so the colours are those of the greedy
+// colouring in order of falling keys, and v's round is one more than the
+// largest round of a neighbour with a larger key.  That is what runs here:
+// the vertices are ranked by their keys, and one workgroup goes through them
+// 64 at a time.  A round as two dependent launches took about 11 us, and a
+// graph has over a thousand rounds.
+//
+// While wave 0 resolves a block (its 64 vertices one after the other, lane j
+// holding vertex j's smallest free colour, each colour given reaching the
+// lanes next to it), the other waves gather for the next block what its rows
+// see of the blocks before: a bitmap of the colours in use and the largest
+// round; the block resolved meanwhile is merged in between two barriers.
+//
+// A block takes about 20 us whatever its edges, a round 10 to 20 us, and a
+// graph of average degree d has about 2 d rounds: sparse graphs (d below n /
+// 100) run the rounds instead, two kernels each: one wave per vertex tests
+// row & U (U: the uncoloured vertices; only they can beat it), then one wave
+// per taken vertex marks the colours of row & ~U in an LDS bitmap and takes
+// its lowest zero bit.  At 20000 vertices of average degree 200 both take
+// 7.2 to 7.6 ms; at degree 1000 38 ms and 9.9 ms.
 #include <string.h>
 
 #include <algorithm>
@@ -25,34 +38,50 @@
 
 namespace {
 
-constexpr int kColWaves = 4;                // waves (vertices) per workgroup
+constexpr int kColWaves = 4;                // waves (vertices) per workgroup of the check
 constexpr int kColMaxWords = 1024;          // row words (65536 vertices)
 constexpr size_t kColAlign = 256;
 constexpr int kColFirstChunk = 8;           // rounds enqueued before the first look at the count
 constexpr int kColMaxChunk = 128;           // ... and at most between two looks
+constexpr int kColThreads = 1024;           // the greedy workgroup
+constexpr int kColLdsWords = 32;            // words of a bitmap of colours kept in LDS (the rest in memory)
+constexpr int kColLdsColours = 64 * kColLdsWords;
+constexpr int kColLdsN = 16384;             // vertices up to which colours and rounds are kept in LDS
+constexpr int kRankThreads = 256, kRankSpan = 256;  // vertices ranked, and compared with, by a workgroup
 
 struct ColCtr {
-  int left;    // vertices not yet coloured; every round kernel returns at once at 0
-  int bad;     // validation: a KZ_* status, most severe first (see k_col_check)
-  int maxc;    // largest colour given
-  int rounds;  // rounds that ran
+  int left;     // rounds: vertices not yet coloured; every round kernel returns at once at 0
+  int bad;      // validation: a KZ_* status, most severe first (see k_col_check)
+  int top;      // largest colour given
+  int rounds;   // rounds
+  unsigned long long ends;  // sum of the degrees
 };
 
 size_t col_up(size_t x) { return (x + kColAlign - 1) / kColAlign * kColAlign; }
 
+// words of a bitmap of colours beyond those in LDS (a vertex's smallest free
+// colour is at most n - 1)
+int col_more(int n) { return n > kColLdsColours ? (n + 63) / 64 + 1 - kColLdsWords : 0; }
+
 struct ColWs {
-  size_t ctr, U, sel, total;
+  size_t ctr, U, sel, rank, order, val, used, total;
 };
 
 ColWs col_ws(int n) {
   ColWs w{};
   size_t o = 0;
-  w.ctr = o;
-  o += col_up(sizeof(ColCtr));
-  w.U = o;
-  o += col_up(sizeof(uint64_t) * (size_t)((n + 63) / 64 + 1));
-  w.sel = o;
-  o += col_up((size_t)n + 1);
+  auto take = [&o](size_t b) {
+    const size_t at = o;
+    o += col_up(b);
+    return at;
+  };
+  w.ctr = take(sizeof(ColCtr));
+  w.U = take(sizeof(uint64_t) * (size_t)((n + 63) / 64));
+  w.sel = take((size_t)n);
+  w.rank = take(sizeof(int) * (size_t)n);
+  w.order = take(sizeof(int) * (size_t)n);
+  w.val = take(n > kColLdsN ? sizeof(unsigned) * (size_t)n : 0);
+  w.used = take(2 * 64 * sizeof(uint64_t) * (size_t)col_more(n));
   w.total = o;
   return w;
 }
@@ -63,16 +92,18 @@ __device__ __forceinline__ bool key_beats(unsigned long long pu, int u, unsigned
 
 // Validation and set-up, one wave per row: no bit at or beyond n
 // (KZ_EINVAL), no self-loop (KZ_ESELFLOOP), symmetric (KZ_EASYM); the
-// most severe found wins (EINVAL, then ESELFLOOP, then EASYM).  colour = -1,
-// U = every vertex.
+// most severe found wins (EINVAL, then ESELFLOOP, then EASYM).  rank = 0,
+// colour = -1, U = every vertex.
 __global__ void __launch_bounds__(kColWaves * 64) k_col_check(int n, const uint64_t *__restrict__ rows, int R,
-                                                              int *colour, uint64_t *U, ColCtr *ctr) {
+                                                              int *rank, int *colour, uint64_t *U, ColCtr *ctr) {
+  __shared__ unsigned long long ends;
+  if (threadIdx.x == 0) ends = 0;
+  __syncthreads();
   const int lane = threadIdx.x & 63;
   const int v = blockIdx.x * kColWaves + (threadIdx.x >> 6);
-  if (v >= n) return;
   const uint64_t *row = rows + (long long)v * R;
-  int bad = 0;  // 3 EINVAL, 2 ESELFLOOP, 1 EASYM
-  for (int w = lane; w < R; w += 64) {
+  int bad = 0, deg = 0;  // bad: 3 EINVAL, 2 ESELFLOOP, 1 EASYM
+  for (int w = lane; v < n && w < R; w += 64) {
     unsigned long long x = row[w];
     const int lo = 64 * w;
     if (lo + 64 > n) {
@@ -80,6 +111,7 @@ __global__ void __launch_bounds__(kColWaves * 64) k_col_check(int n, const uint6
       if (x & past) bad = max(bad, 3);
       x &= ~past;
     }
+    deg += __popcll(x);
     while (x) {
       const int b = __builtin_ctzll(x);
       x &= x - 1;
@@ -89,16 +121,20 @@ __global__ void __launch_bounds__(kColWaves * 64) k_col_check(int n, const uint6
     }
   }
   for (int off = 32; off > 0; off >>= 1) bad = max(bad, __shfl_xor(bad, off, 64));
-  if (lane == 0) {
+  deg = kzi::wave_sum(deg);
+  if (lane == 0 && v < n) {
+    rank[v] = 0;
     colour[v] = -1;
     if (bad) atomicMax(&ctr->bad, bad);
     if (v == 0) ctr->left = n;
+    if ((v & 63) == 0) U[v >> 6] = n - v >= 64 ? ~0ull : (1ull << (n - v)) - 1;
+    atomicAdd(&ends, (unsigned long long)deg);
   }
-  if (lane == 0 && (v & 63) == 0) {
-    const int nb = min(64, n - v);
-    U[v >> 6] = nb == 64 ? ~0ull : (1ull << nb) - 1;
-  }
+  __syncthreads();
+  if (threadIdx.x == 0 && ends) atomicAdd(&ctr->ends, ends);
 }
+
+// ---- sparse graphs: the rounds themselves
 
 // One round's choice, one wave per vertex: sel[v] = v is uncoloured and its
 // key beats every uncoloured neighbour's.
@@ -182,9 +218,244 @@ __global__ void __launch_bounds__(kColWaves * 64) k_col_colour(int n, const uint
   if (c < 0) c = 64 * W;  // every colour below 64*W held (cannot happen: v has fewer than n neighbours)
   if (lane == 0) {
     colour[v] = c;
-    atomicMax(&ctr->maxc, c);
+    atomicMax(&ctr->top, c);
     atomicAnd(&U[v >> 6], ~(1ull << (v & 63)));
     atomicSub(&ctr->left, 1);
+  }
+}
+
+// ---- the greedy colouring in key order
+
+// rank[v] += the vertices of a span of kRankSpan whose keys beat v's.
+__global__ void __launch_bounds__(kRankThreads) k_col_rank(int n, const uint64_t *__restrict__ pri, int *rank) {
+  __shared__ uint64_t sp[kRankThreads];
+  const int t = threadIdx.x, v = blockIdx.x * kRankThreads + t;
+  const uint64_t pv = v < n ? pri[v] : 0;
+  const int u1 = min(n, (int)(blockIdx.y + 1) * kRankSpan);
+  int cnt = 0;
+  for (int u0 = blockIdx.y * kRankSpan; u0 < u1; u0 += kRankThreads) {
+    __syncthreads();
+    sp[t] = u0 + t < u1 ? pri[u0 + t] : 0;
+    __syncthreads();
+    const int m = min(kRankThreads, u1 - u0);
+    for (int i = 0; i < m; ++i) cnt += key_beats(sp[i], u0 + i, pv, v);
+  }
+  if (v < n && cnt) atomicAdd(&rank[v], cnt);
+}
+
+__global__ void __launch_bounds__(256) k_col_order(int n, const int *__restrict__ rank, int *__restrict__ order) {
+  const int v = blockIdx.x * 256 + threadIdx.x;
+  if (v < n) order[rank[v]] = v;
+}
+
+__device__ __forceinline__ int wave_max(int v) {
+  unsigned x = (unsigned)v;
+  x = max(x, kzi::dpp<kzi::kDppRor + 8>(x));
+  x = max(x, kzi::dpp<kzi::kDppRor + 4>(x));
+  x = max(x, kzi::dpp<kzi::kDppRor + 2>(x));
+  x = max(x, kzi::dpp<kzi::kDppRor + 1>(x));
+  return max(max(__builtin_amdgcn_readlane((int)x, 0), __builtin_amdgcn_readlane((int)x, 16)),
+             max(__builtin_amdgcn_readlane((int)x, 32), __builtin_amdgcn_readlane((int)x, 48)));
+}
+
+// The greedy colouring in key order (one workgroup, see the top).  val[u]:
+// vertex u's round less one (high half) and colour (low half), in LDS for
+// VLDS, else in memory.  A gather marks the colours it meets in a byte each
+// (its wave's flags) and packs them by ballots: as atomics on the bitmap 64
+// lanes would meet in a few words.  Colours from kColLdsColours on go to
+// bitmaps in memory (`more` words a row).  What bounds it is a block's
+// chain: the gather of a wave's rows (an LDS read and a byte written per
+// neighbour coloured) or the 64 steps of the resolve, then the merge.
+template <bool VLDS>
+__global__ void __launch_bounds__(kColThreads) k_col_greedy(int n, const uint64_t *__restrict__ rows, int R,
+                                                            const int *__restrict__ order, unsigned *gval,
+                                                            unsigned long long *gused, int more, int *colour,
+                                                            ColCtr *ctr) {
+  constexpr int kPitch = kColLdsWords + 1;  // odd: 64 lanes reading a column meet no bank conflict
+  constexpr int kW = kColThreads / 64;
+  __shared__ unsigned sval[VLDS ? kColLdsN : 1];
+  __shared__ unsigned long long sused[2][64][kPitch];
+  __shared__ unsigned sflag[kW][kColLdsColours / 4];    // a byte per colour
+  __shared__ unsigned long long done[VLDS ? kColLdsN / 64 : kColMaxWords];  // vertices coloured
+  __shared__ unsigned long long adj[2][64], cross[64];  // a block's edges inside, and to the block before
+  __shared__ int most[2][64];                           // largest round seen, of a block's rows
+  __shared__ int resC[64], resR[64], blk[2][64];        // colours and rounds given; a block's vertices
+  __shared__ int ncol;                                  // colours given so far
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int W = (n + 63) >> 6, NB = (n + 63) >> 6;
+  auto far = [&](int par, int i) __attribute__((always_inline)) { return gused + (long long)(par * 64 + i) * more; };
+  // word w of row i's bitmap (those in memory are written by atomics: read
+  // past this unit's cache)
+  auto load = [&](int par, int i, int w) __attribute__((always_inline)) {
+    return w < kColLdsWords ? sused[par][i][w]
+                            : __hip_atomic_load(far(par, i) + w - kColLdsWords, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto mark = [&](int par, int i, int c) __attribute__((always_inline)) {
+    if (c < kColLdsColours) atomicOr(&sused[par][i][c >> 6], 1ull << (c & 63));
+    else atomicOr(far(par, i) + (c >> 6) - kColLdsWords, 1ull << (c & 63));
+  };
+  for (int w = tid; w < W; w += kColThreads) done[w] = 0ull;
+  if (tid == 0) ncol = 0;
+  // what the rows i0, i0 + step, ... of block `b` (buffer par) see of the
+  // vertices done, and their edges inside the block and to the block before
+  // (in the other buffer).  All first loads go out before any is used: every
+  // row is read once, from memory.
+  constexpr int kMine = (64 + kW - 2) / (kW - 1);  // rows a wave gathers
+  constexpr int kAhead = 4;                        // words a lane loads at a time
+  auto gather = [&](int b, int par, int i0, int step) __attribute__((always_inline)) {
+    unsigned *flag = sflag[wid];
+    const int words = (ncol + 128) / 64 + 1;  // bitmap words that may come into use until the block is resolved
+    const int near = min(words, kColLdsWords);
+    const int uj = blk[par][lane], pj = blk[par ^ 1][lane];  // clamped where a block is short
+    unsigned long long in[kMine], before[kMine], x[kMine][kAhead];
+#pragma unroll
+    for (int q = 0; q < kMine; ++q) {
+      const uint64_t *row = rows + (long long)blk[par][min(i0 + q * step, 63)] * R;
+      in[q] = row[uj >> 6];
+      before[q] = row[pj >> 6];
+#pragma unroll
+      for (int t = 0; t < kAhead; ++t) x[q][t] = 64 * t + lane < W ? row[64 * t + lane] : 0ull;
+    }
+#pragma unroll
+    for (int q = 0; q < kMine; ++q) {
+      const int i = i0 + q * step;
+      if (i >= 64 || 64 * b + i >= n) break;
+      for (int w = lane; w < 16 * near; w += 64) flag[w] = 0u;
+      for (int w = kColLdsWords + lane; w < words; w += 64)
+        if (w < kColLdsWords + more)
+          __hip_atomic_store(far(par, i) + w - kColLdsWords, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (words > kColLdsWords) __builtin_amdgcn_s_waitcnt(0);
+      __builtin_amdgcn_wave_barrier();
+      int mr = 0;
+      auto meet = [&](unsigned a) __attribute__((always_inline)) {
+        const int c = (int)(a & 0xffff);
+        if (c < kColLdsColours) ((unsigned char *)flag)[c] = 1;
+        else mark(par, i, c);
+      };
+      auto word = [&](int w, unsigned long long y) __attribute__((always_inline)) {
+        y &= w < W ? done[w] : 0ull;
+        while (y) {
+          // four neighbours a turn (the last one again where there are fewer)
+          unsigned a[4];
+          int u = 0;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            if (y) u = 64 * w + __builtin_ctzll(y);
+            y &= y - 1;
+            a[t] = VLDS ? sval[u] : gval[u];
+          }
+#pragma unroll
+          for (int t = 0; t < 4; ++t) meet(a[t]);
+          mr = max(mr, (int)(max(max(a[0], a[1]), max(a[2], a[3])) >> 16) + 1);
+        }
+      };
+#pragma unroll
+      for (int t = 0; t < kAhead; ++t)
+        if (64 * t < W) word(64 * t + lane, x[q][t]);
+      if (W > 64 * kAhead) {
+        const uint64_t *row = rows + (long long)blk[par][i] * R;
+        for (int w0 = 64 * kAhead; w0 < W; w0 += 64 * kAhead) {
+          unsigned long long z[kAhead];
+#pragma unroll
+          for (int t = 0; t < kAhead; ++t) z[t] = w0 + 64 * t + lane < W ? row[w0 + 64 * t + lane] : 0ull;
+#pragma unroll
+          for (int t = 0; t < kAhead; ++t) word(w0 + 64 * t + lane, z[t]);
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+      for (int w = 0; w < near; ++w) {
+        const unsigned long long m = __ballot(((unsigned char *)flag)[64 * w + lane] != 0);
+        if (lane == 0) sused[par][i][w] = m;
+      }
+      mr = wave_max(mr);
+      const unsigned long long e = __ballot(64 * b + lane < n && ((in[q] >> (uj & 63)) & 1ull));
+      const unsigned long long c = __ballot(b > 0 && ((before[q] >> (pj & 63)) & 1ull));
+      if (lane == 0) {
+        most[par][i] = mr;
+        adj[par][i] = e;
+        cross[i] = c;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  };
+  // block 0 sees nothing done
+  if (wid == 0) {
+    blk[0][lane] = order[min(lane, n - 1)];
+    blk[1][lane] = blk[0][lane];
+  }
+  __syncthreads();
+  if (wid > 0) gather(0, 0, wid - 1, kW - 1);
+  __syncthreads();
+  int top = 0, rounds = 0;
+  for (int b = 0; b < NB; ++b) {
+    const int par = b & 1;
+    // the next block's vertices, before its gather (nobody reads this buffer)
+    if (wid == 0 && b + 1 < NB) blk[par ^ 1][lane] = order[min(64 * (b + 1) + lane, n - 1)];
+    __syncthreads();
+    if (wid == 0) {
+      // resolve block b: lane j's vertex, its smallest free colour m in word
+      // mw of its bitmap, its largest round r seen
+      const bool mine = 64 * b + lane < n;
+      const unsigned long long e = mine ? adj[par][lane] : 0ull;
+      int r = mine ? most[par][lane] : 0, mw = 0;
+      unsigned long long word = mine ? load(par, lane, 0) : 0ull;
+      while (word == ~0ull) word = load(par, lane, ++mw);
+      int m = 64 * mw + __builtin_ctzll(~word);
+      const int nb = min(64, n - 64 * b);
+      for (int i = 0; i < nb; ++i) {
+        const int c = __builtin_amdgcn_readlane(m, i), ri = __builtin_amdgcn_readlane(r, i) + 1;
+        const int cw = c >> 6;
+        const bool next = lane > i && ((e >> i) & 1ull);
+        r = next ? max(r, ri) : r;
+        word |= next && cw == mw ? 1ull << (c & 63) : 0ull;
+        // colours of later words go to the bitmap, a full word gives way to
+        // the next: both are rare
+        if (__ballot((next && cw > mw) || word == ~0ull) != 0ull) {
+          if (next && cw > mw) mark(par, lane, c);
+          while (word == ~0ull) word = load(par, lane, ++mw);
+        }
+        m = 64 * mw + __builtin_ctzll(~word);
+      }
+      resC[lane] = m;
+      resR[lane] = r;  // the round less one
+      if (mine) {
+        top = max(top, m + 1);
+        rounds = max(rounds, r + 1);
+      }
+    } else if (b + 1 < NB) {
+      gather(b + 1, par ^ 1, wid - 1, kW - 1);
+    }
+    __syncthreads();
+    // merge block b into the state and into the next block's rows
+    if (wid == 0) {
+      const int v = blk[par][lane];
+      if (64 * b + lane < n) {
+        const unsigned x = (unsigned)resR[lane] << 16 | (unsigned)resC[lane];
+        if (VLDS) sval[v] = x;
+        else gval[v] = x;
+        colour[v] = resC[lane];
+        atomicOr(&done[v >> 6], 1ull << (v & 63));
+      }
+      const int t = wave_max(64 * b + lane < n ? resC[lane] + 1 : 0);
+      if (lane == 0) ncol = max(ncol, t);
+    }
+    if (b + 1 < NB) {
+      for (int i = wid; i < 64; i += kW) {
+        if (64 * (b + 1) + i >= n) break;
+        const bool hit = (cross[i] >> lane) & 1ull;
+        if (hit) mark(par ^ 1, i, resC[lane]);
+        const int mr = wave_max(hit ? resR[lane] + 1 : 0);
+        if (lane == 0) most[par ^ 1][i] = max(most[par ^ 1][i], mr);
+      }
+    }
+  }
+  if (wid == 0) {
+    top = wave_max(top);
+    rounds = wave_max(rounds);
+    if (lane == 0) {
+      ctr->top = top - 1;
+      ctr->rounds = rounds;
+    }
   }
 }
 
@@ -229,38 +500,57 @@ int kz_colour_jp(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
   ColCtr *ctr = (ColCtr *)(base + z.ctr);
   uint64_t *U = (uint64_t *)(base + z.U);
   uint8_t *sel = (uint8_t *)(base + z.sel);
+  int *rank = (int *)(base + z.rank), *order = (int *)(base + z.order);
+  unsigned *val = (unsigned *)(base + z.val);
+  unsigned long long *used = (unsigned long long *)(base + z.used);
   ColCtr *h = (ColCtr *)ctx->pinned;  // the context's pinned readback buffer (4 KiB)
   const dim3 grid((unsigned)((n + kColWaves - 1) / kColWaves)), block(kColWaves * 64);
+  const unsigned blocks = (unsigned)((n + kRankThreads - 1) / kRankThreads);
+  auto read_back = [&]() {
+    return hipGetLastError() == hipSuccess &&
+           hipMemcpyAsync(h, ctr, sizeof(ColCtr), hipMemcpyDeviceToHost, s) == hipSuccess &&
+           hipStreamSynchronize(s) == hipSuccess;
+  };
   if (hipMemsetAsync(ctr, 0, sizeof(ColCtr), s) != hipSuccess) return done();
-  hipLaunchKernelGGL(k_col_check, grid, block, 0, s, n, rows, (int)row_words, colour, U, ctr);
-  if (hipGetLastError() != hipSuccess ||
-      hipMemcpyAsync(h, ctr, sizeof(ColCtr), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return done();
+  hipLaunchKernelGGL(k_col_check, grid, block, 0, s, n, rows, (int)row_words, rank, colour, U, ctr);
+  if (!read_back()) return done();
   if (h->bad) {
     r.status = h->bad == 3 ? KZ_EINVAL : h->bad == 2 ? KZ_ESELFLOOP : KZ_EASYM;
     return done();
   }
-  // rounds in chunks, ended on the device: one readback per chunk (rounds
-  // past the last one return at once)
-  int chunk = kColFirstChunk, last_left = n;
-  for (;;) {
-    for (int i = 0; i < chunk; ++i) {
-      hipLaunchKernelGGL(k_col_select, grid, block, 0, s, n, rows, (int)row_words, priority, U, sel, ctr);
-      hipLaunchKernelGGL(k_col_colour, grid, block, 0, s, n, rows, (int)row_words, sel, U, colour, ctr);
+  if (100 * h->ends < (unsigned long long)n * (unsigned long long)n) {
+    // rounds in chunks, ended on the device: one readback per chunk (rounds
+    // past the last one return at once)
+    int chunk = kColFirstChunk, last_left = n;
+    for (;;) {
+      for (int i = 0; i < chunk; ++i) {
+        hipLaunchKernelGGL(k_col_select, grid, block, 0, s, n, rows, (int)row_words, priority, U, sel, ctr);
+        hipLaunchKernelGGL(k_col_colour, grid, block, 0, s, n, rows, (int)row_words, sel, U, colour, ctr);
+      }
+      if (!read_back()) return done();
+      if (h->left == 0) break;
+      if (h->left >= last_left) return done();  // cannot happen: every round takes the largest uncoloured key
+      last_left = h->left;
+      chunk = std::min(2 * chunk, kColMaxChunk);
     }
-    if (hipGetLastError() != hipSuccess ||
-        hipMemcpyAsync(h, ctr, sizeof(ColCtr), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return done();
-    if (h->left == 0) break;
-    if (h->left >= last_left) return done();  // cannot happen: every round takes the largest uncoloured key
-    last_left = h->left;
-    chunk = std::min(2 * chunk, kColMaxChunk);
+    r.status = KZ_OK;
+    r.rounds = h->rounds;
+    r.colours = h->top + 1;
+    return done();
   }
+  hipLaunchKernelGGL(k_col_rank, dim3(blocks, (unsigned)((n + kRankSpan - 1) / kRankSpan)), dim3(kRankThreads), 0, s, n,
+                     priority, rank);
+  hipLaunchKernelGGL(k_col_order, dim3(blocks), dim3(kRankThreads), 0, s, n, rank, order);
+  if (n <= kColLdsN)
+    hipLaunchKernelGGL(k_col_greedy<true>, dim3(1), dim3(kColThreads), 0, s, n, rows, (int)row_words, order, val, used,
+                       col_more(n), colour, ctr);
+  else
+    hipLaunchKernelGGL(k_col_greedy<false>, dim3(1), dim3(kColThreads), 0, s, n, rows, (int)row_words, order, val, used,
+                       col_more(n), colour, ctr);
+  if (!read_back()) return done();
   r.status = KZ_OK;
   r.rounds = h->rounds;
-  r.colours = h->maxc + 1;
+  r.colours = h->top + 1;
   return done();
 }
 
