@@ -11,11 +11,11 @@
 //   edge {u,v} fails <=> some class outside {class(u), class(v)} holds no
 //                        common alive neighbour.  Quick reject: such a class
 //                        is certainly empty when PM(u) & PM(v) misses it;
-//                        otherwise the two sorted rows are merged and the
-//                        classes of common alive neighbours collected, until
-//                        every third class has one.
-// Both directions of an edge are tested independently (same answer), so a
-// failing entry clears only itself and no reverse-entry index is needed.
+//                        otherwise the entries of row v are looked up in row
+//                        u and the classes of common alive neighbours
+//                        collected, until every third class has one.
+// Both directions of an edge are quick-rejected independently (same answer);
+// the search of row v meets the reverse entry, so no index of it is kept.
 #include "kz_internal.h"
 
 namespace kzi {
@@ -45,6 +45,18 @@ __device__ __forceinline__ void wg_add2(Hdr *h, int par, int j0, long long a, in
     if (ta) atomicAdd(&h->ctr(par, slot, j0), (unsigned long long)ta);
     if (tb) atomicAdd(&h->ctr(par, slot, j1), (unsigned long long)tb);
   }
+}
+
+constexpr int kCsrTable = 1024;  // slots of the edge test's table of a row ...
+constexpr int kCsrRow = 512;     // ... and the longest row it takes
+
+__device__ __forceinline__ int csr_slot(int x) { return (int)(((unsigned)x * 2654435761u) >> 22); }
+
+// Lane l's value of x.
+__device__ __forceinline__ long long lane_value(long long x, int l) {
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)x, l);
+  const unsigned hi = __builtin_amdgcn_readlane((unsigned)((unsigned long long)x >> 32), l);
+  return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
 // Row bounds of u, or false when they do not lie inside [0, nnz].
@@ -241,91 +253,200 @@ __global__ void __launch_bounds__(256) k_csr_vertex(Plan p, const int64_t *rp, c
   }
 }
 
-// Edge test, one thread per directed entry.  A failing entry is flagged for
-// the apply pass, counted once per undirected edge (u < v) and marks its row
-// u touched for the next pass (the reverse entry fails too and marks v).
+// Edge test, one thread per directed entry.  The quick reject is taken by
+// each of an edge's two entries for itself: both see the same two presence
+// masks; a failing entry is flagged for the apply pass, counted once per
+// undirected edge (u < v) and marks its row touched.  The edges it leaves (u
+// < v) are searched by the whole wave, up to four of a row u at a time, in
+// step, so that four chains of loads are in flight: lanes over row v's
+// entries, each looked up in a hash table of u's live neighbours in LDS (rows
+// over kCsrRow entries: by binary search), and a byte per class tells what has
+// been found (plain stores: as atomics on a mask the lanes would meet in one
+// word).  The lane that meets u in row v knows the reverse entry, so a failing
+// edge flags both.  Bounded by the rows read (256 to 384 bytes of 128-byte
+// lines an edge at degree 50) and their latency.  Three passes at 100 000
+// vertices and 2.5 million edges with planted cliques: 376 -> 141 us at 30
+// classes, 2920 -> 355 us at 4, where nearly every edge is searched (a lane
+// per entry merged the two rows before).
 template <bool FIRST, int KW>
 __global__ void __launch_bounds__(256) k_csr_edge(Plan p, const int64_t *rp, const int32_t *ci,
                                                   long long nnz, const int *colour, const uint8_t *emask,
-                                                  int pass) {
+                                                  int pass, int per_wave) {
   Hdr *h = p.hdr;
   if (csr_bad(h) || h->prio || h->done) return;
-  const int k = p.k;
-  const int cur = pass & 1, nxt = cur ^ 1;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  bool tested = false, removed = false;
-  int marks = -1;  // row to mark touched (the entry failed)
-  if (i < nnz && emask[i]) {
-    const int u = p.src[i], v = ci[i];
-    if (FIRST || p.touched[cur][u] || p.touched[cur][v]) {
-      tested = u < v;
-      // each endpoint's record: its presence mask, then its colour
-      const uint64_t *ru = p.pm + (long long)u * (KW + 1), *rv = p.pm + (long long)v * (KW + 1);
-      unsigned long long mu[KW + 1], mv[KW + 1];
-      if constexpr (KW == 1) {
-        const ulonglong2 a = *(const ulonglong2 *)ru, c = *(const ulonglong2 *)rv;
-        mu[0] = a.x;
-        mu[1] = a.y;
-        mv[0] = c.x;
-        mv[1] = c.y;
-      } else {
+  constexpr int kAtOnce = 4;
+  __shared__ int4 sTab[4][kCsrTable / 4];          // u's live neighbours, -1 where free
+  __shared__ unsigned sSeen[4][kAtOnce][16 * KW];  // a byte per class
+  const int k = p.k, cur = pass & 1, nxt = cur ^ 1;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const long long i = ((long long)blockIdx.x * 4 + wv) * per_wave + lane;
+  bool act = lane < per_wave && i < nnz && (FIRST || emask[i]);
+  int u = -1, v = -1, cu = 0, cv = 0, tested = 0, removed = 0;
+  bool fail = false, open = false;  // open: passes the quick reject, some class to find
+  if (act) {
+    u = p.src[i];
+    v = ci[i];
+    act = FIRST || p.touched[cur][u] || p.touched[cur][v];
+  }
+  if (act) {
+    tested = u < v;
+    // each endpoint's record: its presence mask, then its colour
+    const uint64_t *ru = p.pm + (long long)u * (KW + 1), *rv = p.pm + (long long)v * (KW + 1);
+    unsigned long long mu[KW + 1], mv[KW + 1];
+    if constexpr (KW == 1) {
+      const ulonglong2 a = *(const ulonglong2 *)ru, c = *(const ulonglong2 *)rv;
+      mu[0] = a.x;
+      mu[1] = a.y;
+      mv[0] = c.x;
+      mv[1] = c.y;
+    } else {
 #pragma unroll
-        for (int j = 0; j <= KW; ++j) {
-          mu[j] = ru[j];
-          mv[j] = rv[j];
-        }
+      for (int j = 0; j <= KW; ++j) {
+        mu[j] = ru[j];
+        mv[j] = rv[j];
       }
-      const int cu = (int)mu[KW], cv = (int)mv[KW];
-      unsigned long long need[KW];
-      bool fail = false;
+    }
+    cu = (int)mu[KW];
+    cv = (int)mv[KW];
 #pragma unroll
-      for (int j = 0; j < KW; ++j) {
-        const int lo = j * 64;
-        need[j] = k > lo ? ((k - lo >= 64) ? ~0ull : ((1ull << (k - lo)) - 1)) : 0ull;
-        if ((cu >> 6) == j) need[j] &= ~(1ull << (cu & 63));
-        if ((cv >> 6) == j) need[j] &= ~(1ull << (cv & 63));
-        fail |= (need[j] & ~(mu[j] & mv[j])) != 0;
-      }
-      if (!fail) {
-        // merge the sorted rows; collect classes of common alive neighbours
-        long long a = rp[u], ae = rp[u + 1], c = rp[v], ce = rp[v + 1];
-        bool done = true;  // nothing left to find (k <= 2)?
-#pragma unroll
-        for (int j = 0; j < KW; ++j) done &= need[j] == 0;
-        while (a < ae && c < ce && !done) {
-          const int x = ci[a], y = ci[c];
-          if (x < y) {
-            ++a;
-          } else if (y < x) {
-            ++c;
-          } else {
-            if (emask[a] && emask[c]) {
-              const int cw = colour[x];
-              done = true;
-#pragma unroll
-              for (int j = 0; j < KW; ++j)
-                if ((cw >> 6) == j) need[j] &= ~(1ull << (cw & 63));
-#pragma unroll
-              for (int j = 0; j < KW; ++j) done &= need[j] == 0;
-            }
-            ++a;
-            ++c;
-          }
-        }
-        fail = !done;
-      }
-      if (fail) {
-        p.efail[i] = 1;
-        marks = u;
-        removed = u < v;
-      }
+    for (int j = 0; j < KW; ++j) {
+      const int lo = j * 64;
+      unsigned long long need = k > lo ? ((k - lo >= 64) ? ~0ull : ((1ull << (k - lo)) - 1)) : 0ull;
+      if ((cu >> 6) == j) need &= ~(1ull << (cu & 63));
+      if ((cv >> 6) == j) need &= ~(1ull << (cv & 63));
+      fail |= (need & ~(mu[j] & mv[j])) != 0;
+      open |= need != 0;
+    }
+    open = open && !fail && u < v;
+    if (fail) {
+      p.efail[i] = 1;
+      removed = u < v;
     }
   }
   // entries are in row order: of the lanes marking one row, only the first
   // of each run stores the flag
-  const int prev = __shfl_up(marks, 1, kWave);
-  if (marks >= 0 && ((threadIdx.x & 63) == 0 || prev != marks)) p.touched[nxt][marks] = 1;
-  wg_add2(h, cur, 2, tested ? 1 : 0, 1, removed ? 1 : 0);
+  const int marks = fail ? u : -1, prev = __shfl_up(marks, 1, kWave);
+  if (marks >= 0 && (lane == 0 || prev != marks)) p.touched[nxt][marks] = 1;
+  unsigned long long todo = __ballot(open);
+  long long vb = 0, ve = 0;
+  if (open) {
+    vb = rp[v];
+    ve = rp[v + 1];
+  }
+  while (todo) {
+    // the edges of one row u of this wave's entries
+    const int l0 = __builtin_ctzll(todo);
+    const int qu = __builtin_amdgcn_readlane(u, l0), qcu = __builtin_amdgcn_readlane(cu, l0);
+    unsigned long long same = todo & __ballot(u == qu);
+    todo &= ~same;
+    const long long b = rp[qu];
+    const int len = (int)(rp[qu + 1] - b);
+    const bool hashed = len <= kCsrRow;
+    int *tab = (int *)sTab[wv];
+    __builtin_amdgcn_wave_barrier();
+    if (hashed) {
+#pragma unroll
+      for (int t = 0; t < kCsrTable / 4 / kWave; ++t) sTab[wv][t * kWave + lane] = make_int4(-1, -1, -1, -1);
+      __builtin_amdgcn_wave_barrier();
+      for (int t = lane; t < len; t += kWave) {
+        const int x = ci[b + t];
+        if (!FIRST && !emask[b + t]) continue;
+        int at = csr_slot(x);
+        while (atomicCAS(&tab[at], -1, x) != -1) at = (at + 1) & (kCsrTable - 1);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    while (same) {
+      int l[kAtOnce], qcv[kAtOnce];
+      long long qb[kAtOnce], back[kAtOnce];
+      int ql[kAtOnce];
+      bool found[kAtOnce];
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        l[q] = same ? __builtin_ctzll(same) : -1;
+        same &= same - 1;
+        const int lq = max(l[q], 0);
+        qb[q] = lane_value(vb, lq);
+        ql[q] = (int)(lane_value(ve, lq) - qb[q]);
+        qcv[q] = __builtin_amdgcn_readlane(cv, lq);
+        back[q] = -1;  // the reverse entry, in the lane that meets it
+        found[q] = l[q] < 0;
+      }
+      for (int w = lane; w < kAtOnce * 16 * KW; w += kWave) sSeen[wv][0][w] = 0u;
+      __builtin_amdgcn_wave_barrier();
+      for (int t = 0;; t += kWave) {
+        int y[kAtOnce];
+        bool live[kAtOnce];
+#pragma unroll
+        for (int q = 0; q < kAtOnce; ++q) {
+          const bool in = !found[q] && t + lane < ql[q];
+          y[q] = in ? ci[qb[q] + t + lane] : -1;
+          live[q] = in && (FIRST || emask[qb[q] + t + lane]);
+        }
+#pragma unroll
+        for (int q = 0; q < kAtOnce; ++q)
+          if (y[q] == qu) back[q] = qb[q] + t + lane;
+        if (hashed) {
+          int at[kAtOnce], z[kAtOnce];
+#pragma unroll
+          for (int q = 0; q < kAtOnce; ++q) {
+            at[q] = csr_slot(y[q]);
+            z[q] = tab[at[q]];
+          }
+#pragma unroll
+          for (int q = 0; q < kAtOnce; ++q) {
+            while (live[q] && z[q] != y[q] && z[q] != -1) {
+              at[q] = (at[q] + 1) & (kCsrTable - 1);
+              z[q] = tab[at[q]];
+            }
+            live[q] = live[q] && z[q] == y[q];
+          }
+        } else {
+#pragma unroll
+          for (int q = 0; q < kAtOnce; ++q) {
+            int lo = 0, hi = live[q] ? len : 0;
+            while (lo < hi) {
+              const int mid = (lo + hi) >> 1;
+              if (ci[b + mid] < y[q]) lo = mid + 1;
+              else hi = mid;
+            }
+            live[q] = live[q] && lo < len && ci[b + lo] == y[q] && (FIRST || emask[b + lo]);
+          }
+        }
+        bool more = false;
+        int c[kAtOnce];
+#pragma unroll
+        for (int q = 0; q < kAtOnce; ++q) c[q] = live[q] ? colour[y[q]] : 0;
+#pragma unroll
+        for (int q = 0; q < kAtOnce; ++q)
+          if (live[q]) ((unsigned char *)sSeen[wv][q])[c[q]] = 1;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < kAtOnce; ++q) {
+          if (!found[q] && __ballot(live[q])) {
+            bool all = true;
+            for (int x = lane; all && x - lane < k; x += kWave)
+              all = __ballot(x < k && x != qcu && x != qcv[q] && !((unsigned char *)sSeen[wv][q])[x]) == 0ull;
+            found[q] = all;
+          }
+          more |= !found[q] && t + kWave < ql[q];
+        }
+        if (!more) break;
+      }
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        if (found[q]) continue;
+        if (back[q] >= 0) p.efail[back[q]] = 1;
+        if (lane == l[q]) {
+          p.efail[i] = 1;
+          p.touched[nxt][u] = 1;
+          p.touched[nxt][v] = 1;
+          ++removed;
+        }
+      }
+    }
+  }
+  wg_add2(h, cur, 2, tested, 1, removed);
 }
 
 // Removes the entries that failed this pass (after every test of the pass
@@ -376,9 +497,13 @@ void launch_csr_vertex(const Plan &p, const int64_t *rp, const int32_t *ci, cons
 void launch_csr_edge(const Plan &p, const int64_t *rp, const int32_t *ci, long long nnz, const int *colour,
                      const uint8_t *emask, int pass, bool first, hipStream_t s) {
   if (nnz <= 0) return;
-  const dim3 grid(grid_of(nnz, 256)), block(256);
+  // entries a wave takes: fewer where whole waves of them would not fill the
+  // chip's 8192 wave slots, as a wave searches its edges one group after the
+  // other (1000 vertices, 100 000 edges: 206 us with 64, 58 us with 16)
+  const int per_wave = nnz >= 64LL * 8192 ? 64 : nnz >= 32LL * 8192 ? 32 : 16;
+  const dim3 grid(grid_of(nnz, 4 * per_wave)), block(256);
   const int kw = csr_words(p.k);
-#define KZ_CSR_E(F, W) hipLaunchKernelGGL((k_csr_edge<F, W>), grid, block, 0, s, p, rp, ci, nnz, colour, emask, pass)
+#define KZ_CSR_E(F, W) hipLaunchKernelGGL((k_csr_edge<F, W>), grid, block, 0, s, p, rp, ci, nnz, colour, emask, pass, per_wave)
   if (first) {
     if (kw == 1) KZ_CSR_E(true, 1);
     else if (kw == 4) KZ_CSR_E(true, 4);
