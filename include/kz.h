@@ -615,7 +615,7 @@ int kz_find_clique(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_
  *         layout; map: device int32[out_nodes * 2], per node (v, -1) for
  *         A nodes and (x, y) for C nodes; KZ_EWORKSPACE when out_nodes or
  *         out_row_words is too small for G'.
- * Blocking (two small readbacks). */
+ * Blocking (one small readback). */
 typedef struct kz_struction_result {
   int32_t status;
   int32_t row_words;         /* ceil(nodes / 64)                            */

@@ -7,12 +7,14 @@
 //   A-C: a ~ c(x,y) iff a ~ x and a ~ y (the rule that makes Lemmas 1 and 2
 //   hold; the thesis states none), so omega(G') = omega(G) - 1.
 //
-// Plan: B's mask, every vertex's place in A, and for every x in B the count
-// of its C nodes (neighbours y > x in B), scanned into offsets.  Build: the
-// node map; M[v] = row v compressed onto A's index space (bit t = v ~ A[t]);
-// then one thread per output word: the A part of a word is M[a] (A row) or
-// M[x] & M[y] (C row); the C part of a C row is non-zero only inside its own
-// first vertex's block (y ~ y'), that of an A row holds a ~ x' and a ~ y'.
+// Plan: A in vertex order and, for every x in B, the count of its C nodes
+// (neighbours y > x in B), scanned into offsets.  Build: the node map and M[v]
+// = row v compressed onto A's index space (bit t = v ~ A[t]), then G': a node's
+// A part is M[a] (A node) or M[x] & M[y] (C node), an A node's C part is the
+// transpose of that, and a C node's C part is non-zero only inside its own
+// first vertex's block (y ~ y').  A call enqueues all of it and waits once:
+// the kernels take the node counts from the header and write nothing when they
+// do not fit.
 #include "kz_internal.h"
 
 namespace kzi {
@@ -23,200 +25,225 @@ struct StHdr {
   long long na, nc;    // |A|, |C|
   long long edges2;    // set bits of the input
   int prio;            // input problems (P_*)
-  int pad;
+  int fits;            // the outputs hold G'
 };
+
+constexpr int kStWaves = 4;  // waves (rows) per workgroup
 
 __device__ __forceinline__ bool bit(const uint64_t *row, int v) { return (row[v >> 6] >> (v & 63)) & 1ull; }
 
-// Validation (padding bits, self-loops, symmetry) and bit count; B's mask
-// (one thread per word of the pivot's row).
-__global__ void __launch_bounds__(256) k_st_check(const uint64_t *__restrict__ rows, int n, int R, int pivot,
-                                                  uint64_t *__restrict__ bmask, StHdr *h) {
-  const long long total = (long long)n * R;
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  unsigned long long cnt = 0;
-  int pr = P_NONE;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-    const int v = (int)(i / R), w = (int)(i % R);
-    unsigned long long x = rows[i];
-    cnt += __popcll(x);
-    const long long base = 64LL * w;
-    if (base >= n) {
-      if (x) pr = max(pr, (int)P_EINVAL);
-      continue;
-    }
-    if (base + 64 > n) {
-      const int keep = (int)(n - base);
-      if (x >> keep) pr = max(pr, (int)P_EINVAL);
-      x &= (1ull << keep) - 1;
-    }
-    while (x) {
-      const int t = (int)base + __builtin_ctzll(x);
-      x &= x - 1;
-      if (t == v) pr = max(pr, (int)P_ESELFLOOP);
-      else if (!bit(rows + (long long)t * R, v)) pr = max(pr, (int)P_EASYM);
-    }
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    cnt += __shfl_xor(cnt, off, kWave);
-    pr = max(pr, __shfl_xor(pr, off, kWave));
-  }
-  if ((threadIdx.x & 63) == 0) {
-    if (cnt) atomicAdd((unsigned long long *)&h->edges2, cnt);
-    if (pr != P_NONE) atomicMax(&h->prio, pr);
-  }
-  const int w = blockIdx.x * blockDim.x + threadIdx.x;
-  if (w < R) {
-    const long long lo = 64LL * w;
-    uint64_t valid = lo + 64 <= n ? ~0ull : lo < n ? (1ull << (n - lo)) - 1 : 0ull;
-    if (w == (pivot >> 6)) valid &= ~(1ull << (pivot & 63));
-    bmask[w] = ~rows[(long long)pivot * R + w] & valid;
-  }
+// Word w of B's mask: the vertices that are neither the pivot nor next to it.
+__device__ __forceinline__ uint64_t b_word(const uint64_t *prow, int pivot, int n, int w) {
+  const long long lo = 64LL * w;
+  uint64_t valid = lo + 64 <= n ? ~0ull : lo < n ? (1ull << (n - lo)) - 1 : 0ull;
+  if (w == (pivot >> 6)) valid &= ~(1ull << (pivot & 63));
+  return ~prow[w] & valid;
 }
 
-// Every vertex's place in A (or -1), and every B vertex's count of C nodes.
-__global__ void __launch_bounds__(256) k_st_count(const uint64_t *__restrict__ rows, int n, int R, int pivot,
-                                                  const uint64_t *__restrict__ bmask, int *__restrict__ apos,
-                                                  long long *__restrict__ ccount) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+// Bits of word w above vertex v.
+__device__ __forceinline__ uint64_t above(int v, int w) {
+  const int vw = v >> 6, b = v & 63;
+  return w > vw ? ~0ull : w < vw ? 0ull : b == 63 ? 0ull : ~0ull << (b + 1);
+}
+
+// What a row gives the scan: set bits, C nodes (below 2^28: 2^28 rows of 2^22
+// words are past any memory) with the problems found above them.
+struct StRow {
+  unsigned bits, nodes;
+};
+constexpr int kStPrio = 28;
+
+// One wave per row v, a lane per bit: validation (padding bits, self-loops,
+// symmetry), its set bits, its place in A or its count of C nodes.  The bits
+// of a word look their reverse entries up side by side: bounded by that
+// latency, 8 us at 1000 vertices (and 8 more before, for the counts, in a
+// thread per vertex).
+__global__ void __launch_bounds__(kStWaves * kWave) k_st_check(const uint64_t *__restrict__ rows, int n, int R,
+                                                               int pivot, int *__restrict__ alist,
+                                                               StRow *__restrict__ out) {
+  const int lane = threadIdx.x & 63, v = blockIdx.x * kStWaves + (threadIdx.x >> 6);
   if (v >= n) return;
-  const uint64_t *rp = rows + (long long)pivot * R;
+  const uint64_t *row = rows + (long long)v * R, *prow = rows + (long long)pivot * R;
   const int vw = v >> 6;
-  if (bit(rp, v)) {
-    int before = __popcll(rp[vw] & ((1ull << (v & 63)) - 1));
-    for (int w = 0; w < vw; ++w) before += __popcll(rp[w]);
-    apos[v] = before;
-    ccount[v] = 0;
-  } else {
-    apos[v] = -1;
-    long long c = 0;
-    if (bit(bmask, v)) {
-      const uint64_t *rv = rows + (long long)v * R;
-      // neighbours y > v inside B
-      c = __popcll(rv[vw] & bmask[vw] & ((v & 63) == 63 ? 0ull : ~0ull << ((v & 63) + 1)));
-      for (int w = vw + 1; w < R; ++w) c += __popcll(rv[w] & bmask[w]);
+  unsigned cnt = 0, before = 0, nodes = 0;
+  bool past = false, asym = false;
+#pragma unroll 4
+  for (int w = 0; w < R; ++w) {
+    const uint64_t x = row[w], px = prow[w];
+    cnt += __popcll(x);
+    before += __popcll(px & (w < vw ? ~0ull : w > vw ? 0ull : (1ull << (v & 63)) - 1));
+    nodes += __popcll(x & b_word(prow, pivot, n, w) & above(v, w));
+    const long long t = 64LL * w + lane;
+    if ((x >> lane) & 1ull) {
+      if (t >= n) past = true;
+      else asym |= !bit(rows + t * R, v);
     }
-    ccount[v] = c;
+  }
+  const bool loop = bit(row, v);
+  int pr = P_NONE;
+  if (__ballot(past)) pr = max(pr, (int)P_EINVAL);
+  if (loop) pr = max(pr, (int)P_ESELFLOOP);
+  if (__ballot(asym)) pr = max(pr, (int)P_EASYM);
+  if (lane == 0) {
+    const bool in_a = bit(prow, v);
+    if (in_a) alist[before] = v;
+    out[v] = StRow{cnt, (in_a || v == pivot ? 0u : nodes) | (unsigned)pr << kStPrio};
   }
 }
 
-// Exclusive scan of the counts into C offsets (one workgroup); |A| and |C|.
-__global__ void __launch_bounds__(1024) k_st_scan(const long long *__restrict__ ccount, int n, int na,
+// Scan of the counts into C offsets, and the header (one workgroup).
+__global__ void __launch_bounds__(1024) k_st_scan(const StRow *__restrict__ in, const uint64_t *__restrict__ prow, int n,
+                                                 int R, long long out_nodes, int out_words,
                                                  long long *__restrict__ coff, StHdr *h) {
-  __shared__ long long part[1024];
-  const int tid = threadIdx.x;
+  __shared__ long long nodes[16], bits[16];
+  __shared__ int prio[16], deg[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int per = (n + 1023) / 1024;
   const int lo = tid * per, hi = min(n, lo + per);
-  long long s = 0;
-  for (int v = lo; v < hi; ++v) s += ccount[v];
-  part[tid] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const long long x = tid >= off ? part[tid - off] : 0;
-    __syncthreads();
-    part[tid] += x;
-    __syncthreads();
+  long long s = 0, b = 0;
+  int pr = P_NONE, a = 0;
+  for (int v = lo; v < hi; ++v) {
+    const StRow x = in[v];
+    s += x.nodes & ((1u << kStPrio) - 1);
+    b += x.bits;
+    pr = max(pr, (int)(x.nodes >> kStPrio));
   }
-  long long run = part[tid] - s;
+  for (int w = tid; w < R; w += 1024) a += __popcll(prow[w]);
+  long long upto = s;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const long long y = __shfl_up(upto, off, kWave);
+    if (lane >= off) upto += y;
+    b += __shfl_xor(b, off, kWave);
+    a += __shfl_xor(a, off, kWave);
+    pr = max(pr, __shfl_xor(pr, off, kWave));
+  }
+  if (lane == kWave - 1) {
+    nodes[wave] = upto;
+    bits[wave] = b;
+    deg[wave] = a;
+    prio[wave] = pr;
+  }
+  __syncthreads();
+  long long run = upto - s, all = 0, na = 0;
+  b = 0;
+  pr = P_NONE;
+  for (int i = 0; i < 16; ++i) {
+    if (i < wave) run += nodes[i];
+    all += nodes[i];
+    b += bits[i];
+    na += deg[i];
+    pr = max(pr, prio[i]);
+  }
   for (int v = lo; v < hi; ++v) {
     coff[v] = run;
-    run += ccount[v];
+    run += in[v].nodes & ((1u << kStPrio) - 1);
   }
-  if (tid == 1023) {
-    coff[n] = part[1023];
+  if (tid == 0) {
+    coff[n] = all;
     h->na = na;
-    h->nc = part[1023];
+    h->nc = all;
+    h->edges2 = b;
+    h->prio = pr;
+    h->fits = pr == P_NONE && na + all <= out_nodes && (na + all + 63) / 64 <= out_words;
   }
 }
 
-// The node map: (v, -1) for A nodes, (x, y) for C nodes (one thread per vertex).
-__global__ void __launch_bounds__(256) k_st_map(const uint64_t *__restrict__ rows, int n, int R,
-                                                const uint64_t *__restrict__ bmask, const int *__restrict__ apos,
-                                                const long long *__restrict__ coff, long long na,
-                                                int *__restrict__ map) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  if (apos[v] >= 0) {
-    map[2LL * apos[v]] = v;
-    map[2LL * apos[v] + 1] = -1;
-    return;
+// The node map -- (v, -1) for A nodes, (x, y) for C nodes -- and M[v], bit t
+// of word j = v ~ A[64 j + t].  One wave per vertex.
+__global__ void __launch_bounds__(kStWaves * kWave) k_st_map(const uint64_t *__restrict__ rows, int n, int R, int pivot,
+                                                             const int *__restrict__ alist,
+                                                             const long long *__restrict__ coff,
+                                                             const StHdr *__restrict__ h, int *__restrict__ map,
+                                                             uint64_t *__restrict__ M) {
+  const int lane = threadIdx.x & 63, v = blockIdx.x * kStWaves + (threadIdx.x >> 6);
+  if (v >= n || !h->fits) return;
+  const int na = (int)h->na, RA = (na + 63) / 64;
+  const uint64_t *row = rows + (long long)v * R, *prow = rows + (long long)pivot * R;
+  if (v < na && lane == 0) {
+    map[2LL * v] = alist[v];
+    map[2LL * v + 1] = -1;
   }
-  if (!bit(bmask, v)) return;
-  const uint64_t *rv = rows + (long long)v * R;
+  for (int j = 0; j < RA; ++j) {
+    const int t = 64 * j + lane;
+    const unsigned long long m = __ballot(t < na && bit(row, alist[t]));
+    if (lane == 0) M[(long long)v * RA + j] = m;
+  }
+  if (v == pivot || bit(prow, v)) return;
   long long at = na + coff[v];
-  const int vw = v >> 6;
-  for (int w = vw; w < R; ++w) {
-    uint64_t x = rv[w] & bmask[w];
-    if (w == vw) x &= (v & 63) == 63 ? 0ull : ~0ull << ((v & 63) + 1);
+  for (int w0 = 0; w0 < R; w0 += kWave) {
+    const int w = w0 + lane;
+    uint64_t x = w < R ? row[w] & b_word(prow, pivot, n, w) & above(v, w) : 0ull;
+    int upto = __popcll(x);
+    const int cnt = upto;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int y = __shfl_up(upto, off, kWave);
+      if (lane >= off) upto += y;
+    }
+    long long p = at + upto - cnt;
     while (x) {
       const int y = 64 * w + __builtin_ctzll(x);
       x &= x - 1;
-      map[2 * at] = v;
-      map[2 * at + 1] = y;
-      ++at;
+      map[2 * p] = v;
+      map[2 * p + 1] = y;
+      ++p;
     }
+    at += __shfl(upto, kWave - 1, kWave);
   }
 }
 
-// M[v][j] bit t = v ~ A[64 j + t] (one thread per word of M).
-__global__ void __launch_bounds__(256) k_st_compress(const uint64_t *__restrict__ rows, int n, int R,
-                                                     const int *__restrict__ map, int na, int RA,
-                                                     uint64_t *__restrict__ M) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long long)n * RA) return;
-  const int v = (int)(i / RA), j = (int)(i % RA);
-  const uint64_t *rv = rows + (long long)v * R;
-  uint64_t x = 0;
-  for (int t = 0; t < 64 && 64 * j + t < na; ++t)
-    if (bit(rv, map[2 * (64 * j + t)])) x |= 1ull << t;
-  M[i] = x;
-}
-
-// One output word: node i's adjacency to the nodes 64 j .. 64 j + 63.
-__global__ void __launch_bounds__(256) k_st_rows(const uint64_t *__restrict__ rows, int R,
-                                                 const uint64_t *__restrict__ M, int RA,
-                                                 const int *__restrict__ map, const long long *__restrict__ coff,
-                                                 long long na, long long np, int RP, uint64_t *__restrict__ out) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= np * RP) return;
-  const long long i = idx / RP;
-  const int j = (int)(idx % RP);
-  const long long lo = 64LL * j;
-  uint64_t x = 0;
-  if (lo < np) {
-    const int xi = map[2 * i], yi = map[2 * i + 1];
-    // A part: nodes lo .. min(lo + 64, na)
-    if (lo < na) {
-      uint64_t a = M[(long long)xi * RA + j];
-      if (yi >= 0) a &= M[(long long)yi * RA + j];
-      if (na - lo < 64) a &= (1ull << (na - lo)) - 1;
-      x |= a;
+// G'.  The first RP waves take the A nodes' rows, word j of all of them each:
+// lane q holds what node 64 j + q has in A, 64 of A at a time, and the
+// transpose is those 64 rows' word.  The others take a C node's row each: the
+// words of its own block by a ballot, the others (A part and zeros) a lane a
+// word.  Bounded by the writes: 1000 vertices at p = 0.1, 206 MB, 31 to 41 us
+// (a copy's rate); a thread per word that divided its index by RP and looped
+// over the word's nodes took 180.
+__global__ void __launch_bounds__(kStWaves * kWave) k_st_rows(const uint64_t *__restrict__ rows, int R,
+                                                              const uint64_t *__restrict__ M,
+                                                              const int *__restrict__ map,
+                                                              const long long *__restrict__ coff,
+                                                              const StHdr *__restrict__ h, int RP,
+                                                              uint64_t *__restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  if (!h->fits) return;
+  const long long na = h->na, np = na + h->nc;
+  const int RA = (int)((na + 63) / 64);
+  const long long step = (long long)gridDim.x * kStWaves;
+  long long i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kStWaves + (threadIdx.x >> 6)));
+  for (; i < RP; i += step) {
+    const long long q = 64 * i + lane;
+    const uint64_t *mx = M, *my = M;
+    if (q < np) {
+      const int x = map[2 * q], y = map[2 * q + 1];
+      mx += (long long)x * RA;
+      my += (long long)(y < 0 ? x : y) * RA;
     }
-    // C part: nodes max(lo, na) .. min(lo + 64, np)
-    const long long c0 = lo > na ? lo : na, c1 = lo + 64 < np ? lo + 64 : np;
-    if (c0 < c1) {
-      if (yi < 0) {
-        const uint64_t *ra = rows + (long long)xi * R;
-        for (long long q = c0; q < c1; ++q) {
-          const int xq = map[2 * q], yq = map[2 * q + 1];
-          if (bit(ra, xq) && bit(ra, yq)) x |= 1ull << (q - lo);
-        }
-      } else {
-        // only the block of C nodes whose first vertex is xi
-        const long long b0 = na + coff[xi], b1 = na + coff[xi + 1];
-        const long long s0 = c0 > b0 ? c0 : b0, s1 = c1 < b1 ? c1 : b1;
-        const uint64_t *ry = rows + (long long)yi * R;
-        for (long long q = s0; q < s1; ++q)
-          if (bit(ry, map[2 * q + 1])) x |= 1ull << (q - lo);
-      }
+    for (int j = 0; j < RA; ++j) {
+      const unsigned long long col = wave_transpose64(q < np ? mx[j] & my[j] : 0ull, lane);
+      const long long a = 64LL * j + lane;
+      if (a < na) out[a * RP + i] = col;
     }
-    if (i >= lo && i < lo + 64) x &= ~(1ull << (i - lo));
   }
-  out[idx] = x;
+  for (i += na - RP; i < np; i += step) {
+    const int x = __builtin_amdgcn_readfirstlane(map[2 * i]), y = __builtin_amdgcn_readfirstlane(map[2 * i + 1]);
+    const long long b0 = na + coff[x], b1 = na + coff[x + 1];  // the C nodes of x; not empty, this is one
+    const int s0 = (int)(b0 >> 6), s1 = (int)((b1 - 1) >> 6) + 1;
+    const uint64_t *mx = M + (long long)x * RA, *my = M + (long long)y * RA, *ry = rows + (long long)y * R;
+    uint64_t *row = out + i * RP;
+    for (int j = lane; j < RP; j += kWave)
+      if (j < s0 || j >= s1) row[j] = j < RA ? mx[j] & my[j] : 0ull;
+    for (int j = s0; j < s1; ++j) {
+      const long long q = 64LL * j + lane;
+      const unsigned long long c = __ballot(q >= b0 && q < b1 && bit(ry, map[2 * q + 1]));  // y !~ y: no diagonal
+      if (lane == 0) row[j] = c | (j < RA ? mx[j] & my[j] : 0ull);
+    }
+  }
 }
 
 struct StWs {
-  size_t hdr, bmask, apos, ccount, coff, M, total;
+  size_t hdr, alist, row, coff, M, total;
 };
 
 StWs st_ws(int n, int R) {
@@ -228,9 +255,8 @@ StWs st_ws(int n, int R) {
     return at;
   };
   z.hdr = take(sizeof(StHdr));
-  z.bmask = take(sizeof(uint64_t) * (size_t)(R > 0 ? R : 1));
-  z.apos = take(sizeof(int) * (size_t)(n > 0 ? n : 1));
-  z.ccount = take(sizeof(long long) * (size_t)(n > 0 ? n : 1));
+  z.alist = take(sizeof(int) * (size_t)(n > 0 ? n : 1));
+  z.row = take(sizeof(StRow) * (size_t)(n > 0 ? n : 1));
   z.coff = take(sizeof(long long) * (size_t)(n + 1));
   z.M = take(sizeof(uint64_t) * (size_t)(n > 0 ? n : 1) * (size_t)(R > 0 ? R : 1));
   z.total = o;
@@ -275,17 +301,24 @@ int kz_struction(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
   hipStream_t s = (hipStream_t)stream;
   char *base = (char *)ws;
   StHdr *h = (StHdr *)(base + z.hdr);
-  uint64_t *bmask = (uint64_t *)(base + z.bmask);
-  int *apos = (int *)(base + z.apos);
-  long long *ccount = (long long *)(base + z.ccount);
+  int *alist = (int *)(base + z.alist);
+  StRow *row = (StRow *)(base + z.row);
   long long *coff = (long long *)(base + z.coff);
   uint64_t *M = (uint64_t *)(base + z.M);
   const int R = row_words;
-  if (hipMemsetAsync(h, 0, sizeof(StHdr), s) != hipSuccess) return done(KZ_EHIP);
-  {
-    const long long words = (long long)n * R;
-    const int grid = (int)std::max<long long>(std::min<long long>((words + 255) / 256, 4096), (R + 255) / 256);
-    hipLaunchKernelGGL(k_st_check, dim3(grid), dim3(256), 0, s, rows, n, R, pivot, bmask, h);
+  const dim3 grid((unsigned)((n + kStWaves - 1) / kStWaves)), block(kStWaves * kWave);
+  // outputs that cannot hold a node are not written: the plan alone then
+  const bool build = out && map && out_nodes > 0 && out_row_words > 0;
+  hipLaunchKernelGGL(k_st_check, grid, block, 0, s, rows, n, R, pivot, alist, row);
+  hipLaunchKernelGGL(k_st_scan, dim3(1), dim3(1024), 0, s, row, rows + (long long)pivot * R, n, R,
+                     build ? out_nodes : -1, out_row_words, coff, h);
+  if (build) {
+    // a wave per node the output can hold, and no more than G' can have
+    const long long most = std::min<long long>(out_nodes, (long long)n * n / 2 + n) + out_row_words;
+    const unsigned blocks = (unsigned)std::min<long long>((most + kStWaves - 1) / kStWaves, 1 << 24);
+    hipLaunchKernelGGL(k_st_map, grid, block, 0, s, rows, n, R, pivot, alist, coff, h, map, M);
+    hipLaunchKernelGGL(k_st_rows, dim3(blocks), block, 0, s, rows, R, M,
+                       map, coff, h, out_row_words, out);
   }
   StHdr *hh = (StHdr *)ctx->pinned;
   if (hipGetLastError() != hipSuccess || hipMemcpyAsync(hh, h, sizeof(StHdr), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -294,21 +327,6 @@ int kz_struction(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
   r.input_edges = hh->edges2 / 2;
   const int st0 = st_status(hh->prio);
   if (st0 != KZ_OK) return done(st0);
-  hipLaunchKernelGGL(k_st_count, dim3((n + 255) / 256), dim3(256), 0, s, rows, n, R, pivot, bmask, apos, ccount);
-  // |A| = the pivot's degree, from its row
-  int na = 0;
-  {
-    std::vector<uint64_t> rp(R);
-    if (hipMemcpyAsync(rp.data(), rows + (long long)pivot * R, sizeof(uint64_t) * R, hipMemcpyDeviceToHost, s) !=
-            hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return done(KZ_EHIP);
-    for (int w = 0; w < R; ++w) na += __builtin_popcountll(rp[w]);
-  }
-  hipLaunchKernelGGL(k_st_scan, dim3(1), dim3(1024), 0, s, ccount, n, na, coff, h);
-  if (hipGetLastError() != hipSuccess || hipMemcpyAsync(hh, h, sizeof(StHdr), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return done(KZ_EHIP);
   const long long np = hh->na + hh->nc;
   r.a_nodes = hh->na;
   r.c_nodes = hh->nc;
@@ -316,18 +334,6 @@ int kz_struction(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
   r.row_words = (int32_t)((np + 63) / 64);
   if (!out) return done(KZ_OK);  // plan only
   if (!map || out_nodes < np || out_row_words < (np + 63) / 64) return done(KZ_EWORKSPACE);
-  if (np == 0) return done(KZ_OK);
-  const int RA = (int)((hh->na + 63) / 64);
-  hipLaunchKernelGGL(k_st_map, dim3((n + 255) / 256), dim3(256), 0, s, rows, n, R, bmask, apos, coff, hh->na, map);
-  if (RA > 0) {
-    const long long mw = (long long)n * RA;
-    hipLaunchKernelGGL(k_st_compress, dim3((unsigned)((mw + 255) / 256)), dim3(256), 0, s, rows, n, R, map,
-                       (int)hh->na, RA, M);
-  }
-  const long long ow = np * out_row_words;
-  hipLaunchKernelGGL(k_st_rows, dim3((unsigned)((ow + 255) / 256)), dim3(256), 0, s, rows, R, M, RA, map, coff,
-                     hh->na, np, out_row_words, out);
-  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return done(KZ_EHIP);
   return done(KZ_OK);
 }
 
