@@ -327,7 +327,8 @@ int kz_batch_get_config(const kz_ctx *ctx, kz_batch_config *cfg);
  * GPU_MAX_HW_QUEUES, 4 by default) streams share queues, and a short
  * kernel can wait behind a long one of another lane; work on a stream that
  * shares the session launch's queue (the caller's input stream, say) waits
- * for that launch to end, up to lease_us.
+ * for that launch to end, up to lease_us -- or, once a launch has nothing to
+ * do, about 2 ms: a worker's or an input's wait that long ends it early.
  *
  * A request is a KZ_BITSET_U64 graph in caller-owned device buffers (vmask
  * and emask 128-byte aligned, else KZ_EINVAL); results are the same as

@@ -1153,9 +1153,9 @@ __device__ int find_job(const BatchArgs &a, BatchLds &S, unsigned least) {
   return S.pick;
 }
 
-// Session mode (thread 0): refreshes the device's copy of the host's
-// request count.  The count lives in pinned host memory; one workgroup at a
-// time reads it, at most every kHostPoll ticks.
+// Session mode (thread 0): refreshes the device's copies of the host's
+// request count and of the launch it asked to end.  They live in pinned host memory; one workgroup at a
+// time reads them, at most every kHostPoll ticks.
 __device__ void poll_host(const BatchArgs &a) {
   const unsigned long long now = wall_clock64();
   unsigned long long last = ald(a.hpoll);
@@ -1163,9 +1163,11 @@ __device__ void poll_host(const BatchArgs &a) {
                                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
     return;
   const unsigned long long hh = __hip_atomic_load(a.head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  const unsigned long long hy = __hip_atomic_load(a.head + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   // the copy is written after the count's load has returned (it is the
   // operand); a taker's own acquire orders its reads of the host tables
   if (hh > ald(a.dhead)) __hip_atomic_fetch_max(a.dhead, hh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (hy > ald(a.dhead + 1)) __hip_atomic_fetch_max(a.dhead + 1, hy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Session mode (thread 0): takes the next published request, if any, and
@@ -1261,7 +1263,9 @@ __global__ void __launch_bounds__(NW * 64, 4) k_batch(BatchArgs a) {
       const unsigned long long now = wall_clock64();
       if (!idle0) idle0 = now;
       // a session's workgroups stay for new requests until idle for idle_ticks
-      S.quit = a.session ? now - idle0 > a.idle_ticks || (a.lease_ticks && now - born > a.lease_ticks)
+      // or, once the host has asked this launch to end, until idle
+      S.quit = a.session ? now - idle0 > a.idle_ticks || (a.lease_ticks && now - born > a.lease_ticks) ||
+                               ald(a.dhead + 1) >= a.launch
                          : __hip_atomic_load(a.finished, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= a.G ||
                                now - idle0 > kIdleTicks;
     }

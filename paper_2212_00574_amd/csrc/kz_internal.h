@@ -291,7 +291,9 @@ struct BatchArgs {
   int cap;                            // ring length (>= slots)
   unsigned *ring;                     // [cap] slot of the request at each sequence number;
                                       // the device marks an entry it has read kRingFree
-  const unsigned long long *head;     // requests published (host-written)
+  const unsigned long long *head;     // requests published (host-written), and behind it the number of
+                                      // the last launch asked to end when idle
+  unsigned long long launch;          // this launch's number
   const kz_batch_graph *hgraphs;      // [slots] descriptors (row/vertex offsets unused)
   const BatchPtrs *hptrs;             // [slots] buffers
   const unsigned long long *htickets; // [slots] the request's ticket

@@ -29,8 +29,14 @@
 // the other units to this lane's kernels.  Each workgroup also takes no new
 // request once lease_us has passed since it started, so a launch ends
 // within about lease_us under load and whatever waits behind it on a shared
-// hardware queue runs; the host then starts the next.  Both lanes share the
-// request table and the arena heap under one mutex.
+// hardware queue runs; the host then starts the next.  A launch that has
+// nothing left to do would still hold its queue that long, and a worker whose
+// stream shares it (there are more streams than queues) waits with its request,
+// as the caller's inputs may: when a worker's slice or an input-ready event has
+// been out for kYieldUs and the session lane is empty the host asks the launch
+// to end.  (96 requests of 200 to 12 000 vertices: 11.0
+// ms, the lease, without; the lanes alone take 1.3 and 3.9 ms.)  Both lanes
+// share the request table and the arena heap under one mutex.
 #include <string.h>
 
 #include <atomic>
@@ -56,6 +62,7 @@ constexpr int kMaxWorkers = 8;     // single-graph lane: requests in flight at o
 constexpr int kDefaultWorkers = 6;
 constexpr int kMaxFences = 16;     // input-ready events in flight
 constexpr double kRelaunchUs = 500;  // untaken requests behind a running launch: queue another
+constexpr double kYieldUs = 2000;    // other work out this long: an idle session launch ends
 constexpr int kSlicePasses = 2;    // single-graph lane: passes a request runs before the next one's turn
 constexpr size_t kOutBytes = 256;  // its kz_out, after its workspace
 static_assert(sizeof(kz_out) <= kOutBytes, "a request's kz_out fits its slot");
@@ -93,7 +100,7 @@ FixedLayout fixed_layout(int slots) {
     o += up(b);
     return at;
   };
-  L.ctl = take(3 * kLine);  // queue, count copy, poll time
+  L.ctl = take(3 * kLine);  // queue, copies of the count and of the launch to end, poll time
   L.board = take(sizeof(int) * (size_t)board_size(slots));
   L.jobs = take(sizeof(kzi::BatchJob) * (size_t)slots);
   L.total = o;
@@ -114,7 +121,7 @@ HostLayout host_layout(int slots, int cap) {
     return at;
   };
   L.ring = take(sizeof(unsigned) * (size_t)cap);
-  L.head = take(sizeof(unsigned long long));
+  L.head = take(2 * sizeof(unsigned long long));  // requests published, launch to end
   L.graphs = take(sizeof(kz_batch_graph) * (size_t)slots);
   L.ptrs = take(sizeof(kzi::BatchPtrs) * (size_t)slots);
   L.tickets = take(sizeof(unsigned long long) * (size_t)slots);
@@ -174,12 +181,13 @@ struct Req {
   kz_result res;
 };
 
+using Clock = std::chrono::steady_clock;
+
 struct Fence {
   hipEvent_t ev;
   size_t count;  // pending requests it covers
+  Clock::time_point since;
 };
-
-using Clock = std::chrono::steady_clock;
 
 }  // namespace
 
@@ -211,6 +219,7 @@ struct kz_server {
   std::vector<hipEvent_t> evpool;
   uint64_t published;
   std::deque<hipEvent_t> launches;  // session launches in flight on sstream
+  unsigned long long launched;      // session launches so far (the last one's number)
   bool untaken_seen;
   Clock::time_point untaken_since;
   std::unordered_map<uint64_t, Req> reqs;
@@ -226,6 +235,8 @@ struct kz_server {
   kz_ctx *wctx[kMaxWorkers];  // each worker's context (its own readback buffer)
   hipStream_t wstream[kMaxWorkers];
   std::thread worker[kMaxWorkers];
+  bool out[kMaxWorkers];  // a slice is out since out_since
+  Clock::time_point out_since[kMaxWorkers];
   std::mutex mu;  // everything above that both lanes touch
   std::condition_variable cv;
   std::deque<uint64_t> big;
@@ -289,6 +300,8 @@ void work(kz_server *s, int id) {
       Req &r = s->reqs[t];
       r.state = 1;
       q = r;
+      s->out[id] = true;
+      s->out_since[id] = Clock::now();
     }
     const int first = q.next_pass > 0 ? q.next_pass : 1;
     kz_out o{};
@@ -313,6 +326,7 @@ void work(kz_server *s, int id) {
       }
     }
     std::lock_guard<std::mutex> g(s->mu);
+    s->out[id] = false;
     Req &r = s->reqs[t];
     if (!o.converged) {
       r.next_pass = first + kSlicePasses;
@@ -373,7 +387,7 @@ int set_workers(kz_server *s, int n) {
 // caller's stream (caller holds mu).
 int cover(kz_server *s) {
   if (s->pending.size() <= s->covered || (int)s->fences.size() >= kMaxFences) return KZ_OK;
-  Fence f{take_event(s), s->pending.size() - s->covered};
+  Fence f{take_event(s), s->pending.size() - s->covered, Clock::now()};
   if (!f.ev) return KZ_EHIP;
   if (hipEventRecord(f.ev, s->stream) != hipSuccess) {
     s->evpool.push_back(f.ev);
@@ -436,6 +450,7 @@ int launch_session(kz_server *s) {
   a.htickets = (const unsigned long long *)(s->host_dev + s->H.tickets);
   a.hres = (kz_result *)(s->host_dev + s->H.res);
   a.hdone = (unsigned long long *)(s->host_dev + s->H.done);
+  a.launch = s->launched + 1;
   a.idle_ticks = (unsigned long long)s->idle_us * (unsigned long long)s->clock_khz / 1000ull;
   a.lease_ticks = (unsigned long long)s->lease_us * (unsigned long long)s->clock_khz / 1000ull;
   kzi::BatchConfig c = s->ctx->batch_cfg;
@@ -447,7 +462,22 @@ int launch_session(kz_server *s) {
     return KZ_EHIP;
   }
   s->launches.push_back(e);
+  ++s->launched;
   return KZ_OK;
+}
+
+// The session lane has no request to run, and a slice of the other lane or the
+// inputs of the next requests may wait for its launch to end.
+bool should_yield(const kz_server *s) {
+  if (!s->running.empty() || s->ready > 0) return false;
+  const Clock::time_point now = Clock::now();
+  auto waits = [&now](Clock::time_point since) {
+    return std::chrono::duration<double, std::micro>(now - since).count() > kYieldUs;
+  };
+  if (!s->fences.empty() && waits(s->fences.front().since)) return true;
+  for (int i = 0; i < kMaxWorkers; ++i)
+    if (s->out[i] && waits(s->out_since[i])) return true;
+  return false;
 }
 
 // One step of the session lane (caller holds mu).
@@ -504,6 +534,8 @@ int step(kz_server *s) {
       __atomic_load_n(&s->ring[(s->published - 1) % (uint64_t)s->cap], __ATOMIC_ACQUIRE) != kzi::kRingFree;
   if (!untaken) {
     s->untaken_seen = false;
+    if (!s->launches.empty() && s->head[1] != s->launched && should_yield(s))
+      __atomic_store_n(s->head + 1, s->launched, __ATOMIC_RELEASE);
     return KZ_OK;
   }
   if (s->launches.empty()) {
@@ -596,6 +628,7 @@ int kz_server_create(kz_ctx *ctx, void *arena, size_t arena_bytes, int32_t max_s
   s->covered = s->ready = 0;
   s->published = 0;
   s->untaken_seen = false;
+  s->launched = 0;
   s->next_ticket = 1;
   s->admitted = 0;
   s->split_n = kDefaultSplitN;
@@ -611,6 +644,7 @@ int kz_server_create(kz_ctx *ctx, void *arena, size_t arena_bytes, int32_t max_s
   for (int i = 0; i < kMaxWorkers; ++i) {
     s->wctx[i] = nullptr;
     s->wstream[i] = nullptr;
+    s->out[i] = false;
   }
   if (hipSetDevice(ctx->device) != hipSuccess ||
       hipDeviceGetAttribute(&s->clock_khz, hipDeviceAttributeWallClockRate, ctx->device) != hipSuccess ||
