@@ -455,7 +455,9 @@ int kz_create(kz_ctx **out, int device) {
     c->launches[i] = 0;
   }
   if (hipSetDevice(device) != hipSuccess ||
-      hipHostMalloc((void **)&c->pinned, sizeof(kzi::Hdr), hipHostMallocDefault) != hipSuccess) {
+      hipHostMalloc(&c->pinned, kzi::kPinnedBytes, hipHostMallocDefault) != hipSuccess ||
+      hipHostGetDevicePointer(&c->pinned_dev, c->pinned, 0) != hipSuccess) {
+    if (c->pinned) (void)hipHostFree(c->pinned);
     delete c;
     return KZ_EHIP;
   }
@@ -673,17 +675,14 @@ int kz_kernelize(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_t 
   // runs end there, and a surplus pass still dispatches its grids), then
   // doubling chunks through the tail of a long cascade.  The dense output
   // is unpacked once, after the fixpoint.
-  const kzi::Hdr *hdr = (const kzi::Hdr *)ws;
   int next = 1, chunk = 1;
   for (;;) {
-    if (enqueue_passes(ctx, g, colour, k, (char *)ws, z, mfma, vmask, emask, next, chunk, false, s, nullptr) !=
-        KZ_OK)
+    if (enqueue_passes(ctx, g, colour, k, (char *)ws, z, mfma, vmask, emask, next, chunk, false, s,
+                       (kz_out *)ctx->pinned_dev) != KZ_OK)
       return finish(res, r);
-    if (hipMemcpyAsync(ctx->pinned, hdr, sizeof(kzi::Hdr), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return finish(res, r);
+    if (hipStreamSynchronize(s) != hipSuccess) return finish(res, r);
     prof_collect(ctx);
-    const kz_out &o = ctx->pinned->out;
+    const kz_out &o = *(const kz_out *)ctx->pinned;
     if (o.converged) {
       r = o.result;
       break;

@@ -85,6 +85,13 @@ struct ClqHdr {
   int coff[kBatchK + 1], soff[kBatchK + 1];
 };
 
+// What the host gets.
+struct ClqOut {
+  long long best, nodes, last, live0;
+  int s0, s1;  // vertices of classes 0 and 1 (1 when k = 1)
+  int bad_colour, bad_layout;
+};
+
 // Layout from the sorted colours (one workgroup): class starts by binary
 // search, segment offsets, and the checks (colours in range, sorted, row
 // words = sum of the class segments).
@@ -295,7 +302,7 @@ __global__ void __launch_bounds__(kClqWaves * 64) k_clique_search(const uint64_t
                                                                   unsigned long long *__restrict__ omask,
                                                                   long long *__restrict__ found_root,
                                                                   int *__restrict__ found_pick,
-                                                                  int32_t *__restrict__ clique) {
+                                                                  int32_t *__restrict__ clique, ClqOut *host) {
   __shared__ uint64_t lstack[LDS ? kClqWaves * kClqLdsWords : 1];
   __shared__ int pick_s[kClqWaves][kWave];  // the picks of the list at hand: node << kClqSubBits | class's vertex
   __shared__ int path_s[LDS ? 1 : kClqWaves][LDS ? 1 : kBatchK];
@@ -307,7 +314,10 @@ __global__ void __launch_bounds__(kClqWaves * 64) k_clique_search(const uint64_t
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int slot = blockIdx.x * kClqWaves + wid;
   if (h->bad_colour || h->bad_layout) {
-    if (blockIdx.x == 0 && threadIdx.x < k) clique[threadIdx.x] = -1;
+    if (blockIdx.x == 0) {
+      if (threadIdx.x < k) clique[threadIdx.x] = -1;
+      if (threadIdx.x == 0) *host = ClqOut{kClqNone, 0, 0, 0, 0, 0, h->bad_colour, h->bad_layout};
+    }
     return;
   }
   for (int c = threadIdx.x; c <= k; c += blockDim.x) {
@@ -714,12 +724,16 @@ __global__ void __launch_bounds__(kClqWaves * 64) k_clique_search(const uint64_t
     if (wg_nodes) atomicAdd((unsigned long long *)&h->nodes, wg_nodes);
     if (wg_last) atomicMax(&h->last, wg_last);
     if (wg_found) __threadfence();
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the sums above come before the ticket
     ticket = atomicAdd(&h->done, 1u);
   }
   __syncthreads();
   if (ticket != gridDim.x - 1) return;
   __threadfence();
   const long long best = __hip_atomic_load(&h->best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0)
+    *host = ClqOut{best, __hip_atomic_load(&h->nodes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                   __hip_atomic_load(&h->last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), h->live0, s0, s1, 0, 0};
   if (best == kClqNone) {
     for (int c = threadIdx.x; c < k; c += blockDim.x) clique[c] = -1;
     return;
@@ -806,23 +820,20 @@ int kz_find_clique(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_
   const dim3 grid(kClqMaxWaves / kClqWaves), block(kClqWaves * 64);
   if (words <= kClqLdsWords)
     hipLaunchKernelGGL(k_clique_search<true>, grid, block, 0, s, g->rows, k, R, am, pre, h, stack, share,
-                       omask, froot, fpick, clique);
+                       omask, froot, fpick, clique, (ClqOut *)ctx->pinned_dev);
   else
     hipLaunchKernelGGL(k_clique_search<false>, grid, block, 0, s, g->rows, k, R, am, pre, h, stack, share, omask,
-                       froot, fpick, clique);
-  ClqHdr *hh = (ClqHdr *)ctx->pinned;
-  if (hipGetLastError() != hipSuccess ||
-      hipMemcpyAsync(hh, h, sizeof(ClqHdr), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return done(KZ_EHIP);
+                       froot, fpick, clique, (ClqOut *)ctx->pinned_dev);
+  const ClqOut *hh = (const ClqOut *)ctx->pinned;
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return done(KZ_EHIP);
   if (hh->bad_colour) return done(KZ_ECOLOUR);
   if (hh->bad_layout) return done(KZ_EINVAL);
   r.found = hh->best != kClqNone;
   r.nodes = hh->nodes;
-  const long long nroots = (long long)(hh->coff[1] - hh->coff[0]) * (k > 1 ? hh->coff[2] - hh->coff[1] : 1);
+  const long long nroots = (long long)hh->s0 * hh->s1;
   r.roots = r.found ? hh->last : nroots;
   // the first picks: a live class-0 vertex for every pair up to there
-  if (k > 1) r.nodes += std::min<long long>(r.roots, hh->live0 * (hh->coff[2] - hh->coff[1]));
+  if (k > 1) r.nodes += std::min<long long>(r.roots, hh->live0 * hh->s1);
   return done(KZ_OK);
 }
 

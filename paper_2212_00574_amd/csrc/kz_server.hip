@@ -64,8 +64,6 @@ constexpr int kMaxFences = 16;     // input-ready events in flight
 constexpr double kRelaunchUs = 500;  // untaken requests behind a running launch: queue another
 constexpr double kYieldUs = 2000;    // other work out this long: an idle session launch ends
 constexpr int kSlicePasses = 2;    // single-graph lane: passes a request runs before the next one's turn
-constexpr size_t kOutBytes = 256;  // its kz_out, after its workspace
-static_assert(sizeof(kz_out) <= kOutBytes, "a request's kz_out fits its slot");
 constexpr int kDefaultSplitN = 2048;
 constexpr int kDefaultIdleUs = 20000;
 constexpr int kDefaultLeaseUs = 10000;
@@ -315,13 +313,11 @@ void work(kz_server *s, int id) {
       gr.n = q.r.n;
       gr.rows = q.r.rows;
       gr.row_words = q.r.row_words;
-      kz_out *dout = (kz_out *)(s->arena + q.at + q.bytes - kOutBytes);
-      const int st = kz_kernelize_async(ctx, &gr, q.r.colour, q.r.k, s->arena + q.at, q.bytes - kOutBytes,
-                                        q.r.vmask, q.r.emask, first, kSlicePasses, stream, dout);
+      const int st = kz_kernelize_async(ctx, &gr, q.r.colour, q.r.k, s->arena + q.at, q.bytes, q.r.vmask, q.r.emask,
+                                        first, kSlicePasses, stream, (kz_out *)ctx->pinned_dev);
       if (st != KZ_OK) {
         o.result.status = st;
-      } else if (hipMemcpyAsync(ctx->pinned, dout, sizeof(kz_out), hipMemcpyDeviceToHost, stream) == hipSuccess &&
-                 hipStreamSynchronize(stream) == hipSuccess) {
+      } else if (hipStreamSynchronize(stream) == hipSuccess) {
         o = *(const kz_out *)ctx->pinned;
       }
     }
@@ -575,7 +571,7 @@ int single_bytes(kz_ctx *ctx, const kz_request &r, size_t *bytes) {
   gr.rows = r.rows;
   gr.row_words = r.row_words;
   const int st = kz_workspace_bytes(ctx, &gr, r.k, bytes);
-  *bytes = up(*bytes) + kOutBytes;  // and the result the device writes after every pass
+  *bytes = up(*bytes);
   return st;
 }
 

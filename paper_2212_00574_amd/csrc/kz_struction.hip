@@ -91,10 +91,11 @@ __global__ void __launch_bounds__(kStWaves * kWave) k_st_check(const uint64_t *_
   }
 }
 
-// Scan of the counts into C offsets, and the header (one workgroup).
+// Scan of the counts into C offsets, and the header, here and for the host
+// (one workgroup).
 __global__ void __launch_bounds__(1024) k_st_scan(const StRow *__restrict__ in, const uint64_t *__restrict__ prow, int n,
                                                  int R, long long out_nodes, int out_words,
-                                                 long long *__restrict__ coff, StHdr *h) {
+                                                 long long *__restrict__ coff, StHdr *h, StHdr *host) {
   __shared__ long long nodes[16], bits[16];
   __shared__ int prio[16], deg[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -146,6 +147,7 @@ __global__ void __launch_bounds__(1024) k_st_scan(const StRow *__restrict__ in, 
     h->edges2 = b;
     h->prio = pr;
     h->fits = pr == P_NONE && na + all <= out_nodes && (na + all + 63) / 64 <= out_words;
+    *host = *h;
   }
 }
 
@@ -311,7 +313,7 @@ int kz_struction(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
   const bool build = out && map && out_nodes > 0 && out_row_words > 0;
   hipLaunchKernelGGL(k_st_check, grid, block, 0, s, rows, n, R, pivot, alist, row);
   hipLaunchKernelGGL(k_st_scan, dim3(1), dim3(1024), 0, s, row, rows + (long long)pivot * R, n, R,
-                     build ? out_nodes : -1, out_row_words, coff, h);
+                     build ? out_nodes : -1, out_row_words, coff, h, (StHdr *)ctx->pinned_dev);
   if (build) {
     // a wave per node the output can hold, and no more than G' can have
     const long long most = std::min<long long>(out_nodes, (long long)n * n / 2 + n) + out_row_words;
@@ -320,10 +322,8 @@ int kz_struction(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
     hipLaunchKernelGGL(k_st_rows, dim3(blocks), block, 0, s, rows, R, M,
                        map, coff, h, out_row_words, out);
   }
-  StHdr *hh = (StHdr *)ctx->pinned;
-  if (hipGetLastError() != hipSuccess || hipMemcpyAsync(hh, h, sizeof(StHdr), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return done(KZ_EHIP);
+  const StHdr *hh = (const StHdr *)ctx->pinned;
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return done(KZ_EHIP);
   r.input_edges = hh->edges2 / 2;
   const int st0 = st_status(hh->prio);
   if (st0 != KZ_OK) return done(st0);
