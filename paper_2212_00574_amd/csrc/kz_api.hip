@@ -345,6 +345,19 @@ int check_call(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_t k,
   return KZ_OK;
 }
 
+// Whether a blocking call runs in one workgroup with the graph in LDS.  That
+// takes 26 us and 2 to 15 a pass, the general path 35 (dense 54) and 27 a pass;
+// the lines lie where a dense graph that ends in one pass takes the same on
+// both: dense, 8 classes at p = 0.8: 130 vertices 57 and 58 us, 180 vertices 79
+// and 59; bit rows, 100 vertices 40 and 38 us, 64 in 30 classes 64 and 62.
+// Not with the timing of the kernels on, which it counts by the general path's
+// parts.
+bool small_call(const kz_ctx *ctx, const kz_graph *g, int32_t k, const kzi::WsSizes &z, bool mfma) {
+  if (g->format == KZ_CSR || mfma || ctx->prof || k > kzi::kSmallK || z.Rmax > kzi::kSmallR) return false;
+  if (g->format == KZ_BITSET_U64 && (g->n > 80 || z.Rmax > 16)) return false;
+  return g->n <= kzi::kSmallN && g->n * (z.Rmax | 1) <= kzi::kSmallWords;
+}
+
 // Enqueues setup (first_pass == 1) and passes [first_pass, first_pass +
 // npasses) of the single-graph path, each ended on the device by
 // k_pass_end, then (dense input) the output unpack, which writes only at
@@ -670,6 +683,12 @@ int kz_kernelize(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_t 
   r.status = KZ_EHIP;
   if (hipSetDevice(ctx->device) != hipSuccess) return finish(res, r);
   hipStream_t s = (hipStream_t)stream;
+  if (small_call(ctx, g, k, z, mfma)) {
+    kzi::launch_small(*g, colour, k, vmask, emask, (kzi::Hdr *)ws, (kz_out *)ctx->pinned_dev, s);
+    if (hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess)
+      r = ((const kz_out *)ctx->pinned)->result;
+    return finish(res, r);
+  }
   // The asynchronous passes in chunks, with one look at the device's result
   // per chunk: one pass at a time for the first kSinglePasses passes (most
   // runs end there, and a surplus pass still dispatches its grids), then

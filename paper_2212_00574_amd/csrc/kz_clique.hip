@@ -147,18 +147,6 @@ __global__ void __launch_bounds__(256) k_clique_setup(const int32_t *__restrict_
   }
 }
 
-// Wave prefix sum (inclusive) by lane shifts within rows of 16 and two row
-// broadcasts.
-__device__ __forceinline__ int wave_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
-  return x;
-}
-
 // The live mask in the rows' layout (bit j of word w of class c is vertex
 // coff[c] + 64 (w - soff[c]) + j), a wave per word, and the live neighbours in
 // class 1 of each live vertex of class 0, a wave per vertex (k = 1: 1 for a

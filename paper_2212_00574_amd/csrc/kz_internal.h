@@ -53,6 +53,18 @@ __device__ __forceinline__ int wave_sum(int v) {
          __builtin_amdgcn_readlane((int)x, 32) + __builtin_amdgcn_readlane((int)x, 48);
 }
 
+// Wave prefix sum (inclusive) by lane shifts within rows of 16 and two row
+// broadcasts.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+
 // Transposes a 64x64 bit matrix held one row per lane (lane l holds row l,
 // bit b = column b): returns row l of the transpose, i.e. bit b of the
 // result is bit l of lane b's input.  Six butterfly stages: at stage j,
@@ -116,6 +128,24 @@ struct Hdr {
   int done, pad2;
   kz_out out;  // the result so far
 };
+
+// Folds a pass's counts -- removed vertices and edges, edges tested -- into the
+// result so far (pass 1 tests every edge once: the input's edge count).
+__device__ __forceinline__ void fold_pass(kz_out &o, int pass, int n, long long rv, long long re, long long tests) {
+  if (pass == 1) {
+    o.result.input_edges = tests;
+    o.result.surviving_edges = tests;
+    o.result.surviving_vertices = n;
+  }
+  o.result.edge_tests += tests;
+  o.result.surviving_vertices -= rv;
+  o.result.surviving_edges -= re;
+  o.result.passes = pass;
+  o.last_removed = rv + re;
+  if (rv + re == 0) o.converged = 1;
+  else o.result.rounds += 1;
+  o.result.equals_input = o.result.rounds == 0;
+}
 
 // Device pointers of one kernelization (workspace carve-up + caller buffers).
 struct Plan {
@@ -212,6 +242,13 @@ void launch_csr_vertex(const Plan &p, const int64_t *rp, const int32_t *ci, cons
 void launch_csr_edge(const Plan &p, const int64_t *rp, const int32_t *ci, long long nnz, const int *colour,
                      const uint8_t *emask, int pass, bool first, hipStream_t s);
 void launch_csr_apply(const Plan &p, long long nnz, uint8_t *emask, hipStream_t s);
+
+// Small graphs, one workgroup a call (kz_small.hip): n <= kSmallN vertices, k <=
+// kSmallK classes, rows of R <= kSmallR words (the bound where R is known on
+// the device only) at an odd stride in kSmallWords.
+constexpr int kSmallN = 128, kSmallK = 64, kSmallR = 64, kSmallWords = 3520;
+void launch_small(const kz_graph &g, const int32_t *colour, int k, uint8_t *vmask, void *emask, Hdr *h, kz_out *host,
+                  hipStream_t s);
 
 // Batched path (kz_batch.hip).
 constexpr int kBatchK = 64;          // classes

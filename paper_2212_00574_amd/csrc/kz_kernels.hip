@@ -1290,20 +1290,7 @@ __global__ void __launch_bounds__(64) k_pass_end(Plan p, int pass, int csr, kz_o
     o.result.status = st;
     o.converged = 1;
   } else {
-    if (pass == 1) {
-      // pass 1 tests every edge once: the input's edge count
-      o.result.input_edges = (long long)c2;
-      o.result.surviving_edges = (long long)c2;
-      o.result.surviving_vertices = p.n;
-    }
-    o.result.edge_tests += (long long)c2;
-    o.result.surviving_vertices -= (long long)c0;
-    o.result.surviving_edges -= (long long)c1;
-    o.result.passes = pass;
-    o.last_removed = (long long)(c0 + c1);
-    if (c0 + c1 == 0) o.converged = 1;
-    else o.result.rounds += 1;
-    o.result.equals_input = o.result.rounds == 0;
+    fold_pass(o, pass, p.n, (long long)c0, (long long)c1, (long long)c2);
   }
   h->out = o;
   if (o.converged) h->done = 1;

@@ -1,0 +1,113 @@
+"""Blocking calls on graphs of up to 128 vertices (one workgroup a call) equal
+the general path -- which the timing of the kernels selects -- and the oracle:
+masks and every result field, dense and bit rows, sizes on both sides of the
+rule's limits, empty classes, one and two classes, many passes, and every input
+error."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from oracle import kernelize_bitset  # noqa: E402
+from paper_2212_00574_amd import inputs  # noqa: E402
+from paper_2212_00574_amd.binding import Kernelizer  # noqa: E402
+
+DEV = torch.device("cuda", 0)
+SIZES = [[1], [256], [1, 1], [1, 255], [2, 0, 3], [0, 0, 5], [1] * 50, [4] * 64, [2] * 40, [3, 64, 65], [64, 64, 128],
+         [63, 65, 64, 64], [20] * 5, [12] * 8, [25] * 10, [16] * 16, [85, 85, 86], [86, 85, 86], [37] * 4, [18] * 14,
+         [30] * 4, [128], [32] * 4, [43] * 3, [20] * 4, [27] * 3, [8] * 16, [5] * 16, [5] * 17, [4] * 20, [64, 64]]
+
+
+def both(f):
+    """f under the small path, then under the general one."""
+    kz = Kernelizer(0)
+    out = []
+    for general in (False, True):
+        kz.profile(general)
+        out.append(f(kz))
+    torch.cuda.synchronize()
+    return out
+
+
+def same(a, b, ctx):
+    assert a[2] == b[2], (ctx, a[2], b[2])
+    if a[2]["status"] == 0:
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]), ctx
+
+
+@pytest.mark.parametrize("i", range(len(SIZES)))
+def test_equals_general_path_and_oracle(i):
+    sizes = SIZES[i]
+    k, n = len(sizes), sum(sizes)
+    rng = np.random.default_rng(500 + i)
+    for j, p in enumerate((0.0, 0.15, 0.35, 0.6, 0.9, 1.0)):
+        g = inputs.make_graph(sizes, p, seed=41, gid=100 * i + j, plant=p < 0.5 and 0 not in sizes, shuffle=False)
+        rows, colour, lay = g.bitset()
+        ref = kernelize_bitset(rows, colour, k)
+        r, c = torch.from_numpy(rows.view(np.int64)).to(DEV), torch.from_numpy(colour).to(DEV)
+        small, general = both(lambda kz: kz.kernelize_bitset(r, c, k))
+        same(small, general, (sizes, p))
+        assert small[2]["rounds"] == ref["rounds"] and small[2]["edge_tests"] == ref["edge_tests"], (sizes, p)
+        assert np.array_equal(small[0].cpu().numpy(), ref["vmask"]), (sizes, p)
+        assert np.array_equal(small[1].cpu().numpy().view(np.uint64), ref["emask"]), (sizes, p)
+        # the same graph, dense, in another vertex order
+        perm = rng.permutation(n)
+        adj = inputs.unpack_rows(rows, lay).astype(np.uint8)[np.ix_(perm, perm)]
+        da, dc = torch.from_numpy(np.ascontiguousarray(adj)).to(DEV), torch.from_numpy(colour[perm].copy()).to(DEV)
+        dsmall, dgeneral = both(lambda kz: kz.kernelize_dense(da, dc, k))
+        same(dsmall, dgeneral, ("dense", sizes, p))
+        assert np.array_equal(dsmall[0].cpu().numpy().astype(np.uint8), ref["vmask"][perm]), (sizes, p)
+        keep = inputs.unpack_rows(ref["emask"], lay).astype(np.uint8)[np.ix_(perm, perm)]
+        assert np.array_equal(dsmall[1].cpu().numpy().astype(np.uint8), keep), (sizes, p)
+
+
+@pytest.mark.parametrize("sizes", [[9, 7, 20], [64, 65, 40], [30] * 8])
+def test_input_errors(sizes):
+    k = len(sizes)
+    g = inputs.make_graph(sizes, 0.5, seed=43, gid=0, plant=False, shuffle=False)
+    rows, colour, lay = g.bitset()
+    adj = inputs.unpack_rows(rows, lay).astype(np.uint8)
+    n = lay.n
+
+    def dense(edit, col=None):
+        a = adj.copy()
+        edit(a)
+        d, c = torch.from_numpy(a).to(DEV), torch.from_numpy(colour if col is None else col).to(DEV)
+        x, y = both(lambda kz: kz.kernelize_dense(d, c, k, check=False))
+        assert x[2] == y[2] and x[2]["status"] != 0, (x[2], y[2])
+        return x[2]["status"]
+
+    def bits(edit, col=None, R=lay.R):
+        b = np.zeros((n, R), np.uint64)
+        b[:, :min(R, lay.R)] = rows[:, :min(R, lay.R)]
+        edit(b)
+        d, c = torch.from_numpy(b.view(np.int64)).to(DEV), torch.from_numpy(colour if col is None else col).to(DEV)
+        x, y = both(lambda kz: kz.kernelize_bitset(d, c, k, check=False))
+        assert x[2] == y[2] and x[2]["status"] != 0, (x[2], y[2])
+        return x[2]["status"]
+
+    def put(a, u, v, x=1):
+        a[u, v] = x
+
+    def both_ways(a, u, v):
+        a[u, v] = a[v, u] = 1
+
+    one = np.uint64(1)
+    got = {dense(lambda a: put(a, 3, 3)), dense(lambda a: both_ways(a, 1, 2)), dense(lambda a: put(a, 1, 2)),
+           dense(lambda a: put(a, 0, n - 1, 1 - a[0, n - 1])), dense(lambda a: put(a, 0, n - 1, 2))}
+    bad = colour.copy()
+    bad[n // 2] = k
+    got.add(dense(lambda a: None, bad))
+    bad[n // 2] = -1
+    got.add(bits(lambda a: None, bad))
+    swapped = colour.copy()
+    swapped[[0, n - 1]] = swapped[[n - 1, 0]]
+    got |= {bits(lambda a: None, swapped), bits(lambda a: None, R=lay.R + 1), bits(lambda a: put(a, 2, 0, a[2, 0] | one << np.uint64(2))),
+            bits(lambda a: put(a, 0, 0, a[0, 0] | one << np.uint64(1)))}
+    if sizes[-1] % 64:
+        got.add(bits(lambda a: put(a, 0, lay.R - 1, a[0, lay.R - 1] | one << np.uint64(63))))
+    assert len(got) == 5, got  # invalid, colour, edge in a class, asymmetric, self-loop
