@@ -312,9 +312,8 @@ int enqueue_csr(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_t k
     }
     {
       ProfScope t(ctx, KZ_KERNEL_APPLY, s);
-      kzi::launch_csr_apply(p, nnz, emask, s);
+      kzi::launch_csr_apply(p, nnz, emask, pass, out, s);
     }
-    kzi::launch_pass_end(p, pass, true, out, s);
   }
   return hipGetLastError() == hipSuccess ? KZ_OK : KZ_EHIP;
 }
@@ -431,11 +430,12 @@ int enqueue_passes(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_
       if (mfma) kzi::launch_edge_pass_mfma(p, src, first ? cur : scratch, p.fb, pass, first, s);
       else kzi::launch_edge_pass(p, src, first ? cur : scratch, pass, first, s);
     }
-    if (!first) {
+    if (first) {
+      kzi::launch_pass_end(p, pass, out, s);
+    } else {
       ProfScope t(ctx, KZ_KERNEL_APPLY, s);
-      kzi::launch_apply(p, scratch, cur, s);
+      kzi::launch_apply(p, scratch, cur, pass, out, s);
     }
-    kzi::launch_pass_end(p, pass, false, out, s);
   }
   if (dense && unpack) {
     ProfScope t(ctx, KZ_KERNEL_UNPACK, s);

@@ -451,9 +451,13 @@ __global__ void __launch_bounds__(256) k_csr_edge(Plan p, const int64_t *rp, con
 
 // Removes the entries that failed this pass (after every test of the pass
 // has read the old masks).  Four entries per thread.
-__global__ void __launch_bounds__(256) k_csr_apply(Plan p, long long nnz, uint8_t *emask) {
+__global__ void __launch_bounds__(256) k_csr_apply(Plan p, long long nnz, uint8_t *emask, int pass, kz_out *out) {
   const Hdr *h = p.hdr;
-  if (csr_bad(h) || h->prio || h->done) return;
+  if (h->done) return;
+  // the other blocks may see the run done only when nothing fails, or on an
+  // input error
+  if (blockIdx.x == 0 && threadIdx.x < kWave) pass_end(p, pass, true, out);
+  if (csr_bad(h) || h->prio) return;
   const long long i0 = ((long long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -516,9 +520,8 @@ void launch_csr_edge(const Plan &p, const int64_t *rp, const int32_t *ci, long l
 #undef KZ_CSR_E
 }
 
-void launch_csr_apply(const Plan &p, long long nnz, uint8_t *emask, hipStream_t s) {
-  if (nnz <= 0) return;
-  hipLaunchKernelGGL(k_csr_apply, dim3(grid_of(nnz, 1024)), dim3(256), 0, s, p, nnz, emask);
+void launch_csr_apply(const Plan &p, long long nnz, uint8_t *emask, int pass, kz_out *out, hipStream_t s) {
+  hipLaunchKernelGGL(k_csr_apply, dim3(grid_of(nnz, 1024)), dim3(256), 0, s, p, nnz, emask, pass, out);
 }
 
 }  // namespace kzi

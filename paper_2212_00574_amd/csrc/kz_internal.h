@@ -183,6 +183,55 @@ struct Plan {
   int Sq;
 };
 
+// End of pass `pass` (one wave): the pass's counters, summed over their
+// slots, fold into the result; the run is done at the first pass that
+// removes nothing (the fixpoint of section 4.2's iterated pruning), or at
+// pass 1 when validation found an input error.  `out` gets the result too when
+// it is not null.
+__device__ __forceinline__ void pass_end(const Plan &p, int pass, bool csr, kz_out *out) {
+  Hdr *h = p.hdr;
+  if (h->done) return;
+  const int lane = threadIdx.x, par = pass & 1;
+  unsigned long long c0 = 0, c1 = 0, c2 = 0, c3 = 0;
+  if (lane < kCtrSlots) {
+    c0 = h->ctr(par, lane, 0);
+    c1 = h->ctr(par, lane, 1);
+    c2 = h->ctr(par, lane, 2);
+    c3 = h->ctr(1, lane, 3);  // CSR: entries above minus below the diagonal, with pass 1's counters
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    c0 += (unsigned long long)__shfl_xor((long long)c0, off, kWave);
+    c1 += (unsigned long long)__shfl_xor((long long)c1, off, kWave);
+    c2 += (unsigned long long)__shfl_xor((long long)c2, off, kWave);
+    c3 += (unsigned long long)__shfl_xor((long long)c3, off, kWave);
+  }
+  if (lane != 0) return;
+  kz_out o = h->out;
+  int st = KZ_OK;
+  if (pass == 1) {
+    int prio = h->prio;
+    if (csr && c3 != 0 && prio < P_EASYM) prio = P_EASYM;  // an entry without its reverse
+    st = h->bad_colour           ? KZ_ECOLOUR
+         : h->bad_layout         ? KZ_EINVAL
+         : prio == P_EINVAL      ? KZ_EINVAL
+         : prio == P_ESELFLOOP   ? KZ_ESELFLOOP
+         : prio == P_EASYM       ? KZ_EASYM
+         : prio == P_EILLEGAL    ? KZ_EILLEGAL
+                                 : KZ_OK;
+  }
+  if (st != KZ_OK) {
+    o = kz_out{};
+    o.result.status = st;
+    o.converged = 1;
+  } else {
+    fold_pass(o, pass, p.n, (long long)c0, (long long)c1, (long long)c2);
+  }
+  h->out = o;
+  if (o.converged) h->done = 1;
+  if (out) *out = o;
+}
+
 // Classes per chunk of the bit-row edge test (at most what a workgroup stages
 // at once), and the row stride of F that makes every chunk's load of a row in
 // bounds: a multiple of 4, so rows of F start on 32 bytes.
@@ -222,11 +271,10 @@ void launch_edge_pass(const Plan &p, const uint64_t *src, uint64_t *dst, int pas
 // `fb`, n*Rmax words), then the shared tile epilogue.
 void launch_edge_pass_mfma(const Plan &p, const uint64_t *src, uint64_t *dst, uint64_t *fb, int pass, bool first,
                            hipStream_t s);
-void launch_apply(const Plan &p, const uint64_t *scratch, uint64_t *cur, hipStream_t s);
-// Ends pass `pass` on the device (one wave): folds its counters into the
-// header's result, sets `done` at the fixpoint or on an input error, and
-// copies the result to `out` when it is not null.
-void launch_pass_end(const Plan &p, int pass, bool csr, kz_out *out, hipStream_t s);
+// The passes after the first: the changed tiles, and the pass's end.
+void launch_apply(const Plan &p, const uint64_t *scratch, uint64_t *cur, int pass, kz_out *out, hipStream_t s);
+// Ends pass `pass` on the device (pass_end) in a kernel of its own.
+void launch_pass_end(const Plan &p, int pass, kz_out *out, hipStream_t s);
 void launch_write_out(kz_out *out, const kz_out &v, hipStream_t s);
 void launch_unpack_dense(const Plan &p, const int *colour, const uint64_t *cur, uint8_t *vmask,
                          uint8_t *emask, hipStream_t s);
@@ -241,7 +289,7 @@ void launch_csr_vertex(const Plan &p, const int64_t *rp, const int32_t *ci, cons
                        const uint8_t *emask, int pass, hipStream_t s);
 void launch_csr_edge(const Plan &p, const int64_t *rp, const int32_t *ci, long long nnz, const int *colour,
                      const uint8_t *emask, int pass, bool first, hipStream_t s);
-void launch_csr_apply(const Plan &p, long long nnz, uint8_t *emask, hipStream_t s);
+void launch_csr_apply(const Plan &p, long long nnz, uint8_t *emask, int pass, kz_out *out, hipStream_t s);
 
 // Small graphs, one workgroup a call (kz_small.hip): n <= kSmallN vertices, k <=
 // kSmallK classes, rows of R <= kSmallR words (the bound where R is known on

@@ -1133,13 +1133,16 @@ __global__ void __launch_bounds__(kMfThreads) k_mfma_count(Plan p, const uint64_
   if (row < ul && (wc == 0 || y2)) fb[(long long)(xs + row) * R + Y + wc] = myword;
 }
 
-// Copies the changed tiles of this pass from scratch into the state.
+// Copies the changed tiles of this pass from scratch into the state, and ends
+// the pass (a launch less: 5003 vertices, a cascade, 574 -> 566 us): the
+// other blocks may see the run done only when nothing changed.
 __global__ void __launch_bounds__(128) k_apply(Plan p, const uint64_t *__restrict__ scratch,
-                                               uint64_t *__restrict__ cur) {
+                                               uint64_t *__restrict__ cur, int pass, kz_out *out) {
   const Hdr *h = p.hdr;
   if (stage1_bad(h) || h->done) return;
   const int R = h->R;
   const int cnt = h->tile_count;
+  if (blockIdx.x == 0 && threadIdx.x < kWave) pass_end(p, pass, false, out);
   for (int i = blockIdx.x; i < cnt; i += gridDim.x) {
     const int2 t = p.tiles[i];
     int j = threadIdx.x;
@@ -1249,67 +1252,22 @@ void launch_edge_pass_mfma(const Plan &p, const uint64_t *src, uint64_t *dst, ui
   }
 }
 
-// End of pass `pass` (one wave): the pass's counters, summed over their
-// slots, fold into the result; the run is done at the first pass that
-// removes nothing (the fixpoint of section 4.2's iterated pruning), or at
-// pass 1 when validation found an input error.
-__global__ void __launch_bounds__(64) k_pass_end(Plan p, int pass, int csr, kz_out *out) {
-  Hdr *h = p.hdr;
-  if (h->done) return;
-  const int lane = threadIdx.x, par = pass & 1;
-  unsigned long long c0 = 0, c1 = 0, c2 = 0, c3 = 0;
-  if (lane < kCtrSlots) {
-    c0 = h->ctr(par, lane, 0);
-    c1 = h->ctr(par, lane, 1);
-    c2 = h->ctr(par, lane, 2);
-    c3 = h->ctr(1, lane, 3);  // CSR: entries above minus below the diagonal, with pass 1's counters
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    c0 += (unsigned long long)__shfl_xor((long long)c0, off, kWave);
-    c1 += (unsigned long long)__shfl_xor((long long)c1, off, kWave);
-    c2 += (unsigned long long)__shfl_xor((long long)c2, off, kWave);
-    c3 += (unsigned long long)__shfl_xor((long long)c3, off, kWave);
-  }
-  if (lane != 0) return;
-  kz_out o = h->out;
-  int st = KZ_OK;
-  if (pass == 1) {
-    int prio = h->prio;
-    if (csr && c3 != 0 && prio < P_EASYM) prio = P_EASYM;  // an entry without its reverse
-    st = h->bad_colour           ? KZ_ECOLOUR
-         : h->bad_layout         ? KZ_EINVAL
-         : prio == P_EINVAL      ? KZ_EINVAL
-         : prio == P_ESELFLOOP   ? KZ_ESELFLOOP
-         : prio == P_EASYM       ? KZ_EASYM
-         : prio == P_EILLEGAL    ? KZ_EILLEGAL
-                                 : KZ_OK;
-  }
-  if (st != KZ_OK) {
-    o = kz_out{};
-    o.result.status = st;
-    o.converged = 1;
-  } else {
-    fold_pass(o, pass, p.n, (long long)c0, (long long)c1, (long long)c2);
-  }
-  h->out = o;
-  if (o.converged) h->done = 1;
-  if (out) *out = o;
-}
+// A pass's end where no other kernel does it (pass 1, and rows of one word).
+__global__ void __launch_bounds__(64) k_pass_end(Plan p, int pass, kz_out *out) { pass_end(p, pass, false, out); }
 
 __global__ void k_write_out(kz_out *out, kz_out v) { *out = v; }
 
-void launch_pass_end(const Plan &p, int pass, bool csr, kz_out *out, hipStream_t s) {
-  hipLaunchKernelGGL(k_pass_end, dim3(1), dim3(64), 0, s, p, pass, csr ? 1 : 0, out);
+void launch_pass_end(const Plan &p, int pass, kz_out *out, hipStream_t s) {
+  hipLaunchKernelGGL(k_pass_end, dim3(1), dim3(64), 0, s, p, pass, out);
 }
 
 void launch_write_out(kz_out *out, const kz_out &v, hipStream_t s) {
   hipLaunchKernelGGL(k_write_out, dim3(1), dim3(1), 0, s, out, v);
 }
 
-void launch_apply(const Plan &p, const uint64_t *scratch, uint64_t *cur, hipStream_t s) {
-  if (p.Tmax <= 0) return;
-  hipLaunchKernelGGL(k_apply, dim3(grid_for(p.Tmax, 1, 4096)), dim3(128), 0, s, p, scratch, cur);
+void launch_apply(const Plan &p, const uint64_t *scratch, uint64_t *cur, int pass, kz_out *out, hipStream_t s) {
+  if (p.Tmax <= 0) launch_pass_end(p, pass, out, s);
+  else hipLaunchKernelGGL(k_apply, dim3(grid_for(p.Tmax, 1, 4096)), dim3(128), 0, s, p, scratch, cur, pass, out);
 }
 
 void launch_unpack_dense(const Plan &p, const int *colour, const uint64_t *cur, uint8_t *vmask,
