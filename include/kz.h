@@ -260,12 +260,14 @@ typedef struct kz_batch_graph {
 
 typedef struct kz_batch_config {
   int32_t waves;       /* waves per workgroup: 4, 8 or 16                 */
-  int32_t chunk;       /* third classes staged per step: 4 or 8 (4 when
-                          waves is 16)                                     */
+  int32_t chunk;       /* 4 or 8 (4 when waves is 16): kept for saved
+                          configurations, no effect                        */
   int32_t lpt;         /* 1: largest graphs first; 0: given order         */
   int32_t workgroups;  /* persistent workgroups (0 = fill the device)     */
   int32_t share;       /* 0: a pass with more items than the workgroup has
-                          waves is shared once the queue is empty;
+                          waves is shared once the queue is empty,
+                          earlier when it is very large or its graph has
+                          run long;
                           1: every pass is shared (tests the cross-
                           workgroup path); 2: never (one workgroup per
                           graph)                                           */

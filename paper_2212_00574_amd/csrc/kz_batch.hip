@@ -60,8 +60,16 @@ constexpr unsigned long long kHostPoll = 200;        // 2 us: session mode's loo
 // Claim word: pass (24 bits) | items (20 bits) | next unclaimed item (20 bits).
 constexpr int kItemBits = 20;
 constexpr unsigned kItemMask = (1u << kItemBits) - 1;
-// A pass is shared once the queue is empty, or early when it is very large.
+// A pass is shared once the queue is empty, or earlier when it is very large or
+// its job has run long.
 constexpr int kShareBig = 2048;   // items
+// A job that has run so many passes times the items of this one is shared
+// though graphs wait: run by one workgroup a long cascade (74 passes on 1122
+// vertices, 27 ms) outlasts all the other graphs' work (about 11 ms), shared it
+// takes a third.  Seven batches of 4096 graphs, mean of a batch: 17.9 ms never,
+// 17.4 from 7000 on, 15.6 from 5500, 15.1 from 4096, 15.5 from 3072 (a shared
+// pass costs the others' time), 17.4 from 1536.
+constexpr int kShareWork = 4096;
 
 __device__ __forceinline__ unsigned long long bcast64(unsigned long long x, int lane) {
   const unsigned lo = __builtin_amdgcn_readlane((unsigned)x, lane);
@@ -735,7 +743,7 @@ __device__ bool open_pass(const BatchArgs &a, const GView &V, BatchLds &S) {
   if (tid == 0) {
     bool shared = a.share == 1;
     if (a.share == 0 && ni > NW)
-      shared = ni >= kShareBig ||
+      shared = ni >= kShareBig || (p - S.pass0) * ni >= kShareWork ||
                (a.session ? ald(a.squeue) >= ald(a.dhead) : ald(a.queue) >= a.G);
     S.shared = shared;
     S.base = 0;
