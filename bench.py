@@ -118,10 +118,10 @@ def say(*a):
 # The kernel whose launches set each workload's roofline, and the sources it
 # is built from (a committed counter summary is used only while they match).
 PROFILED = {
-    "c1": ("k_edge", ("kz_kernels.hip", "kz_internal.h")),
-    "c3a": ("k_edge", ("kz_kernels.hip", "kz_internal.h")),
+    "c1": ("k_edge", ("kz_kernels.hip", "kz_mx.h", "kz_internal.h")),
+    "c3a": ("k_edge", ("kz_kernels.hip", "kz_mx.h", "kz_internal.h")),
     "c3b": ("k_csr_edge", ("kz_csr.hip", "kz_internal.h")),
-    "c4": ("k_batch", ("kz_batch.hip", "kz_internal.h")),
+    "c4": ("k_batch", ("kz_batch.hip", "kz_mx.h", "kz_internal.h")),
 }
 
 
