@@ -80,8 +80,8 @@ typedef enum {
                          row_ptr[n] = nnz; vertices in any order.  k must
                          not exceed 1024 (host check, KZ_EINVAL).  Suited to
                          sparse graphs: the edge test first compares the
-                         endpoints' sets of neighbour classes, then merges
-                         the two rows.                                        */
+                         endpoints' sets of neighbour classes, then looks
+                         the entries of one row up in the other.              */
 } kz_format;
 
 typedef struct kz_graph {
@@ -183,7 +183,8 @@ int kz_kernelize(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_t 
  * (dense input: they are written only then).  Returns KZ_OK once enqueued,
  * or a host-detectable error (KZ_EINVAL also for first_pass < 1 or
  * npasses < 1) with nothing enqueued.  kz_kernelize is this call in chunks
- * of passes, with one look at the result between chunks. */
+ * of passes, with one look at the result between chunks (a graph of at most
+ * 128 vertices -- bit rows 80 -- runs in one workgroup instead). */
 int kz_kernelize_async(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_t k,
                        void *ws, size_t ws_bytes, uint8_t *vmask, void *emask,
                        int32_t first_pass, int32_t npasses, void *stream, kz_out *out);
@@ -206,8 +207,10 @@ int kz_kernelize_noalloc(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, 
 
 /* Edge-test implementation used by kz_kernelize for KZ_DENSE_U8 and
  * KZ_BITSET_U64 input (CSR always uses its own):
- *   KZ_EDGE_BITSET  (default) witness search on the bit rows: per third
- *                   class, the first common neighbour ends the search;
+ *   KZ_EDGE_BITSET  (default) witness search on the bit rows: the classes'
+ *                   first words as 4-bit matrix products where that pays,
+ *                   then per third class left the first common neighbour
+ *                   ends the search;
  *   KZ_EDGE_MFMA_I8 per-class common-neighbour counts of every pair of a
  *                   tile as int8 x int8 -> int32 MFMA block contractions
  *                   (exact), an edge failing where some third class counts
@@ -504,8 +507,8 @@ int kz_gen_bitset(kz_ctx *ctx, int32_t k, const int32_t *sizes, double p, uint32
  *   ws, ws_bytes: device workspace of kz_colour_workspace_bytes() bytes,
  *         256-byte aligned;
  *   colour: device int32[n] out, in [0, colours).
- * Blocking: rounds end on the device and go out in chunks, with one small
- * readback per chunk. */
+ * Blocking: a small readback after validation and one at the end (sparse
+ * graphs, of average degree below n / 100: one per chunk of rounds). */
 typedef struct kz_colour_result {
   int32_t status;
   int32_t rounds;
@@ -544,8 +547,8 @@ int kz_colour_jp(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
  *   emask: device uint64[n * row_words], the adjacency left, same layout
  *         (may be the rows buffer itself);
  *   res: host struct receiving the counts.
- * Blocking: the sweep is a chain of parallel scans, each followed by one
- * small readback; returns after the fixpoint.  Outputs are unspecified
+ * Blocking: one launch runs the sweeps, with one small readback; returns
+ * after the fixpoint.  Outputs are unspecified
  * when the status is not KZ_OK. */
 #define KZ_DOM_VERTEX 0
 #define KZ_DOM_EDGE 1
