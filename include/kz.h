@@ -164,8 +164,8 @@ int kz_kernelize(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_t 
 
 /* The asynchronous form of kz_kernelize (section 4.2's pruning, repeated to
  * the fixpoint): enqueues passes first_pass .. first_pass + npasses - 1 on
- * `stream` and returns without waiting.  Every pass ends with a one-wave
- * kernel that folds the pass's removals into the result and, at the first
+ * `stream` and returns without waiting.  Every pass's end on the device
+ * folds the pass's removals into the result and, at the first
  * pass that removes nothing (or at pass 1 on an input error), marks the run
  * converged; the kernels of later passes of the run then return at once.
  * There is no host synchronisation inside, so the call can be captured in a

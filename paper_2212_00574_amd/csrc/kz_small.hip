@@ -26,6 +26,15 @@ constexpr int kSmallList = 128;  // edges a wave lists at a time
 // A value from LDS that is the same in every lane.
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
+// The result, and a header that stops the general path's kernels: they find
+// nothing else of theirs in the workspace.
+__device__ __forceinline__ void end_call(Hdr *h, const kz_out &o, kz_out *host) {
+  h->out = o;
+  h->bad_layout = 1;
+  h->done = 1;
+  *host = o;
+}
+
 template <bool DENSE>
 __global__ void __launch_bounds__(kSmallThreads) k_small(const uint8_t *__restrict__ adj,
                                                          const uint64_t *__restrict__ rows, int row_words,
@@ -93,9 +102,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const uint8_t *__restri
     if (t == 0) {
       o.result.status = bad_colour ? KZ_ECOLOUR : KZ_EINVAL;
       o.converged = 1;
-      h->out = o;
-      h->done = 1;
-      *host = o;
+      end_call(h, o, host);
     }
     return;
   }
@@ -194,9 +201,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const uint8_t *__restri
                         : prio == P_EASYM     ? KZ_EASYM
                                               : KZ_EILLEGAL;
       o.converged = 1;
-      h->out = o;
-      h->done = 1;
-      *host = o;
+      end_call(h, o, host);
     }
     return;
   }
@@ -359,11 +364,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const uint8_t *__restri
     }
     if (t < n) vmask[t] = alive[t];
   }
-  if (t == 0) {
-    h->out = o;
-    h->done = 1;
-    *host = o;
-  }
+  if (t == 0) end_call(h, o, host);
 }
 
 }  // namespace

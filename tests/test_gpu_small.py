@@ -14,7 +14,7 @@ if not torch.cuda.is_available():
 
 from oracle import kernelize_bitset  # noqa: E402
 from paper_2212_00574_amd import inputs  # noqa: E402
-from paper_2212_00574_amd.binding import Kernelizer  # noqa: E402
+from paper_2212_00574_amd.binding import Kernelizer, graph_dense, kz_kernelize  # noqa: E402
 
 DEV = torch.device("cuda", 0)
 SIZES = [[1], [256], [1, 1], [1, 255], [2, 0, 3], [0, 0, 5], [1] * 50, [4] * 64, [2] * 40, [3, 64, 65], [64, 64, 128],
@@ -111,3 +111,22 @@ def test_input_errors(sizes):
     if sizes[-1] % 64:
         got.add(bits(lambda a: put(a, 0, lay.R - 1, a[0, lay.R - 1] | one << np.uint64(63))))
     assert len(got) == 5, got  # invalid, colour, edge in a class, asymmetric, self-loop
+
+
+def test_passes_after_a_small_call_do_nothing():
+    """A small call leaves a workspace in which a continued run finds nothing to do."""
+    g = inputs.make_graph([25] * 4, 0.5, seed=44, gid=0, plant=False, shuffle=False)
+    adj, colour = g.dense()
+    kz = Kernelizer(0)
+    d, c = torch.from_numpy(adj).to(DEV), torch.from_numpy(colour).to(DEV)
+    v = torch.full((100,), 9, dtype=torch.uint8, device=DEV)
+    e = torch.full((100, 100), 9, dtype=torch.uint8, device=DEV)
+    graph = graph_dense(d)
+    ws = kz.workspace(graph, 4)
+    res = kz_kernelize(kz.ctx, graph, c.data_ptr(), 4, ws.data_ptr(), ws.numel(), v.data_ptr(), e.data_ptr(),
+                       torch.cuda.current_stream().cuda_stream)
+    assert res.status == 0
+    v0, e0 = v.clone(), e.clone()
+    kz.run_async(graph, c, 4, v, e, None, first_pass=res.passes + 1, npasses=2, ws=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(v, v0) and torch.equal(e, e0)
