@@ -305,6 +305,13 @@ struct TileRows {
   unsigned long long u[kBlk][kTileWords], v[kBlk][kTileWords];
 };
 
+// A tile's words and pairs to test while the product needs all registers: in
+// scratch memory they were 9 GB of writes a launch of 4096 graphs (six batches:
+// 15.0 ms, 14.5 with this).  With 4 waves a workgroup there is no LDS for it.
+struct Kept {
+  unsigned long long eu[kBlk], et[kBlk], pt[kBlk];
+};
+
 // 16 sums, element e's "zero" to bit e.
 __device__ __forceinline__ unsigned zeros16(const mx_v16f &acc) {
   unsigned z = 0;
@@ -366,9 +373,11 @@ __device__ __forceinline__ int stage_tile(const GView &V, TileRows &W, int xs, i
 
 // Lane u: the pairs (bits v) of `want` with at most `slack` third classes
 // without a witness, as matrix products.  t: first word of the window staged.
+// With `kept` (a constant at each call) the pairs come from there.
 template <bool SLACK>
 __device__ __forceinline__ unsigned long long tile_product(const GView &V, const BatchLds &S, int X, int Y, int lane,
-                                                           unsigned long long want, TileRows &W, int t) {
+                                                           unsigned long long want, const Kept *kept, TileRows &W,
+                                                           int t) {
   const int cx = uni(S.bcls[X]), cy = uni(S.bcls[Y]);
   const int xs = uni(S.bstart[X]), ys = uni(S.bstart[Y]);
   const bool two_u = uni(S.blen[X]) > 32, two_v = uni(S.blen[Y]) > 32;
@@ -445,7 +454,7 @@ __device__ __forceinline__ unsigned long long tile_product(const GView &V, const
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       if (j == 1 && !two_u) break;
-      const unsigned wb = want_bits(want, j, lane);
+      const unsigned wb = want_bits(kept ? kept->pt[lane] : want, j, lane);
       if (w0 < t || w0 >= t + kTileWords) t = stage_tile(V, W, xs, ys, w0, lane);
       mx_v16f a0, a1;
       {
@@ -547,7 +556,9 @@ __device__ __forceinline__ unsigned long long tile_pairs(const GView &V, const B
   return ok[lane];
 }
 
-__device__ __forceinline__ void tile(const GView &V, BatchLds &S, int X, int Y, bool first, int lane, TileRows &W) {
+template <bool KEEP>
+__device__ __forceinline__ void tile(const GView &V, BatchLds &S, int X, int Y, bool first, int lane, TileRows &W,
+                                     Kept *kept) {
   const int R = V.R;
   const uint64_t *src = V.cur;
   const int xs = uni(S.bstart[X]), xl = uni(S.blen[X]), ys = uni(S.bstart[Y]), yl = uni(S.blen[Y]);
@@ -558,18 +569,32 @@ __device__ __forceinline__ void tile(const GView &V, BatchLds &S, int X, int Y, 
   // the first window, in flight with the loads above (the pairs path's list
   // takes its place and stages again)
   stage_tile(V, W, xs, ys, 0, lane);
-  const unsigned long long Eu = lane < xl ? eu & ymask : 0ull;  // the edges of row u = lane
-  const unsigned long long ET = lane < yl ? ev : 0ull;          // and of row v = lane
+  unsigned long long Eu = lane < xl ? eu & ymask : 0ull;  // the edges of row u = lane
+  unsigned long long ET = lane < yl ? ev : 0ull;          // and of row v = lane
   const unsigned long long TU = first ? ~0ull : __ballot(lane < xl && tbit(S.tc, xs + lane));
   const unsigned long long TV = first ? ~0ull : __ballot(lane < yl && tbit(S.tc, ys + lane));
   const unsigned long long Pt = Eu & (((TU >> lane) & 1ull) ? ~0ull : TV);
   unsigned long long Pu = Eu;
   const int cnt = wave_sum(__popcll(Pt));
   if (V.k - 2 > V.slack && cnt > 0) {
+    if constexpr (KEEP) {
+      kept->eu[lane] = Eu;
+      kept->et[lane] = ET;
+      kept->pt[lane] = Pt;
+      asm volatile("" ::: "memory");  // read back, not kept
+    }
+    Kept *k = KEEP ? kept : nullptr;
     const unsigned long long ok = cnt <= kTilePairs ? tile_pairs(V, S, X, Y, lane, Pt, W)
-                                  : V.slack > 0    ? tile_product<true>(V, S, X, Y, lane, Pt, W, 0)
-                                                   : tile_product<false>(V, S, X, Y, lane, Pt, W, 0);
-    Pu &= ~(Pt & ~ok);
+                                  : V.slack > 0    ? tile_product<true>(V, S, X, Y, lane, Pt, k, W, 0)
+                                                   : tile_product<false>(V, S, X, Y, lane, Pt, k, W, 0);
+    if constexpr (KEEP) {
+      asm volatile("" ::: "memory");
+      Eu = kept->eu[lane];
+      ET = kept->et[lane];
+      Pu = Eu & ~(kept->pt[lane] & ~ok);
+    } else {
+      Pu &= ~(Pt & ~ok);
+    }
   }
   // transposes: lane v gets bit v of every P(u) (rows u >= xl hold zero) and,
   // in pass 1, of every E(u), to check that the rows are symmetric
@@ -607,6 +632,14 @@ template <int NW>
 __device__ __forceinline__ TileRows &lds_rows(int wid) {
   __shared__ TileRows W[NW];
   return W[wid];
+}
+template <int NW>
+__device__ __forceinline__ Kept *lds_kept(int wid) {
+  if constexpr (NW > 4) {
+    __shared__ Kept K[NW];
+    return K + wid;
+  }
+  return nullptr;
 }
 
 // The waves of the workgroup take the items of the claimed run one by one.
@@ -647,7 +680,7 @@ __device__ __attribute__((noinline)) void run_items() {
 #pragma unroll 1
       for (int h = 0; h < kVChunk; h += kWave) vertex_chunk(V, S, v0 + h, first, lane);
     } else {
-      tile(V, S, it & kXMask, (it >> kYShift) & kXMask, first, lane, W);
+      tile<(NW > 4)>(V, S, it & kXMask, (it >> kYShift) & kXMask, first, lane, W, lds_kept<NW>(wid));
     }
   }
   __syncthreads();
