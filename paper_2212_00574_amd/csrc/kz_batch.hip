@@ -293,7 +293,8 @@ __device__ __forceinline__ void vertex_chunk(const GView &V, BatchLds &S, int v0
 // bit planes.  Tiles with few pairs to test (later passes: a third of the
 // tiles of 4096 graphs of 4..16 classes of 8..128 vertices have up to 128)
 // take them one per lane.  On those graphs a launch took 28.1 ms with a
-// ballot per row and class, and takes 17.7 ms (15.1 ms with the order below):
+// ballot per row and class, and takes 17.7 ms (12.1 ms with the order below, long
+// cascades shared, and the tile's words kept in LDS):
 // 16 waves keep the vector ALUs busy, about 2000 instructions a tile, 64 of
 // them per class for the minima.  With clique sizes two below the classes
 // (512 graphs) 44.3 and 9.6 ms.
@@ -306,8 +307,8 @@ struct TileRows {
 };
 
 // A tile's words and pairs to test while the product needs all registers: in
-// scratch memory they were 9 GB of writes a launch of 4096 graphs (six batches:
-// 15.0 ms, 14.5 with this).  With 4 waves a workgroup there is no LDS for it.
+// scratch memory they were 2.4 GB of writes a launch of 4096 graphs (six
+// batches: 15.0 ms, 14.5 with this).  With 4 waves a workgroup there is no LDS for it.
 struct Kept {
   unsigned long long eu[kBlk], et[kBlk], pt[kBlk];
 };
