@@ -181,6 +181,9 @@ __global__ void __launch_bounds__(256) k_clique_alive(const uint64_t *__restrict
       if (lane == 0) pre[v] = cnt;
     }
   }
+  // every wave's stores have landed before the one release below: the barrier
+  // does not wait for them, and the release waits for its own wave's only
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();  // by one thread: a release writes the whole L2 back
