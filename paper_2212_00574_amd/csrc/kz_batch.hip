@@ -1130,7 +1130,7 @@ __device__ bool carry(const BatchArgs &a, const GView &V, BatchLds &S) {
   if (tid == 0) {
     const long long rv = (long long)S.removed_v, re = (long long)S.removed_e;
     S.status = 0;
-    if (p == 1 && S.prio)
+    if (p == S.pass0 && S.prio)
       S.status = S.prio == P_EINVAL      ? KZ_EINVAL
                  : S.prio == P_ESELFLOOP ? KZ_ESELFLOOP
                  : S.prio == P_EASYM     ? KZ_EASYM
