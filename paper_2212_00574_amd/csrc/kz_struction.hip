@@ -29,6 +29,10 @@ struct StHdr {
 };
 
 constexpr int kStWaves = 4;  // waves (rows) per workgroup
+// Workgroups of G's rows at most (the waves go round): a launch of 2^32 threads is
+// refused, which the caller's room for nodes alone may ask for, and a workgroup
+// without a row takes its slot all the same.
+constexpr int kStBlocks = 1 << 16;
 
 __device__ __forceinline__ bool bit(const uint64_t *row, int v) { return (row[v >> 6] >> (v & 63)) & 1ull; }
 
@@ -315,9 +319,10 @@ int kz_struction(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
   hipLaunchKernelGGL(k_st_scan, dim3(1), dim3(1024), 0, s, row, rows + (long long)pivot * R, n, R,
                      build ? out_nodes : -1, out_row_words, coff, h, (StHdr *)ctx->pinned_dev);
   if (build) {
-    // a wave per node the output can hold, and no more than G' can have
+    // a wave per node the output can hold, and no more than G' can have nor
+    // than kStBlocks give
     const long long most = std::min<long long>(out_nodes, (long long)n * n / 2 + n) + out_row_words;
-    const unsigned blocks = (unsigned)std::min<long long>((most + kStWaves - 1) / kStWaves, 1 << 24);
+    const unsigned blocks = (unsigned)std::min<long long>((most + kStWaves - 1) / kStWaves, kStBlocks);
     hipLaunchKernelGGL(k_st_map, grid, block, 0, s, rows, n, R, pivot, alist, coff, h, map, M);
     hipLaunchKernelGGL(k_st_rows, dim3(blocks), block, 0, s, rows, R, M,
                        map, coff, h, out_row_words, out);
