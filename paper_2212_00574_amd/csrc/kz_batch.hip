@@ -337,6 +337,12 @@ __device__ __forceinline__ unsigned want_bits(unsigned long long want, int j, in
   return out;
 }
 
+// Orders the wave's reads and writes of LDS before it with those after it.
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Words t .. t + nw - 1 of the rows of the block that starts at slot s0, into
 // LDS: eight lanes a row, eight rows a load.  Rows past the block's end (not
 // past the graph's) are the next block's; no pair to test is in them.
@@ -365,10 +371,10 @@ __device__ __forceinline__ void stage_rows(const GView &V, unsigned long long (*
 // Stages a window of both blocks' rows from word w on and returns its start.
 __device__ __forceinline__ int stage_tile(const GView &V, TileRows &W, int xs, int ys, int w, int lane) {
   const int nw = min(kTileWords, V.R - w);
-  __builtin_amdgcn_wave_barrier();  // the previous window is read
+  wave_order();  // the previous window is read
   stage_rows(V, W.u, xs, w, nw, lane);
   stage_rows(V, W.v, ys, w, nw, lane);
-  __builtin_amdgcn_wave_barrier();
+  wave_order();
   return w;
 }
 
@@ -511,8 +517,11 @@ __device__ __forceinline__ unsigned long long tile_pairs(const GView &V, const B
                                                          unsigned long long want, TileRows &W) {
   const int cx = uni(S.bcls[X]), cy = uni(S.bcls[Y]);
   const int xs = uni(S.bstart[X]), ys = uni(S.bstart[Y]);
-  // the pairs listed in the rows' place, then two in registers
-  unsigned short *list = (unsigned short *)W.u;
+  // the pairs listed in the rows' place, then two in registers.  The list's type
+  // may alias the words', and fences keep its reads and writes between theirs: a
+  // wave barrier alone orders no memory.
+  typedef unsigned short __attribute__((may_alias)) Pair;
+  Pair *list = (Pair *)W.u;
   const int cnt = __popcll(want);
   int at = cnt;
 #pragma unroll
@@ -522,11 +531,12 @@ __device__ __forceinline__ unsigned long long tile_pairs(const GView &V, const B
   }
   const int total = __builtin_amdgcn_readlane(at, kWave - 1);
   at -= cnt;
-  __builtin_amdgcn_wave_barrier();
-  for (unsigned long long x = want; x; x &= x - 1) list[at++] = (unsigned short)(lane << 6 | __builtin_ctzll(x));
-  __builtin_amdgcn_wave_barrier();
+  wave_order();
+  for (unsigned long long x = want; x; x &= x - 1) list[at++] = (Pair)(lane << 6 | __builtin_ctzll(x));
+  wave_order();
   const bool have0 = lane < total, have1 = lane + kWave < total;
   const int p0 = have0 ? list[lane] : 0, p1 = have1 ? list[lane + kWave] : 0;
+  wave_order();
   const bool more = total > kWave;
   const unsigned long long *u0 = W.u[p0 >> 6], *v0 = W.v[p0 & 63], *u1 = W.u[p1 >> 6], *v1 = W.v[p1 & 63];
   int t = -kTileWords, miss0 = 0, miss1 = 0, seen = 0;
@@ -548,12 +558,12 @@ __device__ __forceinline__ unsigned long long tile_pairs(const GView &V, const B
   }
   const int room = V.slack - (V.k - 2 - seen);  // less the third classes without a vertex
   unsigned long long *ok = W.u[0];
-  __builtin_amdgcn_wave_barrier();
+  wave_order();
   ok[lane] = ~0ull;
-  __builtin_amdgcn_wave_barrier();
+  wave_order();
   if (have0 && miss0 > room) atomicAnd(&ok[p0 >> 6], ~(1ull << (p0 & 63)));
   if (have1 && miss1 > room) atomicAnd(&ok[p1 >> 6], ~(1ull << (p1 & 63)));
-  __builtin_amdgcn_wave_barrier();
+  wave_order();
   return ok[lane];
 }
 
