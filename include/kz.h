@@ -262,7 +262,8 @@ typedef struct kz_batch_graph {
 } kz_batch_graph;
 
 typedef struct kz_batch_config {
-  int32_t waves;       /* waves per workgroup: 4, 8 or 16                 */
+  int32_t waves;       /* 4, 8 or 16: kept for saved configurations, no
+                          effect (a workgroup has 16 waves)                */
   int32_t chunk;       /* 4 or 8 (4 when waves is 16): kept for saved
                           configurations, no effect                        */
   int32_t lpt;         /* 1: largest graphs first; 0: given order         */

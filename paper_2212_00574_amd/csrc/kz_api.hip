@@ -218,7 +218,7 @@ BatchWs batch_ws(const kz_batch_graph *graphs, int32_t G) {
 // Persistent workgroups: as many as fit on the device at once (also for
 // small batches: workgroups without a graph help with the running ones).
 int batch_workgroups(const kz_ctx *ctx, const kzi::BatchConfig &cfg) {
-  int wg = cfg.workgroups > 0 ? cfg.workgroups : ctx->cus * (16 / cfg.waves);
+  int wg = cfg.workgroups > 0 ? cfg.workgroups : ctx->cus;  // a workgroup's waves fill a compute unit
   if (wg > kBatchMaxWorkgroups) wg = kBatchMaxWorkgroups;
   return wg < 1 ? 1 : wg;
 }
@@ -539,8 +539,7 @@ int kz_batch_autotune(kz_ctx *ctx, const kz_batch_graph *graphs_host, const kz_b
                       kz_batch_config *best) {
   if (!ctx || !best) return KZ_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  static const kzi::BatchConfig cands[] = {{4, 4, 1, 0, 0}, {4, 8, 1, 0, 0}, {8, 4, 1, 0, 0},
-                                           {8, 8, 1, 0, 0}, {16, 4, 1, 0, 0}, {8, 4, 0, 0, 0}};
+  static const kzi::BatchConfig cands[] = {{16, 4, 1, 0, 0}, {16, 4, 0, 0, 0}};
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return KZ_EHIP;
   int st = KZ_OK;

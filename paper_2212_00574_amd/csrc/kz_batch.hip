@@ -52,6 +52,11 @@ namespace kzi {
 
 namespace {
 
+// Waves of a workgroup: all that a compute unit's registers hold.  Two workgroups
+// of 8 or four of 4 keep as many in flight, but a cascade then has fewer of them
+// to itself and sharing a pass costs more: 4096 graphs 12.2 ms, 27.9 and 82.4; 64
+// graphs 2.3, 5.8 and 17.8.
+constexpr int NW = kBatchWaves;
 constexpr int kVertexItem = 1 << 30;                 // item = kVertexItem | chunk, else X | Y << kYShift
 constexpr int kVChunk = 128;                         // vertices of a vertex item: one line of the vertex mask
 constexpr int kYShift = 9, kXMask = (1 << kYShift) - 1;
@@ -308,7 +313,7 @@ struct TileRows {
 
 // A tile's words and pairs to test while the product needs all registers: in
 // scratch memory they were 2.4 GB of writes a launch of 4096 graphs (six
-// batches: 15.0 ms, 14.5 with this).  With 4 waves a workgroup there is no LDS for it.
+// batches: 15.0 ms, 14.5 with this).
 struct Kept {
   unsigned long long eu[kBlk], et[kBlk], pt[kBlk];
 };
@@ -378,13 +383,12 @@ __device__ __forceinline__ int stage_tile(const GView &V, TileRows &W, int xs, i
   return w;
 }
 
-// Lane u: the pairs (bits v) of `want` with at most `slack` third classes
-// without a witness, as matrix products.  t: first word of the window staged.
-// With `kept` (a constant at each call) the pairs come from there.
+// Lane u: the pairs (bits v) with at most `slack` third classes without a
+// witness, as matrix products; the pairs to test are in `kept`.  t: first word of
+// the window staged.
 template <bool SLACK>
 __device__ __forceinline__ unsigned long long tile_product(const GView &V, const BatchLds &S, int X, int Y, int lane,
-                                                           unsigned long long want, const Kept *kept, TileRows &W,
-                                                           int t) {
+                                                           const Kept &kept, TileRows &W, int t) {
   const int cx = uni(S.bcls[X]), cy = uni(S.bcls[Y]);
   const int xs = uni(S.bstart[X]), ys = uni(S.bstart[Y]);
   const bool two_u = uni(S.blen[X]) > 32, two_v = uni(S.blen[Y]) > 32;
@@ -461,7 +465,7 @@ __device__ __forceinline__ unsigned long long tile_product(const GView &V, const
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       if (j == 1 && !two_u) break;
-      const unsigned wb = want_bits(kept ? kept->pt[lane] : want, j, lane);
+      const unsigned wb = want_bits(kept.pt[lane], j, lane);
       if (w0 < t || w0 >= t + kTileWords) t = stage_tile(V, W, xs, ys, w0, lane);
       mx_v16f a0, a1;
       {
@@ -567,9 +571,8 @@ __device__ __forceinline__ unsigned long long tile_pairs(const GView &V, const B
   return ok[lane];
 }
 
-template <bool KEEP>
 __device__ __forceinline__ void tile(const GView &V, BatchLds &S, int X, int Y, bool first, int lane, TileRows &W,
-                                     Kept *kept) {
+                                     Kept &kept) {
   const int R = V.R;
   const uint64_t *src = V.cur;
   const int xs = uni(S.bstart[X]), xl = uni(S.blen[X]), ys = uni(S.bstart[Y]), yl = uni(S.blen[Y]);
@@ -588,24 +591,17 @@ __device__ __forceinline__ void tile(const GView &V, BatchLds &S, int X, int Y, 
   unsigned long long Pu = Eu;
   const int cnt = wave_sum(__popcll(Pt));
   if (V.k - 2 > V.slack && cnt > 0) {
-    if constexpr (KEEP) {
-      kept->eu[lane] = Eu;
-      kept->et[lane] = ET;
-      kept->pt[lane] = Pt;
-      asm volatile("" ::: "memory");  // read back, not kept
-    }
-    Kept *k = KEEP ? kept : nullptr;
+    kept.eu[lane] = Eu;
+    kept.et[lane] = ET;
+    kept.pt[lane] = Pt;
+    asm volatile("" ::: "memory");  // read back, not kept
     const unsigned long long ok = cnt <= kTilePairs ? tile_pairs(V, S, X, Y, lane, Pt, W)
-                                  : V.slack > 0    ? tile_product<true>(V, S, X, Y, lane, Pt, k, W, 0)
-                                                   : tile_product<false>(V, S, X, Y, lane, Pt, k, W, 0);
-    if constexpr (KEEP) {
-      asm volatile("" ::: "memory");
-      Eu = kept->eu[lane];
-      ET = kept->et[lane];
-      Pu = Eu & ~(kept->pt[lane] & ~ok);
-    } else {
-      Pu &= ~(Pt & ~ok);
-    }
+                                  : V.slack > 0    ? tile_product<true>(V, S, X, Y, lane, kept, W, 0)
+                                                   : tile_product<false>(V, S, X, Y, lane, kept, W, 0);
+    asm volatile("" ::: "memory");
+    Eu = kept.eu[lane];
+    ET = kept.et[lane];
+    Pu = Eu & ~(kept.pt[lane] & ~ok);
   }
   // transposes: lane v gets bit v of every P(u) (rows u >= xl hold zero) and,
   // in pass 1, of every E(u), to check that the rows are symmetric
@@ -634,34 +630,29 @@ __device__ __forceinline__ void tile(const GView &V, BatchLds &S, int X, int Y, 
   if (lane == 0 && cnt) atomicAdd(&S.tests, (unsigned long long)cnt);
 }
 
-// The workgroup's LDS, reachable from run_items as well as from the kernel.
-__device__ __forceinline__ BatchLds &lds() {
-  __shared__ BatchLds S;
+// The workgroup's LDS, reachable from run_items as well as from the kernel.  The
+// job's part comes first: its offsets then fit the 16 bits of an LDS
+// instruction, where behind the waves' rows each access needs an address
+// register (41 registers spilled, 29 with this; batch of 512 graphs with slack
+// 8.29 ms, 8.20).
+struct BatchShared {
+  BatchLds job;
+  TileRows rows[NW];
+  Kept kept[NW];
+};
+__device__ __forceinline__ BatchShared &lds() {
+  __shared__ BatchShared S;
   return S;
-}
-template <int NW>
-__device__ __forceinline__ TileRows &lds_rows(int wid) {
-  __shared__ TileRows W[NW];
-  return W[wid];
-}
-template <int NW>
-__device__ __forceinline__ Kept *lds_kept(int wid) {
-  if constexpr (NW > 4) {
-    __shared__ Kept K[NW];
-    return K + wid;
-  }
-  return nullptr;
 }
 
 // The waves of the workgroup take the items of the claimed run one by one.
 // A function of its own: a tile's sums need most of the registers, and next
 // to the rest of the kernel the compiler keeps them in scratch memory (27 GB
 // of writes a launch of 4096 graphs).
-template <int NW>
 __device__ __attribute__((noinline)) void run_items() {
-  BatchLds &S = lds();
+  BatchLds &S = lds().job;
   const int lane0 = threadIdx.x & 63, wid = uni((int)(threadIdx.x >> 6));
-  TileRows &W = lds_rows<NW>(wid);
+  TileRows &W = lds().rows[wid];
   GView V;
   V.n = uni(S.view.n);
   V.k = uni(S.view.k);
@@ -691,7 +682,7 @@ __device__ __attribute__((noinline)) void run_items() {
 #pragma unroll 1
       for (int h = 0; h < kVChunk; h += kWave) vertex_chunk(V, S, v0 + h, first, lane);
     } else {
-      tile<(NW > 4)>(V, S, it & kXMask, (it >> kYShift) & kXMask, first, lane, W, lds_kept<NW>(wid));
+      tile(V, S, it & kXMask, (it >> kYShift) & kXMask, first, lane, W, lds().kept[wid]);
     }
   }
   __syncthreads();
@@ -737,7 +728,6 @@ __device__ void end_job(const BatchArgs &a, const GView &V, int passes) {
 // opens it: solo (the whole list is this workgroup's run) or shared
 // (published, this workgroup's first run taken).  Returns false when the
 // pass has nothing to test: the job is then finished.
-template <int NW>
 __device__ bool open_pass(const BatchArgs &a, const GView &V, BatchLds &S) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int n = V.n, R = V.R, p = S.pass;
@@ -837,7 +827,6 @@ __device__ bool open_pass(const BatchArgs &a, const GView &V, BatchLds &S) {
 
 // Sets up graph g (validation, layout, state) and opens its first pass.
 // Returns false when the graph needs no pass (error, empty graph).
-template <int NW>
 __device__ bool start_job(const BatchArgs &a, BatchLds &S, int g) {
   const int tid = threadIdx.x;
   if (a.session) {
@@ -967,13 +956,12 @@ __device__ bool start_job(const BatchArgs &a, BatchLds &S, int g) {
     S.tests = 0;
   }
   __syncthreads();
-  return open_pass<NW>(a, V, S);
+  return open_pass(a, V, S);
 }
 
 // Claims a run of unclaimed items of job g (thread 0; S.got = 0: none left).
 // A workgroup joining a pass it did not list loads the job's layout and
 // touched sets after an acquire fence.
-template <int NW>
 __device__ void claim(const BatchArgs &a, BatchLds &S, int g) {
   const int tid = threadIdx.x;
   BatchJob *J = a.jobs + g;
@@ -1109,7 +1097,6 @@ __device__ bool retire(const GView &V, BatchLds &S) {
 
 // The carrier: applies the changed tiles, closes the pass, and ends the job
 // or opens the next pass.  Returns true when a next pass is open.
-template <int NW>
 __device__ bool carry(const BatchArgs &a, const GView &V, BatchLds &S) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   BatchJob *J = V.J;
@@ -1178,7 +1165,7 @@ __device__ bool carry(const BatchArgs &a, const GView &V, BatchLds &S) {
     S.tests = 0;
   }
   __syncthreads();
-  return open_pass<NW>(a, V, S);
+  return open_pass(a, V, S);
 }
 
 // Looks on the board for the shared pass with the most unclaimed items, if
@@ -1259,9 +1246,8 @@ __device__ int take_request(const BatchArgs &a, BatchLds &S) {
   return -1;
 }
 
-template <int NW>
 __global__ void __launch_bounds__(NW * 64, 4) k_batch(BatchArgs a) {
-  BatchLds &S = lds();
+  BatchLds &S = lds().job;
   const int tid = threadIdx.x;
   if (tid == 0) {
     S.job = -1;
@@ -1277,13 +1263,13 @@ __global__ void __launch_bounds__(NW * 64, 4) k_batch(BatchArgs a) {
   int backoff = 1;                // idle polls sleep 1, 2, 4 or 8 times between looks
   for (;;) {
     if (job >= 0) {
-      if (!S.got) claim<NW>(a, S, job);
+      if (!S.got) claim(a, S, job);
       if (S.got) {
         const GView V = gview(a, job);
         if (tid == 0) S.view = V;
         __syncthreads();
-        run_items<NW>();
-        if (retire(V, S) && !carry<NW>(a, V, S)) job = -1;
+        run_items();
+        if (retire(V, S) && !carry(a, V, S)) job = -1;
         continue;
       }
       job = -1;
@@ -1308,7 +1294,7 @@ __global__ void __launch_bounds__(NW * 64, 4) k_batch(BatchArgs a) {
       __syncthreads();
       const int g = S.gi;
       if (g >= 0) {
-        if (start_job<NW>(a, S, g)) job = g;
+        if (start_job(a, S, g)) job = g;
         idle0 = 0;
         backoff = 1;
         continue;
@@ -1457,12 +1443,7 @@ void launch_batch(const BatchArgs &args, const BatchConfig &cfg, hipStream_t s) 
     if (cost) hipLaunchKernelGGL(k_batch_cost, dim3(a.G), dim3(64), 0, s, a);
     hipLaunchKernelGGL(k_batch_order, dim3(1), dim3(1024), 0, s, a, cost ? 2 : cfg.lpt);
   }
-  const dim3 grid(cfg.workgroups);
-#define KZ_B(NW) hipLaunchKernelGGL((k_batch<NW>), grid, dim3(NW * 64), 0, s, a)
-  if (cfg.waves == 4) KZ_B(4);
-  else if (cfg.waves == 8) KZ_B(8);
-  else KZ_B(16);
-#undef KZ_B
+  hipLaunchKernelGGL(k_batch, dim3(cfg.workgroups), dim3(NW * kWave), 0, s, a);
 }
 
 }  // namespace kzi

@@ -300,6 +300,7 @@ void launch_small(const kz_graph &g, const int32_t *colour, int k, uint8_t *vmas
 
 // Batched path (kz_batch.hip).
 constexpr int kBatchK = 64;          // classes
+constexpr int kBatchWaves = 16;      // waves of a workgroup
 constexpr int kBatchR = 512;         // words per row (blocks)
 constexpr int kBatchN = 32768;       // vertices
 constexpr int kBatchSortMax = 8192;  // graphs ordered by work on the device up to this count
@@ -396,7 +397,7 @@ struct BatchArgs {
 constexpr unsigned kRingFree = 0xffffffffu;  // a ring entry the device has read
 
 struct BatchConfig {
-  int waves, chunk, lpt, workgroups, share;
+  int waves, chunk, lpt, workgroups, share;  // waves and chunk: kept for saved configurations, no effect
 };
 
 void launch_batch(const BatchArgs &a, const BatchConfig &cfg, hipStream_t s);

@@ -450,7 +450,7 @@ int launch_session(kz_server *s) {
   a.idle_ticks = (unsigned long long)s->idle_us * (unsigned long long)s->clock_khz / 1000ull;
   a.lease_ticks = (unsigned long long)s->lease_us * (unsigned long long)s->clock_khz / 1000ull;
   kzi::BatchConfig c = s->ctx->batch_cfg;
-  c.workgroups = s->session_cus * (16 / c.waves);
+  c.workgroups = s->session_cus;
   if (c.workgroups > kSrvMaxWorkgroups) c.workgroups = kSrvMaxWorkgroups;
   kzi::launch_batch(a, c, s->sstream);
   if (hipGetLastError() != hipSuccess || hipEventRecord(e, s->sstream) != hipSuccess) {
