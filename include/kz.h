@@ -508,8 +508,8 @@ int kz_gen_bitset(kz_ctx *ctx, int32_t k, const int32_t *sizes, double p, uint32
  *   ws, ws_bytes: device workspace of kz_colour_workspace_bytes() bytes,
  *         256-byte aligned;
  *   colour: device int32[n] out, in [0, colours).
- * Blocking: a small readback after validation and one at the end (sparse
- * graphs, of average degree below n / 100: one per chunk of rounds). */
+ * Blocking: a small readback after validation and one at the end (graphs
+ * that are sparse or turn out to have few rounds: one per chunk of rounds). */
 typedef struct kz_colour_result {
   int32_t status;
   int32_t rounds;

@@ -22,13 +22,18 @@
 // see of the blocks before: a bitmap of the colours in use and the largest
 // round; the block resolved meanwhile is merged in between two barriers.
 //
-// A block takes about 20 us whatever its edges, a round 10 to 20 us, and a
-// graph of average degree d has about 2 d rounds: sparse graphs (d below n /
-// 100) run the rounds instead, two kernels each: one wave per vertex tests
-// row & U (U: the uncoloured vertices; only they can beat it), then one wave
-// per taken vertex marks the colours of row & ~U in an LDS bitmap and takes
-// its lowest zero bit.  At 20000 vertices of average degree 200 both take
-// 7.2 to 7.6 ms; at degree 1000 38 ms and 9.9 ms.
+// The rounds themselves, two kernels each, are the other way: one wave per
+// vertex tests row & U (U: the uncoloured vertices; only they can beat it),
+// then one wave per taken vertex marks the colours of row & ~U in an LDS bitmap
+// and takes its lowest zero bit.  They win where the rounds are few: a random
+// graph of average degree d has about 2 d of them (at 20000 vertices of degree
+// 200 both ways take 7.2 to 7.6 ms, at degree 1000 38 ms and 9.9 ms), but the
+// priorities may order a graph by its classes or its hubs (a complete bipartite
+// graph of 20000 vertices, one side's priorities above the other's: 2 rounds in
+// 1.6 ms, 46 ms by blocks).  So graphs of average degree below n / 100 run the
+// rounds, and others the first few of them, from which rounds_left tells how many
+// are to come (1.7 ms for that bipartite graph; 3000 vertices at p = 0.3, by blocks:
+// 0.84 ms with and without).
 #include <string.h>
 
 #include <algorithm>
@@ -41,8 +46,12 @@ namespace {
 constexpr int kColWaves = 4;                // waves (vertices) per workgroup of the check
 constexpr int kColMaxWords = 1024;          // row words (65536 vertices)
 constexpr size_t kColAlign = 256;
+constexpr int kColSlots = 32;               // spread of the degrees' sums
 constexpr int kColFirstChunk = 8;           // rounds enqueued before the first look at the count
 constexpr int kColMaxChunk = 128;           // ... and at most between two looks
+constexpr int kColProbeN = 512;             // vertices from which the first rounds tell how many are to come
+constexpr double kColProbe = 1.0 / 48;      // ... for this share of the blocks' time
+constexpr double kColProbeHubs = 1.0 / 3;   // ... and while hubs are taken, for this one
 constexpr int kColThreads = 1024;           // the greedy workgroup
 constexpr int kColLdsWords = 32;            // words of a bitmap of colours kept in LDS (the rest in memory)
 constexpr int kColLdsColours = 64 * kColLdsWords;
@@ -54,8 +63,14 @@ struct ColCtr {
   int bad;      // validation: a KZ_* status, most severe first (see k_col_check)
   int top;      // largest colour given
   int rounds;   // rounds
-  unsigned long long ends;  // sum of the degrees
+  unsigned long long gone;  // edges with an end coloured (rounds, where counted)
+  // sums of the degrees and of their squares, over slots of a line each: a
+  // graph's thousands of workgroups would queue at one
+  struct alignas(64) {
+    unsigned long long ends, squares;
+  } sum[kColSlots];
 };
+static_assert(sizeof(ColCtr) <= kzi::kPinnedBytes, "read back into the context's pinned memory");
 
 size_t col_up(size_t x) { return (x + kColAlign - 1) / kColAlign * kColAlign; }
 
@@ -96,8 +111,8 @@ __device__ __forceinline__ bool key_beats(unsigned long long pu, int u, unsigned
 // colour = -1, U = every vertex.
 __global__ void __launch_bounds__(kColWaves * 64) k_col_check(int n, const uint64_t *__restrict__ rows, int R,
                                                               int *rank, int *colour, uint64_t *U, ColCtr *ctr) {
-  __shared__ unsigned long long ends;
-  if (threadIdx.x == 0) ends = 0;
+  __shared__ unsigned long long ends, squares;
+  if (threadIdx.x == 0) ends = squares = 0;
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int v = blockIdx.x * kColWaves + (threadIdx.x >> 6);
@@ -129,12 +144,17 @@ __global__ void __launch_bounds__(kColWaves * 64) k_col_check(int n, const uint6
     if (v == 0) ctr->left = n;
     if ((v & 63) == 0) U[v >> 6] = n - v >= 64 ? ~0ull : (1ull << (n - v)) - 1;
     atomicAdd(&ends, (unsigned long long)deg);
+    atomicAdd(&squares, (unsigned long long)deg * (unsigned long long)deg);
   }
   __syncthreads();
-  if (threadIdx.x == 0 && ends) atomicAdd(&ctr->ends, ends);
+  if (threadIdx.x == 0 && ends) {
+    auto &sum = ctr->sum[blockIdx.x % kColSlots];
+    atomicAdd(&sum.ends, ends);
+    atomicAdd(&sum.squares, squares);
+  }
 }
 
-// ---- sparse graphs: the rounds themselves
+// ---- the rounds themselves
 
 // One round's choice, one wave per vertex: sel[v] = v is uncoloured and its
 // key beats every uncoloured neighbour's.
@@ -144,7 +164,7 @@ __global__ void __launch_bounds__(kColWaves * 64) k_col_select(int n, const uint
                                                                ColCtr *ctr) {
   const int lane = threadIdx.x & 63;
   const int v = blockIdx.x * kColWaves + (threadIdx.x >> 6);
-  if (ctr->left == 0) return;  // coloured in an earlier round of this chunk
+  if (ctr->left == 0 || ctr->bad) return;  // coloured in an earlier round of this chunk, or refused
   if (v == 0 && lane == 0) atomicAdd(&ctr->rounds, 1);
   if (v >= n) return;
   const bool unc = (U[v >> 6] >> (v & 63)) & 1ull;
@@ -174,10 +194,12 @@ __global__ void __launch_bounds__(kColWaves * 64) k_col_select(int n, const uint
 }
 
 // One round's colours, one wave per vertex taken: the smallest colour that
-// no neighbour coloured earlier holds; then v leaves U.
+// no neighbour coloured earlier holds; then v leaves U.  `count`: its edges to the
+// uncoloured are added to ctr->gone (none of those neighbours is taken in this
+// round, so an edge counts once).
 __global__ void __launch_bounds__(kColWaves * 64) k_col_colour(int n, const uint64_t *__restrict__ rows, int R,
                                                                const uint8_t *__restrict__ sel, uint64_t *U,
-                                                               int *colour, ColCtr *ctr) {
+                                                               int *colour, ColCtr *ctr, int count) {
   __shared__ unsigned long long used[kColWaves][kColMaxWords];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int v = blockIdx.x * kColWaves + wid;
@@ -185,15 +207,18 @@ __global__ void __launch_bounds__(kColWaves * 64) k_col_colour(int n, const uint
   // (that kernel then returned at once and sel is a previous round's): a
   // vertex taken in this round keeps it positive until its own wave below
   // has coloured it
-  if (v >= n || ctr->left == 0 || !sel[v]) return;
+  if (v >= n || ctr->left == 0 || ctr->bad || !sel[v]) return;
   const int W = (n + 63) >> 6;
+  int ends = 0;
   unsigned long long *mine = used[wid];
   for (int w = lane; w < W; w += 64) mine[w] = 0ull;
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   const uint64_t *row = rows + (long long)v * R;
   for (int w = lane; w < W; w += 64) {
-    unsigned long long x = row[w] & ~U[w];  // neighbours coloured in earlier rounds
+    const unsigned long long y = row[w], u = U[w];
+    ends += __popcll(y & u);
+    unsigned long long x = y & ~u;  // neighbours coloured in earlier rounds
     while (x) {
       const int b = __builtin_ctzll(x);
       x &= x - 1;
@@ -216,6 +241,10 @@ __global__ void __launch_bounds__(kColWaves * 64) k_col_colour(int n, const uint
     }
   }
   if (c < 0) c = 64 * W;  // every colour below 64*W held (cannot happen: v has fewer than n neighbours)
+  if (count) {
+    ends = kzi::wave_sum(ends);
+    if (lane == 0 && ends) atomicAdd(&ctr->gone, (unsigned long long)ends);
+  }
   if (lane == 0) {
     colour[v] = c;
     atomicMax(&ctr->top, c);
@@ -459,6 +488,47 @@ __global__ void __launch_bounds__(kColThreads) k_col_greedy(int n, const uint64_
   }
 }
 
+// ---- which way
+
+// A graph's degrees, from the check.
+struct ColDegrees {
+  int n;
+  unsigned long long ends, squares;
+  double edges() const { return 0.5 * (double)ends; }
+  bool sparse() const { return 100 * ends < (unsigned long long)n * (unsigned long long)n; }
+  // most edges are a few hubs': the squares' sum is above twice that of even degrees
+  bool hubs() const { return squares > 2 * (ends / (unsigned)n) * ends; }
+  // times in us of a round (its last term is a vertex looking through all its
+  // neighbours: the degree at an edge's end) and of all blocks
+  double round_us() const { return 10 + 4e-4 * n + 3.2e-3 * (double)squares / std::max(1.0, (double)ends); }
+  double blocks_us() const { return (n + 63) / 64 * (n > kColLdsN ? 20.0 : 12.0) + 3e-4 * edges(); }
+  int probe(double share) const { return (int)(share * blocks_us() / round_us()); }
+};
+
+// The rounds to come, from what the last `rounds` of them took: `was` before
+// them, `now` behind them.  At their rate the edges left last edges / e rounds; up
+// to twice that where the vertices go at the same rate (a vertex then takes ever
+// fewer edges along), and twice again on even degrees, where ever fewer vertices
+// beat all their neighbours (3000 vertices at p = 0.3 have 1272 rounds; the first
+// takes 4 vertices), not on hubs'.  Below 0: no edge went, no telling.
+double rounds_left(const ColDegrees &d, const ColCtr &was, const ColCtr &now, int rounds) {
+  const double before = d.edges() - (double)was.gone, left = d.edges() - (double)now.gone;
+  if (left <= 0) return 0;
+  const double e = ((double)now.gone - (double)was.gone) / rounds, v = (double)(was.left - now.left) / rounds;
+  if (e <= 0) return -1;
+  return left / e * (1 + std::min(1.0, 2 * (v / was.left) / (e / before))) * (d.hubs() ? 1 : 2.1);
+}
+
+// Whether the vertices taken had a quarter more edges than the uncoloured on the
+// average: hubs come first, and what they tell may end with them.
+bool hubs_first(const ColDegrees &d, const ColCtr &was, const ColCtr &now) {
+  const double taken = (double)(was.left - now.left), before = d.edges() - (double)was.gone;
+  return ((double)now.gone - (double)was.gone) * was.left > 1.25 * 2 * before * taken;
+}
+
+// Whether that many rounds take less time than the blocks.
+bool by_rounds(const ColDegrees &d, double left) { return left >= 0 && left * d.round_us() < d.blocks_us(); }
+
 }  // namespace
 
 extern "C" {
@@ -511,32 +581,56 @@ int kz_colour_jp(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
            hipMemcpyAsync(h, ctr, sizeof(ColCtr), hipMemcpyDeviceToHost, s) == hipSuccess &&
            hipStreamSynchronize(s) == hipSuccess;
   };
+  int ran = 0;  // rounds enqueued
+  auto enqueue = [&](int rounds, bool count) {
+    for (int i = 0; i < rounds; ++i) {
+      hipLaunchKernelGGL(k_col_select, grid, block, 0, s, n, rows, (int)row_words, priority, U, sel, ctr);
+      hipLaunchKernelGGL(k_col_colour, grid, block, 0, s, n, rows, (int)row_words, sel, U, colour, ctr, (int)count);
+    }
+    ran += rounds;
+  };
   if (hipMemsetAsync(ctr, 0, sizeof(ColCtr), s) != hipSuccess) return done();
   hipLaunchKernelGGL(k_col_check, grid, block, 0, s, n, rows, (int)row_words, rank, colour, U, ctr);
+  // the first rounds go out with the check, as many as a share of the blocks'
+  // time allows whatever the edges
+  ColDegrees d{n, 0, 0};
+  if (n >= kColProbeN) enqueue(std::max(1, d.probe(kColProbe)), true);
   if (!read_back()) return done();
   if (h->bad) {
     r.status = h->bad == 3 ? KZ_EINVAL : h->bad == 2 ? KZ_ESELFLOOP : KZ_EASYM;
     return done();
   }
-  if (100 * h->ends < (unsigned long long)n * (unsigned long long)n) {
+  for (const auto &x : h->sum) {
+    d.ends += x.ends;
+    d.squares += x.squares;
+  }
+  const bool sparse = d.sparse();
+  const int probe = d.probe(kColProbeHubs);
+  ColCtr was{};
+  was.left = n;
+  int chunk = kColFirstChunk, last = ran;
+  for (;;) {
     // rounds in chunks, ended on the device: one readback per chunk (rounds
     // past the last one return at once)
-    int chunk = kColFirstChunk, last_left = n;
-    for (;;) {
-      for (int i = 0; i < chunk; ++i) {
-        hipLaunchKernelGGL(k_col_select, grid, block, 0, s, n, rows, (int)row_words, priority, U, sel, ctr);
-        hipLaunchKernelGGL(k_col_colour, grid, block, 0, s, n, rows, (int)row_words, sel, U, colour, ctr);
-      }
-      if (!read_back()) return done();
-      if (h->left == 0) break;
-      if (h->left >= last_left) return done();  // cannot happen: every round takes the largest uncoloured key
-      last_left = h->left;
-      chunk = std::min(2 * chunk, kColMaxChunk);
+    if (h->left == 0) {
+      r.status = KZ_OK;
+      r.rounds = h->rounds;
+      r.colours = h->top + 1;
+      return done();
     }
-    r.status = KZ_OK;
-    r.rounds = h->rounds;
-    r.colours = h->top + 1;
-    return done();
+    if (last > 0 && h->left >= was.left) return done();  // cannot happen: every round takes the largest uncoloured key
+    int next = chunk;
+    if (!sparse) {
+      const double left = last > 0 ? rounds_left(d, was, *h, last) : -1;
+      if (by_rounds(d, left)) next = (int)std::min((double)chunk, left + 1);
+      else if (last > 0 && ran < probe && hubs_first(d, was, *h)) next = std::min(chunk, probe - ran);
+      else break;
+    }
+    was = *h;
+    last = next;
+    enqueue(next, !sparse);
+    chunk = std::min(2 * chunk, kColMaxChunk);
+    if (!read_back()) return done();
   }
   hipLaunchKernelGGL(k_col_rank, dim3(blocks, (unsigned)((n + kRankSpan - 1) / kRankSpan)), dim3(kRankThreads), 0, s, n,
                      priority, rank);
