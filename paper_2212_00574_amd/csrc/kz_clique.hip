@@ -194,12 +194,26 @@ __global__ void __launch_bounds__(256) k_clique_alive(const uint64_t *__restrict
   __threadfence();
   // counts of the waves' quarters, then their prefix sums
   const int q = (s0 + 3) / 4, lo = min(s0, wid * q), hi = min(s0, lo + q);
+  // kAt loads in flight (100 000 vertices of class 0, one load after the other:
+  // 0.47 ms a call, 0.33 with these)
+  constexpr int kAt = 16;
+  long long x[kAt];
+  auto load = [&](int i0) {
+#pragma unroll
+    for (int j = 0; j < kAt; ++j) {
+      const int i = i0 + j * kWave + lane;
+      x[j] = i < hi ? pre[i] : -1ll;
+    }
+  };
   long long sum = 0;
   int n0 = 0;
-  for (int i = lo + lane; i < hi; i += kWave) {
-    const long long x = pre[i];
-    sum += max(x, 0ll);
-    n0 += x >= 0;
+  for (int i0 = lo; i0 < hi; i0 += kAt * kWave) {
+    load(i0);
+#pragma unroll
+    for (int j = 0; j < kAt; ++j) {
+      sum += max(x[j], 0ll);
+      n0 += x[j] >= 0;
+    }
   }
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
   n0 = wave_sum(n0);
@@ -210,12 +224,15 @@ __global__ void __launch_bounds__(256) k_clique_alive(const uint64_t *__restrict
   __syncthreads();
   long long run = 0;
   for (int i = 0; i < wid; ++i) run += part[i];
-  for (int i0 = lo; i0 < hi; i0 += kWave) {
-    const int i = i0 + lane;
-    const long long x = i < hi ? max(pre[i], 0ll) : 0ll;  // below 2^21: 64 of them fit an int
-    const int s = wave_scan((int)x);
-    if (i < hi) pre[i] = run + s - x;
-    run += __builtin_amdgcn_readlane(s, kWave - 1);
+  for (int i0 = lo; i0 < hi; i0 += kAt * kWave) {
+    load(i0);
+#pragma unroll
+    for (int j = 0; j < kAt; ++j) {
+      const int i = i0 + j * kWave + lane, y = (int)max(x[j], 0ll);  // below 2^21: 64 of them fit an int
+      const int s = wave_scan(y);
+      if (i < hi) pre[i] = run + s - y;
+      run += __builtin_amdgcn_readlane(s, kWave - 1);
+    }
   }
   if (threadIdx.x == 0) {
     bool empty = false;  // a class with no vertex: no clique, no root
@@ -802,7 +819,8 @@ int kz_find_clique(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_
   long long *froot = (long long *)(base + z.root);
   int *fpick = (int *)(base + z.pick);
   hipLaunchKernelGGL(k_clique_setup, dim3(1), dim3(256), 0, s, colour, n, k, R, h, share, froot, omask);
-  hipLaunchKernelGGL(k_clique_alive, dim3((unsigned)std::min((R + 2 * (n / k)) / 4 + 1, 2048)), dim3(256), 0, s,
+  // 512 workgroups at most: each ends with a release, which writes its XCD's L2 back
+  hipLaunchKernelGGL(k_clique_alive, dim3((unsigned)std::min((R + 2 * (n / k)) / 4 + 1, 512)), dim3(256), 0, s,
                      g->rows, vmask, k, R, h, am, pre);
   // A node of every level fits LDS: level d has at most R - d words left, as
   // every class before it has one (an empty class ends the search).
