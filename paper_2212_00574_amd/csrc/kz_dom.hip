@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(256) k_dom_setup(const uint64_t *__restrict__ 
 // 2.6 -> 0.87 and 5.5 -> 2.8 ms; the earlier form tested node by node, a
 // chain of dependent loads per test.
 constexpr int kDomLdsWords = 19840;  // rows kept in LDS up to this many words ...
-constexpr int kDomLdsR = 32;         // ... and this row width (then at most 1127 nodes)
+constexpr int kDomLdsR = 32;         // ... and this row width (then at most 1102 nodes)
 constexpr int kDomLdsNodes = 1152;
 
 template <int GL, int WPL>
@@ -128,8 +128,25 @@ __device__ __forceinline__ unsigned long long group_lanes(bool p, int lane) {
 template <int GL, int WPL>
 __device__ __forceinline__ void dom_strike(const uint64_t *rows, int R, int lane, DomSet<GL, WPL> &cur,
                                            DomSet<GL, WPL> &T, const uint64_t *D) {
-  constexpr int kAhead = WPL < 16 ? 4 : 1;  // rows in flight
+  constexpr int kAhead = WPL < 8 ? 4 : WPL < 16 ? 2 : 1;  // rows in flight
   const int gl = lane & (GL - 1), base = lane & ~(GL - 1);
+  if constexpr (GL == 1) {
+    // a row is a word: a lane's own loop
+    static_assert(WPL == 1, "rows of one word");
+    while (cur.w[0] && T.w[0]) {
+      uint64_t m[kAhead];
+      int x = 0;
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) {
+        if (T.w[0]) x = __builtin_ctzll(T.w[0]);
+        T.w[0] &= T.w[0] - 1;
+        m[i] = rows[x * R] & (D && ((D[0] >> x) & 1ull) ? (1ull << x) - 1 : ~0ull);
+      }
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) cur.w[0] &= ~m[i];
+    }
+    return;
+  }
   for (;;) {
     bool mine = false, left = false;
     int x = 0;  // this lane's first node of T
@@ -174,30 +191,58 @@ __device__ __forceinline__ void dom_strike(const uint64_t *rows, int R, int lane
   }
 }
 
-// The same for sparse graphs, where a struck row takes out few nodes: every
-// node of cur against row b, a lane per word.
+// Whether row a lies inside row b.
+__device__ __forceinline__ bool dom_inside(const uint64_t *ra, const uint64_t *rb, int R) {
+  for (int w = 0; w < R; ++w)
+    if (ra[w] & ~rb[w]) return false;
+  return true;
+}
+
+// For sparse graphs, where a struck row takes out few nodes: whether row b has
+// one of cur's nodes inside, a lane per word, up to the group's first.
 template <int GL, int WPL>
-__device__ __forceinline__ void dom_scan(const uint64_t *rows, int R, int b, int lane, DomSet<GL, WPL> &cur) {
+__device__ __forceinline__ bool dom_scan(const uint64_t *rows, int R, int b, int lane, const DomSet<GL, WPL> &cur) {
   const uint64_t *rb = rows + (long long)b * R;
-#pragma unroll
+#pragma unroll 1
   for (int j = 0; j < WPL; ++j) {
-    uint64_t cand = cur.w[j];
-    while (cand) {
-      const int i = __builtin_ctzll(cand);
-      cand &= cand - 1;
-      const uint64_t *ra = rows + (long long)(64 * ((lane & (GL - 1)) + GL * j) + i) * R;
-      for (int w = 0; w < R; ++w)
-        if (ra[w] & ~rb[w]) {
-          cur.w[j] &= ~(1ull << i);
-          break;
-        }
+    uint64_t cand = 0ull;
+#pragma unroll
+    for (int q = 0; q < WPL; ++q) cand = q == j ? cur.w[q] : cand;
+    const int base = 64 * ((lane & (GL - 1)) + GL * j);
+    while (group_lanes<GL>(cand != 0ull, lane) != 0ull) {
+      bool hit = false;
+      if (cand) {
+        hit = dom_inside(rows + (long long)(base + __builtin_ctzll(cand)) * R, rb, R);
+        cand &= cand - 1;
+      }
+      if (group_lanes<GL>(hit, lane) != 0ull) return true;
     }
   }
+  return false;
 }
 
 __device__ __forceinline__ uint64_t dom_valid(int w, int n) {
   const int lo = 64 * w;
   return lo + 64 <= n ? ~0ull : lo < n ? (1ull << (n - lo)) - 1 : 0ull;
+}
+
+// Whether dom_scan is the faster one for a graph of that average degree.  Rows in
+// memory: a scan is bounded by the loads of 64 rows at once, one for every word
+// looked at until one has a bit that b lacks (0.77 us each with 16 waves at it, for 16
+// b); striking takes about n ln(n) / degree rows, 4 or fewer at a time, a
+// round trip each (1.2 to 3 us by the words a lane holds).  Scanned and struck: 2100
+// nodes of degree 42 8 and 17 ms, of degree 210 2.8 and 2.4; 5000 of degree 250 20
+// and 32, of degree 2500 8.5 and 2.9.
+template <int NT, int GL, int WPL, bool LDS>
+__device__ __forceinline__ bool dom_scans(float degree, int n, int R) {
+  if (degree * degree * degree < 8.f * n) return true;
+  if (LDS || 4.f * degree > n) return false;
+  const float d = fmaxf(degree, 1e-3f), off = 1.f - d / (float)n;
+  const float words = fminf(1.f / (1.f - __expf(-d / (float)R * off)), (float)R);
+  const float scan = 0.012f * min(R, kWave) * 64.f * (float)((R + kWave - 1) / kWave) * off * words / 16.f;
+  const float rows = fminf((float)n, (float)n * __logf((float)n) / d);
+  const float strike = rows * (WPL == 1 ? 0.3f : WPL < 8 ? 0.6f : WPL < 16 ? 1.5f : 4.f) / (float)(NT / GL);
+  return scan < strike;
 }
 
 // ---- vertex dominance (Definition 4.3.1): the whole fixpoint, one workgroup
@@ -235,8 +280,7 @@ __global__ void __launch_bounds__(NT) k_dom_vertex_run(uint64_t *__restrict__ st
     first[0] = first[1] = n;
   }
   __syncthreads();
-  const double degree = (double)h->dirs / n;
-  const bool sparse = degree * degree * degree < 8. * n;
+  const bool sparse = dom_scans<NT, GL, WPL, LDS>((float)h->dirs / (float)n, n, R);
   long long sweeps = 0, steps = 0;
   int par = 0;
   for (;;) {
@@ -254,12 +298,15 @@ __global__ void __launch_bounds__(NT) k_dom_vertex_run(uint64_t *__restrict__ st
           if (w == (b >> 6)) cur.w[j] &= ~(1ull << (b & 63));
           T.w[j] = cur.w[j];
         }
-        if (sparse) dom_scan<GL, WPL>(rows, R, b, lane, cur);
-        else dom_strike<GL, WPL>(rows, R, lane, cur, T, nullptr);
-        bool some = false;
+        if (sparse) {
+          hit = dom_scan<GL, WPL>(rows, R, b, lane, cur);
+        } else {
+          dom_strike<GL, WPL>(rows, R, lane, cur, T, nullptr);
+          bool some = false;
 #pragma unroll
-        for (int j = 0; j < WPL; ++j) some |= cur.w[j] != 0ull;
-        hit = group_lanes<GL>(some, lane) != 0ull;
+          for (int j = 0; j < WPL; ++j) some |= cur.w[j] != 0ull;
+          hit = group_lanes<GL>(some, lane) != 0ull;
+        }
         if (hit && gl == 0) atomicMin(&first[par], b);
       }
       __syncthreads();
@@ -269,8 +316,19 @@ __global__ void __launch_bounds__(NT) k_dom_vertex_run(uint64_t *__restrict__ st
         b0 += kGroups;
         continue;
       }
-      // the step that dominates someone: its group has the set
-      if (b == bf) {
+      // the step that dominates someone: its group has the set, or a scan knew
+      // of one and the workgroup tests every node
+      const uint64_t *rb = rows + (long long)bf * R;
+      if (sparse) {
+        for (int x0 = tid & ~63; x0 < n; x0 += NT) {
+          const int x = x0 + lane, w = x0 >> 6;
+          const uint64_t may = AL[w] & ~rb[w] & ~(w == (bf >> 6) ? 1ull << (bf & 63) : 0ull);
+          const unsigned long long in =
+              __ballot(((may >> lane) & 1ull) && dom_inside(rows + (long long)x * R, rb, R));
+          if (lane == 0) D[w] = in;
+        }
+        for (int w = (n + 63) / 64 + tid; w < R; w += NT) D[w] = 0ull;
+      } else if (b == bf) {
 #pragma unroll
         for (int j = 0; j < WPL; ++j) {
           const int w = gl + GL * j;
@@ -290,7 +348,6 @@ __global__ void __launch_bounds__(NT) k_dom_vertex_run(uint64_t *__restrict__ st
       // the deleted nodes lose their rows; their neighbours (all in N(b))
       // lose them, in the words listed in dw.  Row b itself does not change.
       const int nd = ndw;
-      const uint64_t *rb = rows + (long long)bf * R;
       for (int x = tid; x < n; x += NT) {
         uint64_t *rx = rows + (long long)x * R;
         if ((D[x >> 6] >> (x & 63)) & 1ull) {
@@ -335,67 +392,51 @@ __global__ void __launch_bounds__(NT) k_dom_vertex_run(uint64_t *__restrict__ st
 // takes one b at a time from the list of the nodes not adjacent to a (where a
 // has few neighbours, of those next to one of them); nodes
 // already deleted in the step (D) join the list, for the nodes after them,
-// and count as gone from N(a) for the nodes after them.
-template <int NT, int GL, int WPL, bool LDS>
-__global__ void __launch_bounds__(NT) k_dom_edge_run(uint64_t *__restrict__ st, int n, int R, DomHdr *h) {
+// and count as gone from N(a) for the nodes after them.  In thin graphs (average
+// degree below the root of n) every wave counts a's neighbours first: a node
+// without any is no step, with no barrier; one with few needs no list of the
+// others; and a turn that sees every neighbour found is the last (a star's
+// leaves: the first b is enough).
+template <bool LDS>
+struct EdgeLds {
+  static constexpr int kWords = LDS ? kDomLdsR : kDomMaxWords;
+  uint64_t rows[LDS ? kDomLdsWords : 1];
+  uint64_t na[kWords], D[kWords], Dn[kWords];  // N(a); deleted so far; found in this pass
+  unsigned short list[LDS ? kDomLdsNodes : 64 * kDomMaxWords];
+  int cnt[2], near[2];
+  long long found;  // the last pass that found a node
+  unsigned long long nd;
+};
+
+template <int NT, int GL, int WPL, bool LDS, bool THIN>
+__device__ __forceinline__ void dom_edge_sweeps(uint64_t *__restrict__ st, int n, int R, DomHdr *h, EdgeLds<LDS> &S) {
   constexpr int kGroups = NT / GL;
-  constexpr int kWords = LDS ? kDomLdsR : kDomMaxWords;
-  __shared__ uint64_t sRows[LDS ? kDomLdsWords : 1];
-  __shared__ uint64_t na[kWords], D[kWords], Dn[kWords];  // N(a); deleted so far; found in this pass
-  __shared__ unsigned short list[LDS ? kDomLdsNodes : 64 * kDomMaxWords];
-  __shared__ int cnt[2];
-  __shared__ long long found;  // the last pass that found a node
-  __shared__ unsigned long long nd;
+  uint64_t *na = S.na, *D = S.D, *Dn = S.Dn;
+  unsigned short *list = S.list;
+  int *cnt = S.cnt;
   const int tid = threadIdx.x, lane = tid & 63, gl = lane & (GL - 1), group = tid / GL;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (h->prio != P_NONE) return;
-  uint64_t *rows = LDS ? sRows : st;
-  if (LDS)
-    for (int i = tid; i < n * R; i += NT) sRows[i] = st[i];
-  if (tid == 0) {
-    cnt[0] = cnt[1] = 0;
-    found = -1;
-    nd = 0;
-  }
-  __syncthreads();
+  uint64_t *rows = LDS ? S.rows : st;
   long long sweeps = 0, passes = 0;
   unsigned long long deleted = 0;  // this thread's share
   int par = 0;
   for (;;) {
     bool any_sweep = false;
-    for (int a = 0; a < n; ++a, par ^= 1) {
+    for (int a = 0; a < n; ++a) {
       // word w's nodes to the list, a lane per bit (the whole wave calls it)
-      auto append = [&](int w, uint64_t m) __attribute__((always_inline)) {
+      auto append = [&](int *count, int w, uint64_t m) __attribute__((always_inline)) {
         if (!m) return;
         int at = 0;
-        if (lane == 0) at = atomicAdd(&cnt[par], __popcll(m));
+        if (lane == 0) at = atomicAdd(count, __popcll(m));
         at = __builtin_amdgcn_readfirstlane(at);
         if ((m >> lane) & 1ull)
           list[at + __popcll(m & ((1ull << lane) - 1))] = (unsigned short)(64 * w + lane);
       };
       auto self = [&](int w) { return w == (a >> 6) ? 1ull << (a & 63) : 0ull; };
-      for (int w = wid; w < R; w += NT / kWave) {
-        const uint64_t x = rows[(long long)a * R + w];
-        if (lane == 0) {
-          na[w] = x;
-          D[w] = 0;
-          Dn[w] = 0;
-        }
-        append(w, ~x & dom_valid(w, n) & ~self(w));
-      }
-      __syncthreads();
-      if (tid == 0) cnt[par ^ 1] = 0;  // the next step's: nobody uses it in this one
-      int have = cnt[par];
-      bool grew = false;
-      const int deg = n - 1 - have;
-      if ((long long)deg * deg < have && have > 2 * kGroups) {
-        // few neighbours, many turns: only their neighbours can be b (gathered
-        // in Dn)
-        __syncthreads();
-        if (tid == 0) cnt[par] = 0;
-        __syncthreads();
-        for (int w = wid; w < R; w += NT / kWave) append(w, na[w]);
-        __syncthreads();
+      // few neighbours, many turns: only their neighbours can be b
+      auto is_few = [&](int deg, int others) { return (long long)deg * deg < others && others > 2 * kGroups; };
+      // their neighbours, gathered in Dn, from the list to the list
+      auto nodes_next = [&](int deg) __attribute__((always_inline)) {
         for (int i = group; i < deg; i += kGroups) {
           const uint64_t *ru = rows + (long long)list[i] * R;
           for (int w = gl; w < R; w += GL) {
@@ -403,15 +444,63 @@ __global__ void __launch_bounds__(NT) k_dom_edge_run(uint64_t *__restrict__ st, 
             if (x) atomicOr((unsigned long long *)&Dn[w], (unsigned long long)x);
           }
         }
-        __syncthreads();
-        if (tid == 0) cnt[par] = 0;
-        __syncthreads();
+      };
+      auto list_next = [&]() __attribute__((always_inline)) {
         for (int w = wid; w < R; w += NT / kWave) {
-          append(w, Dn[w] & ~na[w] & ~self(w));
+          append(&cnt[par], w, Dn[w] & ~na[w] & ~self(w));
           if (lane == 0) Dn[w] = 0;
         }
+      };
+      int deg = 0;
+      bool few = false;
+      if constexpr (THIN) {
+        for (int w = lane; w < R; w += kWave) deg += __popcll(rows[(long long)a * R + w]);
+        deg = wave_sum(deg);
+        if (deg == 0) {
+          ++passes;
+          continue;
+        }
+        few = is_few(deg, n - 1 - deg);
+      }
+      for (int w = wid; w < R; w += NT / kWave) {
+        const uint64_t x = rows[(long long)a * R + w];
+        if (lane == 0) {
+          na[w] = x;
+          D[w] = 0;
+          Dn[w] = 0;
+        }
+        if (THIN && few) append(&S.near[par], w, x);
+        else append(&cnt[par], w, ~x & dom_valid(w, n) & ~self(w));
+      }
+      __syncthreads();
+      if (tid == 0) {  // the next step's: nobody uses them in this one
+        cnt[par ^ 1] = 0;
+        if (THIN) S.near[par ^ 1] = 0;
+      }
+      bool grew = false;
+      if (THIN && few) {
+        nodes_next(deg);
         __syncthreads();
-        have = cnt[par];
+        list_next();
+        __syncthreads();
+      }
+      int have = cnt[par];
+      if constexpr (!THIN) {
+        deg = n - 1 - have;
+        if (is_few(deg, have)) {
+          __syncthreads();
+          if (tid == 0) cnt[par] = 0;
+          __syncthreads();
+          for (int w = wid; w < R; w += NT / kWave) append(&cnt[par], w, na[w]);
+          __syncthreads();
+          nodes_next(deg);
+          __syncthreads();
+          if (tid == 0) cnt[par] = 0;
+          __syncthreads();
+          list_next();
+          __syncthreads();
+          have = cnt[par];
+        }
       }
       int old = 0;  // list entries the last pass has tested
       for (;;) {
@@ -420,6 +509,7 @@ __global__ void __launch_bounds__(NT) k_dom_edge_run(uint64_t *__restrict__ st, 
           const int b = list[i];
           const bool later = grew && ((D[b >> 6] >> (b & 63)) & 1ull);  // b counts for the nodes after it
           DomSet<GL, WPL> cur, T;
+          bool left = false;  // nodes not found yet
 #pragma unroll
           for (int j = 0; j < WPL; ++j) {
             const int w = gl + GL * j;
@@ -429,10 +519,14 @@ __global__ void __launch_bounds__(NT) k_dom_edge_run(uint64_t *__restrict__ st, 
               const uint64_t after = !later || w > (b >> 6) ? ~0ull
                                      : w == (b >> 6)        ? ~((2ull << (b & 63)) - 1)
                                                             : 0ull;
-              cur.w[j] = x & rb & ~D[w] & after;
+              uint64_t open = x & ~D[w];
+              if (THIN) open &= ~__hip_atomic_load(&Dn[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+              left |= open != 0ull;
+              cur.w[j] = open & rb & after;
               T.w[j] = x & ~rb;
             }
           }
+          if (THIN && group_lanes<GL>(left, lane) == 0ull) break;
           if (i < old) {
             // tested before: something changes only where T meets a node
             // deleted in this step
@@ -449,21 +543,22 @@ __global__ void __launch_bounds__(NT) k_dom_edge_run(uint64_t *__restrict__ st, 
           for (int j = 0; j < WPL; ++j)
             if (cur.w[j]) {
               atomicOr((unsigned long long *)&Dn[gl + GL * j], (unsigned long long)cur.w[j]);
-              found = pass;
+              S.found = pass;
             }
         }
         __syncthreads();
-        if (found != pass) break;
+        if (S.found != pass) break;
         grew = true;
         old = have;
         for (int w = wid; w < R; w += NT / kWave) {
           const uint64_t add = Dn[w] & ~D[w];
           if (lane == 0) D[w] |= add;
-          append(w, add);
+          append(&cnt[par], w, add);
         }
         __syncthreads();
         have = cnt[par];
       }
+      par ^= 1;
       if (!grew) continue;
       // apply: {a, u} for every u in D
       any_sweep = true;
@@ -480,15 +575,35 @@ __global__ void __launch_bounds__(NT) k_dom_edge_run(uint64_t *__restrict__ st, 
     ++sweeps;
   }
   if (LDS)
-    for (int i = tid; i < n * R; i += NT) st[i] = sRows[i];
-  if (deleted) atomicAdd(&nd, deleted);
+    for (int i = tid; i < n * R; i += NT) st[i] = S.rows[i];
+  if (deleted) atomicAdd(&S.nd, deleted);
   __syncthreads();
   if (tid == 0) {
-    h->de = (long long)nd;
+    h->de = (long long)S.nd;
     h->sweeps = sweeps;
     h->events = h->de;
     h->passes = passes;
   }
+}
+
+template <int NT, int GL, int WPL, bool LDS>
+__global__ void __launch_bounds__(NT) k_dom_edge_run(uint64_t *__restrict__ st, int n, int R, DomHdr *h) {
+  __shared__ EdgeLds<LDS> S;
+  const int tid = threadIdx.x;
+  if (h->prio != P_NONE) return;
+  if (LDS)
+    for (int i = tid; i < n * R; i += NT) S.rows[i] = st[i];
+  if (tid == 0) {
+    S.cnt[0] = S.cnt[1] = S.near[0] = S.near[1] = 0;
+    S.found = -1;
+    S.nd = 0;
+  }
+  __syncthreads();
+  // a thin graph's steps look at their node first (what that takes is 6 to 20 % of
+  // the short steps of dense graphs)
+  const double mean = (double)h->dirs / n;
+  if (mean * mean < n) dom_edge_sweeps<NT, GL, WPL, LDS, true>(st, n, R, h, S);
+  else dom_edge_sweeps<NT, GL, WPL, LDS, false>(st, n, R, h, S);
 }
 
 int dom_status(int prio) {
@@ -534,25 +649,38 @@ int kz_dominance(kz_ctx *ctx, int32_t mode, int32_t n, const uint64_t *rows, int
   const long long words = (long long)n * R;
   const int grid = (int)std::min<long long>((words + 255) / 256, 4096);
   hipLaunchKernelGGL(k_dom_setup, dim3(grid), dim3(256), 0, s, rows, emask, vmask, n, R, h);
-  // rows in LDS where they fit; a group of 4 to 64 lanes a row, several words
-  // a lane beyond 64; fewer waves at the barriers where the rows are short
-#define KZ_DOM(NT, GL, WPL, LDS)                                                                                 \
-  do {                                                                                                           \
-    if (mode == KZ_DOM_VERTEX)                                                                                   \
-      hipLaunchKernelGGL((k_dom_vertex_run<NT, GL, WPL, LDS>), dim3(1), dim3(NT), 0, s, emask, vmask, n, R, h);  \
-    else                                                                                                         \
-      hipLaunchKernelGGL((k_dom_edge_run<NT, GL, WPL, LDS>), dim3(1), dim3(NT), 0, s, emask, n, R, h);           \
+  // rows in LDS where they fit; a group of 1 to 64 lanes a row, several words
+  // a lane beyond 64; fewer waves at the barriers where the rows are short (64
+  // nodes at p = 0.5, edges: 0.92 ms with 64 groups of 4 lanes, 0.24 with a lane a
+  // row and one wave; 100 nodes at p = 0.1: 1.4 and 0.94 with 2 lanes)
+#define KZ_DOM_V(NT, GL, WPL, LDS) \
+  hipLaunchKernelGGL((k_dom_vertex_run<NT, GL, WPL, LDS>), dim3(1), dim3(NT), 0, s, emask, vmask, n, R, h)
+#define KZ_DOM_E(NT, GL, WPL, LDS) \
+  hipLaunchKernelGGL((k_dom_edge_run<NT, GL, WPL, LDS>), dim3(1), dim3(NT), 0, s, emask, n, R, h)
+#define KZ_DOM(NT, GL, WPL, LDS)                          \
+  do {                                                    \
+    if (mode == KZ_DOM_VERTEX) KZ_DOM_V(NT, GL, WPL, LDS); \
+    else KZ_DOM_E(NT, GL, WPL, LDS);                      \
   } while (0)
   if (words <= kDomLdsWords && R <= kDomLdsR) {
-    if (R <= 4) KZ_DOM(256, 4, 1, true);
+    if (R == 1) KZ_DOM(64, 1, 1, true);
+    else if (R == 2) KZ_DOM(256, 2, 1, true);
+    else if (R <= 4) KZ_DOM(256, 4, 1, true);
     else if (R <= 8) KZ_DOM(512, 8, 1, true);
     else if (R <= 16) KZ_DOM(1024, 16, 1, true);
     else KZ_DOM(1024, 32, 1, true);
   } else if (R <= 32) KZ_DOM(1024, 32, 1, false);
-  else if (R <= 64) KZ_DOM(1024, 64, 1, false);
-  else if (R <= 256) KZ_DOM(1024, 64, 4, false);
+  else if (R <= 64) {
+    // twice the groups for the edges; a vertex step that deletes drops the others'
+    // work (twins 15 ms, 20 with 32 groups)
+    if (mode == KZ_DOM_VERTEX) KZ_DOM_V(1024, 64, 1, false);
+    else KZ_DOM_E(1024, 32, 2, false);
+  } else if (R <= 256) KZ_DOM(1024, 64, 4, false);
+  else if (R <= 512) KZ_DOM(1024, 64, 8, false);
   else KZ_DOM(1024, 64, 16, false);
 #undef KZ_DOM
+#undef KZ_DOM_V
+#undef KZ_DOM_E
   DomHdr *hh = (DomHdr *)ctx->pinned;
   if (hipGetLastError() != hipSuccess ||
       hipMemcpyAsync(hh, h, sizeof(DomHdr), hipMemcpyDeviceToHost, s) != hipSuccess ||
