@@ -161,6 +161,25 @@ def test_dense_graphs_lose_their_twins(n, p):
         kz.close()
 
 
+@pytest.mark.parametrize("n", [2049, 4097, 17000])
+def test_a_step_deletes_nearly_all(n):
+    """Nodes all next to the same three: the first takes all the others, with their
+    edges, and of the three the first then takes the others."""
+    R = (n + 63) // 64
+    hubs = (5, 70, n - 1)
+    nbr = {v: set(hubs) for v in range(n) if v not in hubs}
+    nbr.update({h: set(nbr) - set(hubs) for h in hubs})
+    kz = Kernelizer(0)
+    try:
+        print("dominance nearly all", n, flush=True)
+        vm, em, res = kz.dominance(torch.from_numpy(pack(n, R, nbr).view(np.int64)).cuda(), KZ_DOM_VERTEX)
+        assert np.flatnonzero(vm.cpu().numpy()).tolist() == [0, 5]
+        assert np.array_equal(em.cpu().numpy().view(np.uint64), pack(n, R, {0: {5}, 5: {0}}))
+        assert (res["sweeps"], res["events"], res["deleted_edges"]) == (1, 2, 3 * (n - 4) + 2)
+    finally:
+        kz.close()
+
+
 def test_a_star_takes_few_turns():
     n = 2100
     nbr = {0: set(range(1, n)), **{v: {0} for v in range(1, n)}}
