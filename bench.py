@@ -1087,7 +1087,7 @@ def run_colouring(args):
     return {"metric": "colouring time", "value": out["n20000"]["ms"], "unit": "ms", "higher_is_better": False,
             "config": {"workload": "colouring: " + WORKLOADS["colouring"], "seed": args.seed},
             "graphs": out, "oracle_equal": out["n3000"].get("oracle_equal"),
-            "note": "each round is two launches and one readback: launch-latency bound (us_per_round)"}
+            "note": "one blocking call; us_per_round: its time over the rounds"}
 
 
 # --------------------------------------------------------------- dominance

@@ -461,7 +461,10 @@ typedef enum {
   KZ_KERNEL_COUNT = 6
 } kz_kernel;
 
-/* Turns timing on (on != 0) or off; clears the accumulated times. */
+/* Turns timing on (on != 0) or off; clears the accumulated times.  While it is
+ * on, a small dense graph takes the kernels of the larger ones and not the
+ * single launch that it takes otherwise: the times are of those kernels.
+ * Results are the same. */
 int kz_profile_enable(kz_ctx *ctx, int on);
 
 /* Accumulated milliseconds and launch count of one kernel family. */

@@ -359,7 +359,7 @@ bool small_call(const kz_ctx *ctx, const kz_graph *g, int32_t k, const kzi::WsSi
 
 // Enqueues setup (first_pass == 1) and passes [first_pass, first_pass +
 // npasses) of the single-graph path, each ended on the device by
-// k_pass_end, then (dense input) the output unpack, which writes only at
+// pass_end, then (dense input) the output unpack, which writes only at
 // the fixpoint.  No host synchronisation: the whole call can be captured.
 int enqueue_passes(kz_ctx *ctx, const kz_graph *g, const int32_t *colour, int32_t k, char *base,
                    const kzi::WsSizes &z, bool mfma, uint8_t *vmask, void *emask, int first_pass, int npasses,

@@ -1335,7 +1335,10 @@ __global__ void __launch_bounds__(NW * 64, 4) k_batch(BatchArgs a) {
 // vertices, p = 0.2..0.8, those with lam in 0.03 .. 0.3 run 8 to 16 passes on
 // average and up to 119, the others 2 to 7; a long cascade that starts late
 // keeps the launch waiting: 18.0 ms in order of size, 15.0 ms in this order,
-// 14.7 ms in order of the true number of passes.
+// 14.7 ms in order of the true number of passes.  lam knows nothing of a clique
+// size below the number of classes, where an edge survives that many empty
+// ones: 512 such graphs of two less take the same in this order and as given
+// (9.40 and 9.36 ms, 9.65 and 9.63), few graphs for the chip's workgroups.
 constexpr int kCostRows = 16;
 __global__ void __launch_bounds__(64) k_batch_cost(BatchArgs a) {
   const int g = blockIdx.x, lane = threadIdx.x;

@@ -226,8 +226,9 @@ __global__ void __launch_bounds__(256) k_csr_first(Plan p, const int64_t *rp, co
       }
       // Symmetry: every entry (u,v) with v > u must have its reverse (v,u),
       // found by binary search in row v; with as many entries below the
-      // diagonal as above it (summed on the host), reversal then maps the
-      // upper entries onto the lower ones, so the lower ones need no search.
+      // diagonal as above it (summed on the device at the pass's end), reversal
+      // then maps the upper entries onto the lower ones, so the lower ones need
+      // no search.
       if (v < u) {
         --balance;
         continue;

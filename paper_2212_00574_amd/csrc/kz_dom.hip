@@ -104,7 +104,7 @@ __global__ void __launch_bounds__(256) k_dom_setup(const uint64_t *__restrict__ 
 // few rows, as the graphs are dense.  What bounds it is the chain of LDS or
 // L2 reads of a step.  Edge mode on the evaluation recipe at 1100 nodes (rows
 // in LDS) 73.9 -> 11.0 ms, at 1900 (rows in L2) 271 -> 26.8 ms; vertex mode
-// 2.6 -> 0.87 and 5.5 -> 2.8 ms; the earlier form tested node by node, a
+// 2.6 -> 0.87 and 5.5 -> 1.9 ms; the earlier form tested node by node, a
 // chain of dependent loads per test.
 constexpr int kDomLdsWords = 19840;  // rows kept in LDS up to this many words ...
 constexpr int kDomLdsR = 32;         // ... and this row width (then at most 1102 nodes)

@@ -110,7 +110,7 @@ struct Hdr {
   // counters).  Workgroups add into slot (id % kCtrSlots) so that thousands
   // of same-address atomics do not serialise; each slot is one 128-byte
   // cache line holding both parities (atomics on one line serialise too);
-  // k_pass_end sums the slots.
+  // pass_end sums the slots.
   unsigned long long ctrw[kCtrSlots][kCtrStride];
   __host__ __device__ unsigned long long &ctr(int par, int slot, int j) { return ctrw[slot][par * 4 + j]; }
   __host__ __device__ const unsigned long long &ctr(int par, int slot, int j) const {
@@ -122,7 +122,7 @@ struct Hdr {
   int bad_layout;        // stage 1: bitset colours unsorted / row stride mismatch
   int R;                 // words per row == number of 64-slot blocks
   int n, k, pad;
-  // the pass loop's state on the device (k_pass_end): set once a pass
+  // the pass loop's state on the device (pass_end): set once a pass
   // removed nothing or pass 1 found an input error; every later pass kernel
   // of the run then returns at once
   int done, pad2;

@@ -305,7 +305,7 @@ __global__ void __launch_bounds__(256) k_pack_dense(Plan p, const uint8_t *adj, 
 // (lane v = slot 64*block + v) and its 4 waves split the classes (wave w
 // walks c = w, w+4, ...); only alive vertices touched by the previous round
 // are tested.  For each tested row it also refreshes the first-word matrix
-// F[v*k + c] (the first word of row v's class-c segment), which the edge
+// F[v*kF + c] (the first word of row v's class-c segment), which the edge
 // pass tests first.  Also resets the bookkeeping the edge pass of this pass
 // fills.
 __global__ void __launch_bounds__(256) k_vertex(Plan p, const int *scls, const uint64_t *__restrict__ src,
@@ -678,7 +678,7 @@ __device__ __forceinline__ void tile_finish(const Plan &p, uint64_t *__restrict_
 // meet no bank conflict.  Per two classes a wave issues 8 MFMAs (256 cycles
 // of the matrix cores) and 112 vector instructions (448 cycles), 64 of them
 // the minima: vector issue bounds it.  Measured at 20 classes of 1000, p =
-// 0.3: 242 us, of which about 86 us pass without the product and the search
+// 0.3: 255 us, of which about 86 us pass without the product and the search
 // (652 us before, with a ballot per row and class over 64 lanes of which 30 %
 // held an edge; 10 classes of 800 at p = 0.2: 219 -> 78 us).  Three waves a
 // SIMD (CH <= 20, 51 KB of LDS) against two: 274 and 337 us.  All words of
@@ -986,7 +986,7 @@ __global__ void __launch_bounds__(kEdgeThreads) k_edge_mf(Plan p, const uint64_t
 // 256 rows to bytes in LDS (double-buffered) and each wave accumulates a
 // 64 x 64 quarter with 32x32x32 int8 MFMAs.  A class with a zero count marks
 // the pair in the fail bits `fb` (same layout as the rows; words of block Y
-// and Y+1 in the rows of blocks X and X+1); k_edge<.., true> turns them
+// and Y+1 in the rows of blocks X and X+1); k_edge_mf turns them
 // into the next state with the usual worklist and counter epilogue.
 typedef int mf_v4i __attribute__((ext_vector_type(4)));
 typedef int mf_v16i __attribute__((ext_vector_type(16)));
