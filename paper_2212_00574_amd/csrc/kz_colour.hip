@@ -34,6 +34,7 @@
 // rounds, and others the first few of them, from which rounds_left tells how many
 // are to come (1.7 ms for that bipartite graph; 3000 vertices at p = 0.3, by blocks:
 // 0.84 ms with and without).
+#include <stddef.h>
 #include <string.h>
 
 #include <algorithm>
@@ -58,21 +59,29 @@ constexpr int kColLdsColours = 64 * kColLdsWords;
 constexpr int kColLdsN = 16384;             // vertices up to which colours and rounds are kept in LDS
 constexpr int kRankThreads = 256, kRankSpan = 256;  // vertices ranked, and compared with, by a workgroup
 
+constexpr size_t kColHead = 256;            // bytes of the counters before the sums
+
 struct ColCtr {
   int left;     // rounds: vertices not yet coloured; every round kernel returns at once at 0
   int bad;      // validation: a KZ_* status, most severe first (see k_col_check)
   int top;      // largest colour given
   int rounds;   // rounds
   unsigned long long gone;  // edges with an end coloured (rounds, where counted)
-  // sums of the degrees and of their squares, over slots of a line each: a
-  // graph's thousands of workgroups would queue at one
+  char pad[kColHead - 24];
+  // sums of the degrees and of their squares, over slots (col_slots) of a line
+  // each: a graph's thousands of workgroups would queue at one.  They lie where
+  // the greedy pass writes its order later (ColWs), so the workspace holds no more.
   struct alignas(64) {
     unsigned long long ends, squares;
   } sum[kColSlots];
 };
 static_assert(sizeof(ColCtr) <= kzi::kPinnedBytes, "read back into the context's pinned memory");
+static_assert(offsetof(ColCtr, sum) == kColHead && kColHead % kColAlign == 0, "the sums take the order's place");
 
 size_t col_up(size_t x) { return (x + kColAlign - 1) / kColAlign * kColAlign; }
+
+// slots of the sums: as many as the order of n vertices has room for
+int col_slots(int n) { return (int)std::min<size_t>(kColSlots, col_up(sizeof(int) * (size_t)n) / 64); }
 
 // words of a bitmap of colours beyond those in LDS (a vertex's smallest free
 // colour is at most n - 1)
@@ -90,11 +99,11 @@ ColWs col_ws(int n) {
     o += col_up(b);
     return at;
   };
-  w.ctr = take(sizeof(ColCtr));
+  w.ctr = take(kColHead);
+  w.order = take(sizeof(int) * (size_t)n);  // behind the counters: see ColCtr
   w.U = take(sizeof(uint64_t) * (size_t)((n + 63) / 64));
   w.sel = take((size_t)n);
   w.rank = take(sizeof(int) * (size_t)n);
-  w.order = take(sizeof(int) * (size_t)n);
   w.val = take(n > kColLdsN ? sizeof(unsigned) * (size_t)n : 0);
   w.used = take(2 * 64 * sizeof(uint64_t) * (size_t)col_more(n));
   w.total = o;
@@ -110,7 +119,8 @@ __device__ __forceinline__ bool key_beats(unsigned long long pu, int u, unsigned
 // most severe found wins (EINVAL, then ESELFLOOP, then EASYM).  rank = 0,
 // colour = -1, U = every vertex.
 __global__ void __launch_bounds__(kColWaves * 64) k_col_check(int n, const uint64_t *__restrict__ rows, int R,
-                                                              int *rank, int *colour, uint64_t *U, ColCtr *ctr) {
+                                                              int *rank, int *colour, uint64_t *U, ColCtr *ctr,
+                                                              int slots) {
   __shared__ unsigned long long ends, squares;
   if (threadIdx.x == 0) ends = squares = 0;
   __syncthreads();
@@ -148,7 +158,7 @@ __global__ void __launch_bounds__(kColWaves * 64) k_col_check(int n, const uint6
   }
   __syncthreads();
   if (threadIdx.x == 0 && ends) {
-    auto &sum = ctr->sum[blockIdx.x % kColSlots];
+    auto &sum = ctr->sum[blockIdx.x % (unsigned)slots];
     atomicAdd(&sum.ends, ends);
     atomicAdd(&sum.squares, squares);
   }
@@ -576,9 +586,11 @@ int kz_colour_jp(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
   ColCtr *h = (ColCtr *)ctx->pinned;  // the context's pinned readback buffer (4 KiB)
   const dim3 grid((unsigned)((n + kColWaves - 1) / kColWaves)), block(kColWaves * 64);
   const unsigned blocks = (unsigned)((n + kRankThreads - 1) / kRankThreads);
-  auto read_back = [&]() {
+  const int slots = col_slots(n);
+  const size_t sums = kColHead + slots * sizeof(ctr->sum[0]);
+  auto read_back = [&](size_t bytes) {
     return hipGetLastError() == hipSuccess &&
-           hipMemcpyAsync(h, ctr, sizeof(ColCtr), hipMemcpyDeviceToHost, s) == hipSuccess &&
+           hipMemcpyAsync(h, ctr, bytes, hipMemcpyDeviceToHost, s) == hipSuccess &&
            hipStreamSynchronize(s) == hipSuccess;
   };
   int ran = 0;  // rounds enqueued
@@ -589,20 +601,20 @@ int kz_colour_jp(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
     }
     ran += rounds;
   };
-  if (hipMemsetAsync(ctr, 0, sizeof(ColCtr), s) != hipSuccess) return done();
-  hipLaunchKernelGGL(k_col_check, grid, block, 0, s, n, rows, (int)row_words, rank, colour, U, ctr);
+  if (hipMemsetAsync(ctr, 0, sums, s) != hipSuccess) return done();
+  hipLaunchKernelGGL(k_col_check, grid, block, 0, s, n, rows, (int)row_words, rank, colour, U, ctr, slots);
   // the first rounds go out with the check, as many as a share of the blocks'
   // time allows whatever the edges
   ColDegrees d{n, 0, 0};
   if (n >= kColProbeN) enqueue(std::max(1, d.probe(kColProbe)), true);
-  if (!read_back()) return done();
+  if (!read_back(sums)) return done();
   if (h->bad) {
     r.status = h->bad == 3 ? KZ_EINVAL : h->bad == 2 ? KZ_ESELFLOOP : KZ_EASYM;
     return done();
   }
-  for (const auto &x : h->sum) {
-    d.ends += x.ends;
-    d.squares += x.squares;
+  for (int i = 0; i < slots; ++i) {
+    d.ends += h->sum[i].ends;
+    d.squares += h->sum[i].squares;
   }
   const bool sparse = d.sparse();
   const int probe = d.probe(kColProbeHubs);
@@ -630,7 +642,7 @@ int kz_colour_jp(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
     last = next;
     enqueue(next, !sparse);
     chunk = std::min(2 * chunk, kColMaxChunk);
-    if (!read_back()) return done();
+    if (!read_back(kColHead)) return done();
   }
   hipLaunchKernelGGL(k_col_rank, dim3(blocks, (unsigned)((n + kRankSpan - 1) / kRankSpan)), dim3(kRankThreads), 0, s, n,
                      priority, rank);
@@ -641,7 +653,7 @@ int kz_colour_jp(kz_ctx *ctx, int32_t n, const uint64_t *rows, int32_t row_words
   else
     hipLaunchKernelGGL(k_col_greedy<false>, dim3(1), dim3(kColThreads), 0, s, n, rows, (int)row_words, order, val, used,
                        col_more(n), colour, ctr);
-  if (!read_back()) return done();
+  if (!read_back(kColHead)) return done();
   r.status = KZ_OK;
   r.rounds = h->rounds;
   r.colours = h->top + 1;
